@@ -765,8 +765,8 @@ int aiwc_rf_predict(const aiwc_rf_forest* f, int32_t forest_index, const uint8_t
     const int32_t nt = f->params[forest_index].num_trees;
     const int64_t t0 = f->first_task[forest_index];
     require_fitted(f);
-    DevBuf<int64_t> sum((size_t)n, s);
-    launch_predict(f->nodes.p, f->node_base.p, (int32_t)t0, (int32_t)(t0 + nt), codes, n, f->n_cols, sum.p,
+    DevBuf<int64_t> sum(predict_by_row(trees_of(f, forest_index), n, nt) ? 0 : (size_t)n, s);
+    launch_predict(trees_of(f, forest_index), (int32_t)t0, (int32_t)(t0 + nt), codes, n, f->n_cols, sum.p,
                    y_log10_out, nt, s);
   });
 }
@@ -787,7 +787,7 @@ int aiwc_rf_predict_noalloc(const aiwc_rf_forest* f, int32_t forest_index, const
     const int64_t t0 = f->first_task[forest_index];
     require_fitted(f);
     // the same kernels as aiwc_rf_predict, with the row sums in the fixed array
-    launch_predict(f->nodes.p, f->node_base.p, (int32_t)t0, (int32_t)(t0 + nt), codes, n, f->n_cols,
+    launch_predict(trees_of(f, forest_index), (int32_t)t0, (int32_t)(t0 + nt), codes, n, f->n_cols,
                    noalloc_predict_scratch(), y_log10_out, nt, s);
   });
 }
@@ -804,7 +804,7 @@ int aiwc_rf_predict_sum(const aiwc_rf_forest* f, int32_t forest_index, int32_t t
     hipStream_t s = as_stream(stream);
     const int64_t t0 = f->first_task[forest_index];
     require_fitted(f);
-    launch_predict(f->nodes.p, f->node_base.p, (int32_t)(t0 + tree_begin), (int32_t)(t0 + tree_end), codes, n,
+    launch_predict(trees_of(f, forest_index), (int32_t)(t0 + tree_begin), (int32_t)(t0 + tree_end), codes, n,
                    f->n_cols, sum_out, nullptr, nt, s);
   });
 }
@@ -939,10 +939,11 @@ int aiwc_rf_select_device(const aiwc_rf_forest* f, int32_t forest_index, const u
     const int64_t t0 = f->first_task[forest_index];
     require_fitted(f);
     const int64_t rows = m * D;
-    DevBuf<uint8_t> expanded((size_t)(rows * f->n_cols), s);
-    DevBuf<int64_t> sum((size_t)rows, s);
+    const bool by_row = predict_by_row(trees_of(f, forest_index), rows, nt);
+    DevBuf<uint8_t> expanded(by_row ? 0 : (size_t)(rows * f->n_cols), s);
+    DevBuf<int64_t> sum(by_row ? 0 : (size_t)rows, s);
     DevBuf<double> times_tmp(times_out ? 0 : (size_t)rows, s);
-    launch_select_device(f->nodes.p, f->node_base.p, (int32_t)t0, (int32_t)(t0 + nt), feature_codes, m, f->n_cols, D,
+    launch_select_device(trees_of(f, forest_index), (int32_t)t0, (int32_t)(t0 + nt), feature_codes, m, f->n_cols, D,
                          nt, expanded.p, sum.p, times_out ? times_out : times_tmp.p, best_out, s);
   });
 }

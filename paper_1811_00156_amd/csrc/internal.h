@@ -305,6 +305,18 @@ bool launch_fit_graph(const GrowConfig& cfg, const GrowLaunch& g, const uint8_t*
                       const int32_t* d_n_bins, const double* y, int64_t* y_fp, uint32_t* d_status, int32_t mtry_max,
                       int grid, hipStream_t s);
 
+// The grown trees of a fit, as traversal reads them: the node pool, and per task
+// its first node and node count; train_rows: the rows they were grown on.
+struct TreesView {
+  const uint64_t* nodes;
+  const int64_t* node_base;
+  const int32_t* n_nodes;
+  int32_t train_rows;
+};
+inline TreesView trees_of(const aiwc_rf_forest* f, int32_t forest_index) {
+  return {f->nodes.p, f->node_base.p, f->n_nodes.p, f->n_train[(size_t)forest_index]};
+}
+
 // oob.hip: out-of-bag sums of every training row of forests [f0, f1), then
 // the squared and absolute errors of the out-of-bag predictions per forest.
 struct OobForest {
@@ -337,16 +349,21 @@ constexpr int64_t kNoAllocPredictRows = int64_t(1) << 20;
 // That array's address on the current device (looked up once per device with
 // hipGetSymbolAddress, then cached); allocates nothing.
 int64_t* noalloc_predict_scratch();
-void launch_predict(const uint64_t* nodes, const int64_t* node_base, int32_t tree_begin, int32_t tree_end,
-                    const uint8_t* codes, int64_t n, int32_t C, int64_t* sum, double* y, int32_t num_trees,
-                    hipStream_t s);
+void launch_predict(const TreesView& F, int32_t tree_begin, int32_t tree_end, const uint8_t* codes, int64_t n,
+                    int32_t C, int64_t* sum, double* y, int32_t num_trees, hipStream_t s);
+// Whether a prediction of n rows goes one workgroup per row: it then writes y
+// itself and needs no row sums (`sum` may be null), and a device selection of
+// as many (kernel, device) rows needs no expanded codes.
+bool predict_by_row(const TreesView& F, int64_t n, int32_t n_trees);
+// Lets a kernel take all of the device's LDS as dynamic LDS (set once per device).
+void allow_lds(const void* kernel);
 
 void launch_rank_accuracy(const double* times, const double* truth, int64_t m, int32_t D, int32_t* correct,
                           int32_t* counted, int32_t* hit, hipStream_t s);
 
-void launch_select_device(const uint64_t* nodes, const int64_t* node_base, int32_t tree_begin, int32_t tree_end,
-                          const uint8_t* feature_codes, int64_t m, int32_t C, int32_t n_devices, int32_t num_trees,
-                          uint8_t* expanded, int64_t* sum, double* times, int32_t* best, hipStream_t s);
+void launch_select_device(const TreesView& F, int32_t tree_begin, int32_t tree_end, const uint8_t* feature_codes,
+                          int64_t m, int32_t C, int32_t n_devices, int32_t num_trees, uint8_t* expanded, int64_t* sum,
+                          double* times, int32_t* best, hipStream_t s);
 
 // Device properties of the current device (cached).
 struct DeviceInfo {

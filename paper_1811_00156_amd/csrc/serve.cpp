@@ -159,7 +159,7 @@ void aiwc_rf_server::launch(Slot& s, std::vector<Request>&& batch, int64_t first
   s.reqs = std::move(batch);
   uint8_t* dc = d_codes + first * n_cols;
   AIWC_HIP(hipMemcpyAsync(dc, hc, (size_t)(rows * n_cols), hipMemcpyHostToDevice, s.stream));
-  launch_predict(forest->nodes.p, forest->node_base.p, (int32_t)t0, (int32_t)(t0 + num_trees), dc, rows, n_cols,
+  launch_predict(trees_of(forest, forest_index), (int32_t)t0, (int32_t)(t0 + num_trees), dc, rows, n_cols,
                  d_sum + first, d_out + first, num_trees, s.stream);
   AIWC_HIP(hipMemcpyAsync(h_out + first, d_out + first, sizeof(double) * (size_t)rows, hipMemcpyDeviceToHost,
                           s.stream));

@@ -1,0 +1,81 @@
+"""Prediction kernels at the edges of their dispatch: rows per workgroup, tree
+chunks, row strides and alignments.  Sums of integers and one rounding: the
+answers equal the oracle's bit for bit."""
+import numpy as np
+import pytest
+
+from tests._gpu import log, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rf():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1811_00156_amd import rf as _rf
+
+    return _rf
+
+
+def _fitted(rf, oracle, C, n, trees, bins, seed, mtry=None):
+    rng = np.random.default_rng(seed)
+    codes = rng.integers(0, bins, (n, C)).astype(np.uint8)
+    y = rng.normal(0.0, 1.0, n)
+    nb = np.full(C, bins, np.int32)
+    mtry = mtry or max(1, C // 3)
+    forest = rf.aiwc_rf_fit(to_dev(codes), rf.aiwc_rf_binner_from_counts(nb), to_dev(y),
+                            rf.make_params(trees, mtry, 2, True, seed))
+    return forest, oracle.fit(codes, nb, y, trees, mtry, 2, seed=seed), rng
+
+
+# rows x trees on both sides of the per-row kernel's limit (1024 rows, 2^18 pairs),
+# whole and broken workgroups of 256 rows, one chunk of trees and many; columns
+# with even and odd row strides, and the widest row (255 columns)
+@pytest.mark.parametrize("C,trees,rows", [
+    (2, 1, (1, 1024, 1025, 1280)), (35, 9, (1, 255, 1023, 1024, 1025, 5000, 29128)),
+    (64, 300, (3, 873, 874, 1000, 4097)), (65, 1030, (1, 254, 255, 300, 513)), (255, 20, (7, 1024, 1025, 1300)),
+])
+def test_predict_paths(rf, oracle, C, trees, rows):
+    import torch
+
+    log(f"predict paths C={C} trees={trees}")
+    forest, of, rng = _fitted(rf, oracle, C, 700, trees, 61, C)
+    q = rng.integers(0, 256, (max(rows), C)).astype(np.uint8)
+    P, yhat = oracle.predict(of, q)
+    dq = to_dev(q)
+    for n in rows:
+        assert np.array_equal(rf.aiwc_rf_predict(forest, dq[:n]).cpu().numpy(), yhat[:n]), n
+        lo = trees // 3
+        s = rf.aiwc_rf_predict_sum(forest, dq[:n], 0, max(1, lo)).cpu().numpy()
+        if lo >= 1:
+            s = s + rf.aiwc_rf_predict_sum(forest, dq[:n], lo, trees).cpu().numpy()
+        assert np.array_equal(s, P[:n]), n
+        # codes that start at an odd address
+        flat = torch.empty(n * C + 1, dtype=torch.uint8, device="cuda")
+        off = flat[1:].view(n, C)
+        off.copy_(dq[:n])
+        assert np.array_equal(rf.aiwc_rf_predict(forest, off).cpu().numpy(), yhat[:n]), n
+
+
+# (kernel, device) rows below and above the per-row kernel's limit
+@pytest.mark.parametrize("D,m", [(1, 5), (15, 4), (15, 68), (15, 69), (32, 100)])
+def test_select_paths(rf, oracle, D, m):
+    log(f"select paths D={D} m={m}")
+    rng = np.random.default_rng(D + m)
+    n, C = 600, 12
+    codes = rng.integers(0, 40, (n, C)).astype(np.uint8)
+    codes[:, -1] = rng.integers(0, D, n)
+    nb = np.array([40] * (C - 1) + [D], np.int32)
+    y = rng.normal(0.0, 1.0, n)
+    forest = rf.aiwc_rf_fit(to_dev(codes), rf.aiwc_rf_binner_from_counts(nb), to_dev(y), rf.make_params(30, 5, 3, True, 4))
+    of = oracle.fit(codes, nb, y, 30, 5, 3, seed=4)
+    feat = rng.integers(0, 40, (m, C - 1)).astype(np.uint8)
+    best, times = rf.aiwc_rf_select_device(forest, to_dev(feat), n_devices=D)
+    rows = np.concatenate([np.repeat(feat, D, axis=0), np.tile(np.arange(D, dtype=np.uint8), m)[:, None]], axis=1)
+    _, yhat = oracle.predict(of, rows)
+    yhat = yhat.reshape(m, D)
+    assert np.array_equal(times.cpu().numpy(), yhat)
+    assert np.array_equal(best.cpu().numpy(), yhat.argmin(axis=1))
