@@ -822,7 +822,7 @@ int aiwc_rf_oob_error(const aiwc_rf_forest* f, int32_t forest_begin, int32_t for
     const int32_t nf = forest_end - forest_begin;
     std::vector<OobForest> fr((size_t)nf);
     int64_t rows = 0;
-    int32_t max_n = 1;
+    int32_t max_n = 1, max_trees = 1;
     for (int32_t k = 0; k < nf; ++k) {
       const int32_t fi = forest_begin + k;
       fr[k].first_task = f->first_task[fi];
@@ -831,6 +831,7 @@ int aiwc_rf_oob_error(const aiwc_rf_forest* f, int32_t forest_begin, int32_t for
       fr[k].train_off = f->train_off[fi];
       fr[k].row_off = rows;
       rows += f->n_train[fi];
+      max_trees = std::max(max_trees, fr[k].num_trees);
       max_n = std::max(max_n, f->n_train[fi]);
     }
     DevBuf<OobForest> d_fr((size_t)nf, s);
@@ -840,8 +841,8 @@ int aiwc_rf_oob_error(const aiwc_rf_forest* f, int32_t forest_begin, int32_t for
     const int32_t blocks = (max_n + 255) / 256;
     DevBuf<double> partial((size_t)3 * nf * blocks, s);
     DevBuf<double> result((size_t)3 * nf, s);
-    launch_oob(f->nodes.p, f->d_tasks.p, f->node_base.p, f->inbag.p, f->train_rows.p, d_fr.p, nf, max_n, codes,
-               f->n_cols, y_log10, oob_sum_out ? oob_sum_out : sum_tmp.p, oob_count_out ? oob_count_out : cnt_tmp.p,
+    launch_oob(trees_of(f, forest_begin), f->d_tasks.p, f->inbag.p, f->train_rows.p, d_fr.p, nf, max_n, max_trees,
+               rows, codes, f->n_cols, y_log10, oob_sum_out ? oob_sum_out : sum_tmp.p, oob_count_out ? oob_count_out : cnt_tmp.p,
                partial.p, result.p, s);
     std::vector<double> res((size_t)3 * nf);
     AIWC_HIP(hipMemcpyAsync(res.data(), result.p, sizeof(double) * res.size(), hipMemcpyDeviceToHost, s));
@@ -867,7 +868,7 @@ int aiwc_rf_heldout_error(const aiwc_rf_forest* f, int32_t forest_begin, int32_t
     const int32_t nf = forest_end - forest_begin;
     std::vector<OobForest> fr((size_t)nf);
     int64_t rows = 0;
-    int32_t max_n = 0;
+    int32_t max_n = 0, max_trees = 1;
     for (int32_t k = 0; k < nf; ++k) {
       const int32_t fi = forest_begin + k;
       fr[k].first_task = f->first_task[fi];
@@ -876,6 +877,7 @@ int aiwc_rf_heldout_error(const aiwc_rf_forest* f, int32_t forest_begin, int32_t
       fr[k].train_off = f->test_off[fi];
       fr[k].row_off = rows;
       rows += f->n_test[fi];
+      max_trees = std::max(max_trees, fr[k].num_trees);
       max_n = std::max(max_n, f->n_test[fi]);
     }
     std::vector<double> res((size_t)3 * nf, 0.0);
@@ -887,8 +889,8 @@ int aiwc_rf_heldout_error(const aiwc_rf_forest* f, int32_t forest_begin, int32_t
       const int32_t blocks = std::max(1, (max_n + 255) / 256);
       DevBuf<double> partial((size_t)3 * nf * blocks, s);
       DevBuf<double> result((size_t)3 * nf, s);
-      launch_heldout(f->nodes.p, f->node_base.p, f->test_rows.p, d_fr.p, nf, max_n, codes, f->n_cols, y_log10,
-                     pred_sum_out ? pred_sum_out : sum_tmp.p, cnt.p, partial.p, result.p, s);
+      launch_heldout(trees_of(f, forest_begin), f->test_rows.p, d_fr.p, nf, max_n, max_trees, rows, codes, f->n_cols,
+                     y_log10, pred_sum_out ? pred_sum_out : sum_tmp.p, cnt.p, partial.p, result.p, s);
       AIWC_HIP(hipMemcpyAsync(res.data(), result.p, sizeof(double) * res.size(), hipMemcpyDeviceToHost, s));
     }
     AIWC_HIP(hipStreamSynchronize(s));

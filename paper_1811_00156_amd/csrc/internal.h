@@ -326,15 +326,15 @@ struct OobForest {
   int64_t train_off;  // -1 = rows 0 .. n_train-1
   int64_t row_off;    // first slot of this forest's rows in the per-row outputs
 };
-void launch_oob(const uint64_t* nodes, const TreeTask* tasks, const int64_t* node_base, const uint64_t* inbag,
-                const int32_t* train_rows, const OobForest* forests, int32_t n_forests, int32_t max_n_train,
+void launch_oob(const TreesView& T, const TreeTask* tasks, const uint64_t* inbag, const int32_t* train_rows,
+                const OobForest* forests, int32_t n_forests, int32_t max_n_train, int32_t max_trees, int64_t total,
                 const uint8_t* codes, int32_t C, const double* y, int64_t* sum, int32_t* count, double* partial,
                 double* result, hipStream_t s);
 // Held-out error: the same per-forest reduction over each forest's held-out
 // rows (OobForest.train_off / n_train name the held-out list in test_rows),
 // every row predicted by all of the forest's trees.
-void launch_heldout(const uint64_t* nodes, const int64_t* node_base, const int32_t* test_rows,
-                    const OobForest* forests, int32_t n_forests, int32_t max_n_test, const uint8_t* codes, int32_t C,
+void launch_heldout(const TreesView& T, const int32_t* test_rows, const OobForest* forests, int32_t n_forests,
+                    int32_t max_n_test, int32_t max_trees, int64_t total, const uint8_t* codes, int32_t C,
                     const double* y, int64_t* sum, int32_t* count, double* partial, double* result, hipStream_t s);
 
 // tune.cpp: the annealing search of aiwc_rf_tune_sa (arguments checked there).

@@ -8,62 +8,116 @@
 // index order), so the result does not depend on scheduling.
 #include "device.h"
 #include "internal.h"
+#include "traverse.h"
 
 namespace aiwc {
 namespace {
 
 constexpr int kOobBlock = 256;
 
-__global__ __launch_bounds__(kOobBlock) void k_oob_sums(const uint64_t* __restrict__ nodes,
-                                                        const TreeTask* __restrict__ tasks,
-                                                        const int64_t* __restrict__ node_base,
-                                                        const uint64_t* __restrict__ inbag,
-                                                        const int32_t* __restrict__ train_rows,
-                                                        const OobForest* __restrict__ forests,
-                                                        const uint8_t* __restrict__ codes, int32_t C,
-                                                        int64_t* __restrict__ sum, int32_t* __restrict__ count) {
+// Leaf sums and tree counts of a forest's rows: its training rows, each under
+// the trees that left it out (OOB), or its held-out rows under every tree.
+// A workgroup takes R rows of a forest and a chunk of its trees: the rows' codes
+// and their running sums lie in the LDS, and each wave takes trees of its own.
+// It lists the rows that the tree left out (a bitmap word per 64 rows), so that
+// every lane walks a row of it, K rows per lane at a time, with the tree's first
+// nodes in the wave's part of the LDS.  One thread per row and forest walking
+// every tree in turn, codes and nodes gathered from memory, took 11.7 ms for the
+// paper's frame and 2000 trees (nine workgroups) and 19.5 ms for the tuning
+// grid's 1700 forests; now 0.13 and 5.6 ms, bound by the latency of the walk's
+// dependent reads (128 nodes per tree in the LDS; 256 and 512 cost waves: 6.8
+// and 8.9 ms).
+constexpr int kScoreWaves = 8;
+constexpr uint32_t kScoreTop = 128;
+
+template <bool OOB>
+__global__ __launch_bounds__(kScoreWaves* kWave) void k_score(
+    const uint64_t* __restrict__ nodes, const TreeTask* __restrict__ tasks, const int64_t* __restrict__ node_base,
+    const int32_t* __restrict__ n_nodes, const uint64_t* __restrict__ inbag, const int32_t* __restrict__ row_list,
+    const OobForest* __restrict__ forests, const uint8_t* __restrict__ codes, int32_t C, int32_t R, int32_t n_chunks,
+    unsigned long long* __restrict__ sum, int32_t* __restrict__ count) {
+  extern __shared__ __align__(16) uint8_t lds[];
+  constexpr int BLOCK = kScoreWaves * kWave, K = 2;
   const OobForest F = forests[blockIdx.y];
-  const int64_t i = (int64_t)blockIdx.x * kOobBlock + threadIdx.x;
-  if (i >= F.n_train) return;
-  const int64_t row = F.train_off >= 0 ? train_rows[F.train_off + i] : i;
-  const uint8_t* rp = codes + row * C;
-  int64_t P = 0;
-  int32_t cnt = 0;
-  for (int32_t t = 0; t < F.num_trees; ++t) {
-    const int64_t off = tasks[F.first_task + t].inbag_off;
-    if (off < 0) continue;  // no bootstrap: every row is in bag
-    if ((inbag[off + i / kWave] >> (i % kWave)) & 1ull) continue;
-    const uint64_t* tn = nodes + node_base[F.first_task + t];
-    uint64_t v = tn[0];
-    while (node_col(v) != kLeafCol) v = tn[node_left(v) + (rp[node_col(v)] > node_bin(v) ? 1u : 0u)];
-    P += node_q(v);
-    ++cnt;
+  const int32_t r0 = (int32_t)blockIdx.x * R;
+  const int32_t nr = min(R, F.n_train - r0);
+  const int32_t chunk = (F.num_trees + n_chunks - 1) / n_chunks;
+  const int32_t t0 = (int32_t)blockIdx.z * chunk, t1 = min(F.num_trees, t0 + chunk);
+  if (nr <= 0 || (t0 >= t1 && t0 > 0)) return;
+  const int tid = (int)threadIdx.x, wid = tid / kWave, lane = (int)lane_id();
+  const uint32_t st = (uint32_t)staged_stride(C);
+  uint64_t* s_sum = reinterpret_cast<uint64_t*>(lds);                       // [R]
+  uint64_t* top = s_sum + R + (size_t)wid * kScoreTop;                          // [kScoreTop] of each wave
+  uint32_t* s_cnt = reinterpret_cast<uint32_t*>(s_sum + R + (size_t)kScoreWaves * kScoreTop);  // [R]
+  uint16_t* list = reinterpret_cast<uint16_t*>(s_cnt + R) + (size_t)wid * (OOB ? R : 0);
+  uint8_t* rows = reinterpret_cast<uint8_t*>(s_cnt + R) + (OOB ? (size_t)2 * kScoreWaves * R : 0);
+  stage_rows<BLOCK>(rows, codes, C, F.train_off >= 0 ? row_list + F.train_off : nullptr, r0, nr);
+  for (int i = tid; i < nr; i += BLOCK) {
+    s_sum[i] = 0;
+    s_cnt[i] = 0;
   }
-  sum[F.row_off + i] = P;
-  count[F.row_off + i] = cnt;
+  __syncthreads();
+  const int nw = (nr + kWave - 1) / kWave;  // bitmap words of these rows (at most 64)
+  for (int32_t t = t0 + wid; t < t1; t += kScoreWaves) {
+    const int64_t task = F.first_task + t;
+    uint32_t n_rows = (uint32_t)nr;
+    if constexpr (OOB) {
+      const int64_t bits = tasks[task].inbag_off;
+      if (bits < 0) continue;  // no bootstrap: every row is in bag
+      const uint64_t word = lane < nw ? inbag[bits + r0 / kWave + lane] : ~0ull;
+      n_rows = 0;
+      for (int i = 0; i < nw; ++i) {
+        uint64_t out = ~read_lane(word, i);
+        if (64 * i + 64 > nr) out &= ~0ull >> (64 * i + 64 - nr);
+        if ((out >> lane) & 1ull) list[n_rows + (uint32_t)__popcll(out & ((1ull << lane) - 1ull))] = (uint16_t)(64 * i + lane);
+        n_rows += (uint32_t)__popcll(out);
+      }
+    }
+    const uint64_t* tn = nodes + node_base[task];
+    const uint32_t nn = min((uint32_t)n_nodes[task], kScoreTop);
+    for (uint32_t i = lane; i < nn; i += kWave) top[i] = tn[i];
+    wave_lds_sync();
+    for (uint32_t j0 = 0; j0 < n_rows; j0 += K * kWave) {
+      uint32_t row[K], off[K];
+      bool on[K];
+      uint64_t v[K];
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const uint32_t j = j0 + (uint32_t)(k * kWave + lane);
+        on[k] = j < n_rows;
+        row[k] = on[k] ? (OOB ? list[j] : j) : 0u;
+        off[k] = row[k] * st;
+      }
+      walk_tree<K>(top, kScoreTop, tn, rows, off, on, v);
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        if (on[k]) {
+          atomicAdd((unsigned long long*)&s_sum[row[k]], (unsigned long long)node_q(v[k]));
+          if (OOB) atomicAdd(&s_cnt[row[k]], 1u);
+        }
+    }
+    wave_lds_sync();
+  }
+  __syncthreads();
+  for (int i = tid; i < nr; i += BLOCK) {
+    const int64_t o = F.row_off + r0 + i;
+    if (n_chunks > 1) {
+      atomicAdd(&sum[o], (unsigned long long)s_sum[i]);
+      if (OOB) atomicAdd(&count[o], (int32_t)s_cnt[i]);
+    } else {
+      sum[o] = s_sum[i];
+      if (OOB) count[o] = (int32_t)s_cnt[i];
+    }
+    // a held-out prediction is the forest mean: every tree counts
+    if (!OOB && t0 == 0) count[o] = F.num_trees;
+  }
 }
 
-// Held-out rows: every tree of the forest predicts; count = num.trees, so the
-// prediction formed below is the forest mean of the prediction entry points.
-__global__ __launch_bounds__(kOobBlock) void k_heldout_sums(const uint64_t* __restrict__ nodes,
-                                                            const int64_t* __restrict__ node_base,
-                                                            const int32_t* __restrict__ test_rows,
-                                                            const OobForest* __restrict__ forests,
-                                                            const uint8_t* __restrict__ codes, int32_t C,
-                                                            int64_t* __restrict__ sum, int32_t* __restrict__ count) {
-  const OobForest F = forests[blockIdx.y];
-  const int64_t i = (int64_t)blockIdx.x * kOobBlock + threadIdx.x;
-  if (i >= F.n_train) return;
-  const uint8_t* rp = codes + (int64_t)test_rows[F.train_off + i] * C;
-  int64_t P = 0;
-  for (int32_t t = 0; t < F.num_trees; ++t) {
-    const uint64_t* tn = nodes + node_base[F.first_task + t];
-    uint64_t v = tn[0];
-    while (node_col(v) != kLeafCol) v = tn[node_left(v) + (rp[node_col(v)] > node_bin(v) ? 1u : 0u)];
-    P += node_q(v);
+__global__ void k_zero_scores(unsigned long long* sum, int32_t* count, int64_t n) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    sum[i] = 0ull;
+    if (count) count[i] = 0;
   }
-  sum[F.row_off + i] = P;
-  count[F.row_off + i] = F.num_trees;
 }
 
 // Per workgroup: sums of squared error, absolute error and rows with a
@@ -131,33 +185,65 @@ __global__ void k_oob_final(const double* partial, int32_t n_forests, int32_t bl
   result[3 * f + 2] = c;
 }
 
-}  // namespace
-
-void launch_oob(const uint64_t* nodes, const TreeTask* tasks, const int64_t* node_base, const uint64_t* inbag,
-                const int32_t* train_rows, const OobForest* forests, int32_t n_forests, int32_t max_n_train,
-                const uint8_t* codes, int32_t C, const double* y, int64_t* sum, int32_t* count, double* partial,
-                double* result, hipStream_t s) {
-  const int32_t blocks = (max_n_train + kOobBlock - 1) / kOobBlock;
-  const dim3 grid((unsigned)blocks, (unsigned)n_forests);
-  k_oob_sums<<<grid, kOobBlock, 0, s>>>(nodes, tasks, node_base, inbag, train_rows, forests, codes, C, sum, count);
-  AIWC_HIP(hipGetLastError());
-  k_oob_partial<<<grid, kOobBlock, 0, s>>>(sum, count, train_rows, forests, y, partial);
+void launch_errors(const int32_t* row_list, const OobForest* forests, int32_t n_forests, int32_t max_n,
+                   const double* y, const int64_t* sum, const int32_t* count, double* partial, double* result,
+                   hipStream_t s) {
+  const int32_t blocks = std::max(1, (max_n + kOobBlock - 1) / kOobBlock);
+  k_oob_partial<<<dim3((unsigned)blocks, (unsigned)n_forests), kOobBlock, 0, s>>>(sum, count, row_list, forests, y,
+                                                                               partial);
   AIWC_HIP(hipGetLastError());
   k_oob_final<<<(n_forests + 255) / 256, 256, 0, s>>>(partial, n_forests, blocks, result);
   AIWC_HIP(hipGetLastError());
 }
 
-void launch_heldout(const uint64_t* nodes, const int64_t* node_base, const int32_t* test_rows,
-                    const OobForest* forests, int32_t n_forests, int32_t max_n_test, const uint8_t* codes, int32_t C,
+// Launch of k_score over `total` rows of n_forests forests, the largest of max_n
+// rows: R rows per workgroup, and enough tree chunks to fill the CUs when the
+// forests and row blocks alone do not.
+template <bool OOB>
+void launch_score(const TreesView& T, const TreeTask* tasks, const uint64_t* inbag, const int32_t* row_list,
+                  const OobForest* forests, int32_t n_forests, int32_t max_n, int32_t max_trees, int64_t total,
+                  const uint8_t* codes, int32_t C, int64_t* sum, int32_t* count, hipStream_t s) {
+  const int64_t st = staged_stride(C);
+  const int64_t row_bytes = st + 12 + (OOB ? 2 * kScoreWaves : 0), tops = (int64_t)kScoreWaves * kScoreTop * 8;
+  // up to 512 rows, so that three workgroups (24 waves) fit a CU: the tuning
+  // grid's out-of-bag scores take 5.6 ms with 512 rows, 6.6 with 256 (each
+  // tree's first nodes serve fewer rows) and 8.3 with 1024 (two workgroups)
+  const int64_t room = (int64_t)device_info().lds_per_block / 3 - tops;
+  const int64_t most = std::min<int64_t>(512, room / row_bytes) / kWave * kWave;
+  const int64_t n_rb = (max_n + most - 1) / most;
+  const int64_t R = ((max_n + n_rb - 1) / n_rb + kWave - 1) / kWave * kWave;
+  const size_t lds = (size_t)(R * row_bytes + tops);
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(32 / kScoreWaves, (int64_t)(device_info().lds_per_block / lds)));
+  const int64_t slots = per_cu * device_info().cus, wgs = n_rb * n_forests;
+  int64_t n_chunks = std::min<int64_t>((2 * slots + wgs - 1) / wgs, (max_trees + kScoreWaves - 1) / kScoreWaves);
+  n_chunks = std::max<int64_t>(1, n_chunks);
+  if (n_chunks > 1) {
+    const int zb = (int)std::max<int64_t>(1, std::min<int64_t>(1024, (total + 255) / 256));
+    k_zero_scores<<<zb, 256, 0, s>>>(reinterpret_cast<unsigned long long*>(sum), OOB ? count : nullptr, total);
+    AIWC_HIP(hipGetLastError());
+  }
+  k_score<OOB><<<dim3((unsigned)n_rb, (unsigned)n_forests, (unsigned)n_chunks), kScoreWaves * kWave, lds, s>>>(
+      T.nodes, tasks, T.node_base, T.n_nodes, inbag, row_list, forests, codes, C, (int32_t)R, (int32_t)n_chunks,
+      reinterpret_cast<unsigned long long*>(sum), count);
+  AIWC_HIP(hipGetLastError());
+}
+}  // namespace
+
+void launch_oob(const TreesView& T, const TreeTask* tasks, const uint64_t* inbag, const int32_t* train_rows,
+                const OobForest* forests, int32_t n_forests, int32_t max_n_train, int32_t max_trees, int64_t total,
+                const uint8_t* codes, int32_t C, const double* y, int64_t* sum, int32_t* count, double* partial,
+                double* result, hipStream_t s) {
+  launch_score<true>(T, tasks, inbag, train_rows, forests, n_forests, max_n_train, max_trees, total, codes, C, sum,
+                     count, s);
+  launch_errors(train_rows, forests, n_forests, max_n_train, y, sum, count, partial, result, s);
+}
+
+void launch_heldout(const TreesView& T, const int32_t* test_rows, const OobForest* forests, int32_t n_forests,
+                    int32_t max_n_test, int32_t max_trees, int64_t total, const uint8_t* codes, int32_t C,
                     const double* y, int64_t* sum, int32_t* count, double* partial, double* result, hipStream_t s) {
-  const int32_t blocks = std::max(1, (max_n_test + kOobBlock - 1) / kOobBlock);
-  const dim3 grid((unsigned)blocks, (unsigned)n_forests);
-  k_heldout_sums<<<grid, kOobBlock, 0, s>>>(nodes, node_base, test_rows, forests, codes, C, sum, count);
-  AIWC_HIP(hipGetLastError());
-  k_oob_partial<<<grid, kOobBlock, 0, s>>>(sum, count, test_rows, forests, y, partial);
-  AIWC_HIP(hipGetLastError());
-  k_oob_final<<<(n_forests + 255) / 256, 256, 0, s>>>(partial, n_forests, blocks, result);
-  AIWC_HIP(hipGetLastError());
+  launch_score<false>(T, nullptr, nullptr, test_rows, forests, n_forests, max_n_test, max_trees, total, codes, C, sum,
+                      count, s);
+  launch_errors(test_rows, forests, n_forests, max_n_test, y, sum, count, partial, result, s);
 }
 
 }  // namespace aiwc

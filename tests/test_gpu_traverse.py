@@ -79,3 +79,54 @@ def test_select_paths(rf, oracle, D, m):
     yhat = yhat.reshape(m, D)
     assert np.array_equal(times.cpu().numpy(), yhat)
     assert np.array_equal(best.cpu().numpy(), yhat.argmin(axis=1))
+
+
+# training rows around a bitmap word and a workgroup's 512 rows, one and several
+# tree chunks, rows too wide for 512 of them, and a forest without bootstrap
+@pytest.mark.parametrize("C,n,trees,boot", [
+    (35, 2, 3, True), (35, 63, 9, True), (35, 64, 1, True), (34, 65, 40, True), (35, 511, 8, True), (35, 512, 9, True),
+    (35, 513, 70, True), (3, 1025, 300, True), (255, 700, 20, True), (35, 600, 10, False),
+])
+def test_oob_paths(rf, oracle, C, n, trees, boot):
+    log(f"oob paths C={C} n={n} trees={trees}")
+    rng = np.random.default_rng(n + C)
+    codes = rng.integers(0, 61, (n, C)).astype(np.uint8)
+    y = rng.normal(0.0, 1.0, n)
+    nb = np.full(C, 61, np.int32)
+    mtry = max(1, C // 4)
+    dc, dy = to_dev(codes), to_dev(y)
+    forest = rf.aiwc_rf_fit(dc, rf.aiwc_rf_binner_from_counts(nb), dy, rf.make_params(trees, mtry, 2, boot, 9))
+    res = rf.aiwc_rf_oob_error(forest, dc, dy, n_train=n)
+    of = oracle.fit(codes, nb, y, trees, mtry, 2, seed=9, bootstrap=boot)
+    P, cnt, (_, _, m) = oracle.oob(of, codes, y, mtry, 2, seed=9, bootstrap=boot)
+    assert np.array_equal(res.sums.cpu().numpy(), P)
+    assert np.array_equal(res.counts.cpu().numpy(), cnt)
+    assert res.rows[0] == m
+
+
+# held-out rows of folds of very different sizes, one of them a single row and one
+# above a workgroup's rows, each under all of its forest's trees
+@pytest.mark.parametrize("sizes,trees", [((1, 64, 200), 7), ((600, 3, 513), 33)])
+def test_heldout_paths(rf, oracle, sizes, trees):
+    log(f"heldout paths {sizes}")
+    rng = np.random.default_rng(trees)
+    n, C = sum(sizes) + 40, 21
+    fold = rng.permutation(np.repeat(np.arange(-1, len(sizes)), (40,) + sizes)).astype(np.int8)
+    codes = rng.integers(0, 50, (n, C)).astype(np.uint8)
+    y = rng.normal(0.0, 1.0, n)
+    nb = np.full(C, 50, np.int32)
+    dc, dy = to_dev(codes), to_dev(y)
+    forest = rf.aiwc_rf_fit(dc, rf.aiwc_rf_binner_from_counts(nb), dy,
+                            [rf.make_params(trees + k, 6, 2, True, 5) for k in range(len(sizes))], to_dev(fold),
+                            list(range(len(sizes))))
+    res = rf.aiwc_rf_heldout_error(forest, dc, dy, n_heldout=sum(sizes))
+    sums, at = res.sums.cpu().numpy(), 0
+    for k, size in enumerate(sizes):
+        of = oracle.fit(codes, nb, y, trees + k, 6, 2, seed=5, train_rows=np.nonzero(fold != k)[0])
+        P, yhat = oracle.predict(of, codes[fold == k])
+        assert np.array_equal(sums[at:at + size], P), k
+        e = yhat - y[fold == k]
+        assert res.rows[k] == size
+        # n non-negative terms summed in two orders: within 2 n 2^-53 of each other
+        assert abs(res.mse[k] - (e * e).mean()) <= 2 * (size + 1) * 2.0 ** -53 * (e * e).mean()
+        at += size
