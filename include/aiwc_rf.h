@@ -188,10 +188,12 @@ int aiwc_rf_forest_stats(const aiwc_rf_forest* forest, int32_t forest_index, int
  * change results; this reports which one ran, for tests and profiles. */
 typedef struct {
   int32_t block;          /* threads per workgroup of the grow kernel */
-  int32_t waves_per_simd; /* occupancy the grow kernel was compiled for */
+  int32_t waves_per_simd; /* occupancy the shape asks for; at 64 threads and 5, a code matrix that fits the LDS
+                             beside their areas is shared by workgroups of sixteen such one-wave teams, whose
+                             kernel is compiled for 4 */
   int32_t wide_limit;     /* nodes with more in-bag rows are searched by the whole workgroup */
   int32_t big_cols;       /* candidate columns per large-node task */
-  int32_t grid;           /* workgroups of the (largest) persistent grow launch */
+  int32_t grid;           /* workgroups (of one tree, or of sixteen teams) of the (largest) persistent grow launch */
   int32_t wide_phase;     /* 1 when the kernel with the workgroup-wide phase ran */
   int32_t graph;          /* 1 when the fit ran as one executable-graph launch (fused grid) */
   int32_t graph_reused;   /* 1 when that graph was built by an earlier fit of the same shape */

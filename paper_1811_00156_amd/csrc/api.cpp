@@ -167,18 +167,18 @@ GrowConfig tune_grow(const GrowConfig& base, int64_t n_items, int32_t n_cols, in
   for (const GrowConfig& c : tune_candidates(base)) {
     int grid = 0;
     try {
-      grid = grow_grid_size(c, trial, mtry_max, n_cols);
+      grid = grow_grid_size(c, trial, mtry_max, n_cols, n);
     } catch (const Error&) {
       continue;  // the shape does not fit this device
     }
-    DevBuf<uint8_t> scratch(per_wg * (size_t)grid, s);
+    DevBuf<uint8_t> scratch(per_wg * (size_t)grid * grow_teams(c, mtry_max, n_cols, n), s);
     // each shape is timed twice and keeps its faster run
     float ms = -1.0f;
     for (int rep = 0; rep < 2; ++rep) {
       launch_init(nullptr, queue, s);
       AIWC_HIP(hipEventRecord(e0, s));
       const GrowLaunch g{codes, codes_p, d_train, d_trial, (int32_t)trial, F->nodes.p, F->node_N.p,
-                         F->n_nodes.p, F->work.p, F->inbag.p, queue, scratch.p, base.n_cap};
+                         F->n_nodes.p, F->work.p, F->inbag.p, queue, scratch.p, base.n_cap, n};
       launch_grow(c, g, n_cols, binner->d_n_bins.p, y_fp, F->status.p, mtry_max, grid, s);
       AIWC_HIP(hipEventRecord(e1, s));
       AIWC_HIP(hipEventSynchronize(e1));
@@ -490,6 +490,7 @@ void fit_common(const uint8_t* codes, int64_t n, int32_t n_cols, const aiwc_rf_b
     tuned = true;
   }
   const size_t per_wg = grow_scratch_bytes(n_cap, mtry_max, grow_has_wide_phase(cfg), grouped);
+  const size_t teams = (size_t)grow_teams(cfg, mtry_max, n_cols, n);
   aiwc_rf_launch_info& LI = F->launch;
   LI.block = cfg.block;
   LI.waves_per_simd = grow_has_wide_phase(cfg) ? 4 : cfg.occupancy;
@@ -501,33 +502,33 @@ void fit_common(const uint8_t* codes, int64_t n, int32_t n_cols, const aiwc_rf_b
 
   if (plain) {
     // one launch sequence per forest, as separate fits would issue them
-    const int grid_max = grow_grid_size(cfg, n_tasks, mtry_max, n_cols);
-    DevBuf<uint8_t> scratch(per_wg * (size_t)grid_max, s);
+    const int grid_max = grow_grid_size(cfg, n_tasks, mtry_max, n_cols, n);
+    DevBuf<uint8_t> scratch(per_wg * (size_t)grid_max * teams, s);
     launch_init(F->status.p, nullptr, s);
     AIWC_HIP(hipEventRecord(F->grow_begin, s));
     int grid_used = 0;
     for (int32_t f = 0; f < n_forests; ++f) {
       const int64_t t0 = F->first_task[f];
       const int32_t nt = params_host[f].num_trees;
-      const int grid = grow_grid_size(cfg, nt, mtry_max, n_cols);
+      const int grid = grow_grid_size(cfg, nt, mtry_max, n_cols, n);
       grid_used = std::max(grid_used, grid);
       launch_init(nullptr, queue.p, s);
       launch_prepare(codes, n, n_cols, binner->d_n_bins.p, y_log10, y_fp.p, codes_p.p, F->status.p, s);
       const GrowLaunch g{codes, codes_p.p, d_train.p, F->d_tasks.p + t0, nt, F->nodes.p, F->node_N.p,
-                         F->n_nodes.p + t0, F->work.p + kWorkWords * t0, F->inbag.p, queue.p, scratch.p, n_cap};
+                         F->n_nodes.p + t0, F->work.p + kWorkWords * t0, F->inbag.p, queue.p, scratch.p, n_cap, n};
       launch_grow(cfg, g, n_cols, binner->d_n_bins.p, y_fp.p, F->status.p, mtry_max, grid, s);
     }
     AIWC_HIP(hipEventRecord(F->grow_end, s));
     LI.grid = grid_used;
   } else {
-    const int grid = grow_grid_size(cfg, n_groups, mtry_max, n_cols, grouped);
+    const int grid = grow_grid_size(cfg, n_groups, mtry_max, n_cols, n, grouped);
     LI.grid = grid;
-    DevBuf<uint8_t> scratch(per_wg * (size_t)grid, s);
+    DevBuf<uint8_t> scratch(per_wg * (size_t)grid * teams, s);
     const GrowLaunch g{codes,     codes_p.p, d_train.p,
                        F->d_tasks.p, (int32_t)n_tasks, F->nodes.p,
                        F->node_N.p, F->n_nodes.p, F->work.p,
                        F->inbag.p, queue.p,   scratch.p,
-                       n_cap,     grouped ? F->group_task.p : nullptr, grouped ? F->group_first.p : nullptr,
+                       n_cap,     n,         grouped ? F->group_task.p : nullptr, grouped ? F->group_first.p : nullptr,
                        (int32_t)n_groups};
     if (n_forests > 1) {
       // fused grid: the whole fit as one executable-graph launch (timing events

@@ -30,6 +30,8 @@
 // the order in which rows are visited never changes a result.
 #include <limits.h>
 
+#include <type_traits>
+
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -243,15 +245,42 @@ struct GrowArgs {
   size_t scratch_stride;
   uint32_t union_bytes;  // dynamic LDS
   uint32_t wave_bytes;   // per-wave area of the split-search tasks
+  // teams in one workgroup: rows of the code matrix in the LDS, the bytes it
+  // takes there, and each team's bytes (union_bytes and its Shared)
+  uint32_t lcode_rows, lcode_bytes, team_bytes;
 };
 
 __device__ __forceinline__ uint32_t rfl(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// Workgroup exclusive scan of one u32 per thread; `total` receives the sum.
+// A team of BLOCK threads grows a tree: the workgroup, or (BLOCK = 64) one wave,
+// of which a workgroup may hold several.
+template <int BLOCK>
+__device__ __forceinline__ int team_tid() {
+  return BLOCK == kWave ? (int)lane_id() : (int)threadIdx.x;
+}
+template <int BLOCK>
+__device__ __forceinline__ void team_sync() {
+  if constexpr (BLOCK == kWave) {
+    // the wave's earlier memory operations, in LDS and in global memory, are
+    // complete before its later ones: no other wave is waited for
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  } else {
+    __syncthreads();
+  }
+}
+
+// Team exclusive scan of one u32 per thread; `total` receives the sum.
 template <int BLOCK>
 __device__ __forceinline__ uint32_t block_exscan(uint32_t v, uint32_t* tmp, uint32_t& total) {
   constexpr int NW = BLOCK / kWave;
   const int lane = (int)lane_id(), wid = threadIdx.x / kWave;
+  if constexpr (NW == 1) {
+    const uint32_t incl = wave_incl_scan_u32(v);
+    total = read_lane(incl, kWave - 1);
+    return incl - v;
+  }
   const uint32_t incl = wave_incl_scan_u32(v);
   if (lane == kWave - 1) tmp[wid] = incl;
   __syncthreads();
@@ -273,6 +302,11 @@ template <int BLOCK>
 __device__ __forceinline__ uint64_t block_exscan64(uint64_t v, uint64_t* tmp, uint64_t& total) {
   constexpr int NW = BLOCK / kWave;
   const int lane = (int)lane_id(), wid = threadIdx.x / kWave;
+  if constexpr (NW == 1) {
+    const uint64_t incl = wave_incl_scan<uint64_t>(v);
+    total = read_lane(incl, kWave - 1);
+    return incl - v;
+  }
   const uint64_t incl = wave_incl_scan<uint64_t>(v);
   if (lane == kWave - 1) tmp[wid] = incl;
   __syncthreads();
@@ -294,6 +328,7 @@ __device__ __forceinline__ T block_sum(T v, T* tmp) {
   constexpr int NW = BLOCK / kWave;
   const int lane = (int)lane_id(), wid = threadIdx.x / kWave;
   v = wave_sum(v);
+  if constexpr (NW == 1) return v;
   if (lane == 0) tmp[wid] = v;
   __syncthreads();
   T s = 0;
@@ -348,9 +383,32 @@ __device__ __forceinline__ void draw_candidates(uint8_t* perm, int pst, uint64_t
   for (; i < cand_stride(mtry); ++i) out[i] = (uint8_t)last;
 }
 
+// A row's codes, read by column: in the workgroup's LDS copy of the code matrix
+// (LC) or in global memory.
+template <bool LC>
+struct RowCodes;
+template <>
+struct RowCodes<false> {
+  const uint8_t* p;
+  __device__ __forceinline__ uint32_t operator[](uint32_t c) const { return gload(p + c); }
+};
+template <>
+struct RowCodes<true> {
+  const __attribute__((address_space(3))) uint8_t* p;
+  __device__ __forceinline__ uint32_t operator[](uint32_t c) const { return p[c]; }
+};
+
+template <bool LC>
 struct Ctx {
   const GrowArgs* a;
   const TreeTask* T;
+  const uint8_t* lcodes;  // LC: the code matrix in the LDS, rows of C bytes
+  __device__ __forceinline__ RowCodes<LC> row(uint32_t r) const {
+    if constexpr (LC)
+      return {(const __attribute__((address_space(3))) uint8_t*)(lcodes + r * (uint32_t)a->C)};
+    else
+      return {a->rcodes + (size_t)r * a->rC};
+  }
   Scratch sc;
   const uint64_t* buf;  // this level's entries
   uint64_t* nbuf;       // the next level's entries
@@ -393,8 +451,8 @@ __device__ __forceinline__ uint64_t scan_packed_small(uint64_t h) {
 // segment reductions, and the node's rows placed into its children's segments
 // of the next level (left ones first, in lane order, then the right ones), so
 // that the partition skips it; the segment's first lane writes the decision.
-template <int W>
-__device__ __forceinline__ void small_finish(const Ctx& x, uint32_t k, bool node_ok, int r, int sbase, bool split,
+template <int W, bool LC>
+__device__ __forceinline__ void small_finish(const Ctx<LC>& x, uint32_t k, bool node_ok, int r, int sbase, bool split,
                                              uint32_t col, uint32_t bin, bool valid, bool left, uint64_t e,
                                              uint32_t start) {
   const uint32_t w = entry_w(e);
@@ -492,8 +550,114 @@ __device__ __forceinline__ void byte_plane_sums(uint32_t code, const uint32_t* s
   }
 }
 
+// Left sums of a candidate's splits for the whole wave by matrix instructions:
+// for every lane the sums, over its segment's W rows whose code is at most its
+// own row's, of the rows' weights and of their w y.  A 16 x 16 x 64 product of
+// signed bytes contracts the wave's 64 rows: its A operand holds the rows' digits
+// (staged once per task, negated), its B operand the comparisons, and its
+// accumulator's layout gives lane 16 q + j rows 4 q .. 4 q + 3 of column j, the
+// four digit sums of that lane's own split.
+//   A: lane 16 b + i holds row i's bytes for the wave's rows 16 b .. 16 b + 15;
+//      row 4 q + p is digit p of the rows that quarter q's lanes sum over.
+//   B: lane 16 b + j holds column j's comparisons with the rows 16 b .. 16 b + 15:
+//      W <= 16: its own row's code against its own segment (the quarter's other
+//      segments 0); W = 32: two products, with rows j and 16 + j of its node, each
+//      with the A rows of the quarters it is for.
+// Digits: word 0 the weight (at most 127), words 1..3 (4) the balanced base-256
+// digits of w y.  A comparison is the byte 0x80 = -128, so a sum comes out
+// times 128 and one exact shift divides that out.
+// Against the dot products above it drops the LDS reads of the planes and, of
+// the VALU instructions per candidate, two thirds for W = 32 (48 -> 16) and half
+// for W = 8 and 16: the tuning grid's launch issues 11 % fewer VALU and 31 %
+// fewer LDS instructions.  It holds eight registers more through the candidate
+// loop, which only the kernel of k_grow_teams has to spare: there the grid takes
+// 261 ms with it and 280 without; kernels of 96 and 80 registers spill for it and
+// lose (the grid 287 -> 292 ms, 2000 trees on 2220 rows 2.29 -> 2.36 ms).
+typedef int v4i_t __attribute__((ext_vector_type(4)));
+
+// Bit 7 of each byte: the byte of c4 is at most `code`, whose broadcasts are kb
+// (all four bytes) and kh (kb with bit 7 set).  C7 (every code below 128): 128 +
+// code - c stays in [1, 255] in each byte, so no borrow crosses the bytes and its
+// bit 7 is the comparison.  Otherwise the low seven bits are compared that way
+// and bit 7 decides where it differs.
+template <bool C7>
+__device__ __forceinline__ uint32_t bytes_le(uint32_t c4, uint32_t kb, uint32_t kh) {
+  if constexpr (C7) return kh - c4;
+  const uint32_t t = kh - (c4 & 0x7F7F7F7Fu);
+  return (kb & ~c4) | (~(kb ^ c4) & t);
+}
+
 template <int W>
-__device__ __forceinline__ void small_task(const Ctx& x, const NodeDesc* list, uint32_t t, uint32_t n_list, WaveHist& wl) {
+struct SegDigits {
+  static constexpr int H = W == 32 ? 2 : 1;  // products per candidate
+  v4i_t a[H];
+};
+
+// A operands of digits 0..3, from the staged digit planes (plane p's byte of the
+// wave's row r at planes + 64 p + r); TOP: of digit 4 alone, in its first row.
+template <int W, bool TOP>
+__device__ __forceinline__ SegDigits<W> seg_digits(const uint8_t* planes, int lane) {
+  const int b = lane >> 4, q = (lane >> 2) & 3, p = lane & 3;
+  const v4i_t v = *reinterpret_cast<const v4i_t*>(planes + 64 * (TOP ? 4 : p) + 16 * b);
+  SegDigits<W> d;
+#pragma unroll
+  for (int h = 0; h < d.H; ++h) {
+    const bool mine = (W == 32 ? q == (b & 2) + h : q == b) && (!TOP || p == 0);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) d.a[h][u] = mine ? v[u] : 0;
+  }
+  return d;
+}
+
+template <int W, bool C7, bool B3>
+__device__ __forceinline__ void matrix_sums(const SegDigits<W>& A, const uint8_t* planes, const uint8_t* col_codes,
+                                            uint32_t code, int lane, uint32_t& NL, int64_t& SL, bool light) {
+  constexpr uint32_t kTop = 0x80808080u;
+  v4i_t acc = {0, 0, 0, 0}, acc4 = {0, 0, 0, 0};
+  if constexpr (W <= 16) {
+    const uint32_t kb = code * 0x01010101u, kh = kb | kTop;
+    const uint32_t* seg = reinterpret_cast<const uint32_t*>(col_codes + (lane & ~(W - 1)));
+    uint32_t c[W / 4];
+#pragma unroll
+    for (int u = 0; u < W / 4; ++u) c[u] = bytes_le<C7>(seg[u], kb, kh);
+    v4i_t bm;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      // word u belongs to the quarter's segment 4 u / W
+      const uint32_t m = W == 16 || (lane & 15) / W == 4 * u / W ? kTop : 0u;
+      bm[u] = (int)(c[u % (W / 4)] & m);
+    }
+    acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(A.a[0], bm, acc, 0, 0, 0);
+    if constexpr (!B3)
+      acc4 = __builtin_amdgcn_mfma_i32_16x16x64_i8(seg_digits<W, true>(planes, lane).a[0], bm, acc4, 0, 0, 0);
+  } else {
+    const uint4 c4 = *reinterpret_cast<const uint4*>(col_codes + (lane & 0x30));
+    SegDigits<W> A4;
+    if constexpr (!B3) A4 = seg_digits<W, true>(planes, lane);
+#pragma unroll
+    for (int h = 0; h < SegDigits<W>::H; ++h) {
+      const uint32_t kb = (uint32_t)col_codes[(lane & 0x20) + 16 * h + (lane & 15)] * 0x01010101u;
+      const uint32_t kh = kb | kTop;
+      const v4i_t bm = {(int)(bytes_le<C7>(c4.x, kb, kh) & kTop), (int)(bytes_le<C7>(c4.y, kb, kh) & kTop),
+                        (int)(bytes_le<C7>(c4.z, kb, kh) & kTop), (int)(bytes_le<C7>(c4.w, kb, kh) & kTop)};
+      acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(A.a[h], bm, acc, 0, 0, 0);
+      if constexpr (!B3) acc4 = __builtin_amdgcn_mfma_i32_16x16x64_i8(A4.a[h], bm, acc4, 0, 0, 0);
+    }
+  }
+  // every accumulator is a multiple of 128
+  NL = (uint32_t)(acc[0] >> 7);
+  if (light) {  // the sum fits 32 bits (its terms need not: they wrap)
+    uint32_t v = (uint32_t)(acc[1] >> 7) + ((uint32_t)acc[2] << 1) + ((uint32_t)acc[3] << 9);
+    if constexpr (!B3) v += (uint32_t)acc4[0] << 17;
+    SL = (int32_t)v;
+  } else {
+    SL = (int64_t)(acc[1] >> 7) + (int64_t)acc[2] * 2 + (int64_t)acc[3] * 512;
+    if constexpr (!B3) SL += (int64_t)acc4[0] * 131072;
+  }
+}
+
+template <int W, bool LC>
+__device__ __forceinline__ void small_task(const Ctx<LC>& x, const NodeDesc* list, uint32_t t, uint32_t n_list, WaveHist& wl) {
   const GrowArgs& a = *x.a;
   const int mtry = x.T->mtry;
   const int lane = (int)lane_id();
@@ -514,34 +678,50 @@ __device__ __forceinline__ void small_task(const Ctx& x, const NodeDesc* list, u
   uint8_t* area = reinterpret_cast<uint8_t*>(&wl);
   uint8_t* s_codes = area + 512;  // [64 columns][64 lanes]
   // The rows' weights and w y, staged in the first 512 bytes.  When every weight
-  // of the wave fits a byte (bootstrap multiplicities nearly always do), as byte
-  // planes: the group of rows 4j..4j+3 takes 32 bytes, word 0 their weights and
-  // words 1..4 bytes 0..3 of their w y (|w y| < 2^30: two's complement, the top
-  // byte signed), so that four rows' left sums are five 4-byte dot products
-  // (four when every w y fits 24 bits).  Otherwise packed (w, w y) words, one
-  // per row.
-  const bool bytes_ok = !a.wide_sums && __ballot(w > 255u) == 0ull;
-  // every w y of the wave fits 24 bits: its top byte is a sign extension, and
-  // three byte planes of w y carry it
-  const bool b3 = __ballot(wy < -(int64_t)(1 << 23) || wy >= (int64_t)(1 << 23)) == 0ull;
+  // of the wave is small (bootstrap multiplicities nearly always are), as signed
+  // digits for the matrix products (MX, weights up to 127: 64 bytes of -w, then
+  // 64 of each balanced base-256 digit of -w y) or as byte planes for the dot
+  // products (weights up to 255: the group of rows 4j..4j+3 takes 32 bytes, word 0
+  // their weights and words 1..4 bytes 0..3 of their w y, two's complement).
+  // |w y| < 2^30 takes four digits or bytes, three when every w y of the wave
+  // fits 24 bits.  Otherwise packed (w, w y) words, one per row.
+  constexpr bool MX = LC;
+  const bool bytes_ok = !a.wide_sums && __ballot(w > (MX ? 127u : 255u)) == 0ull;
+  const uint32_t u = 0x80808080u - (uint32_t)(int32_t)wy;  // digit j of -w y is byte j of u less 128
+  const bool b3 = MX ? __ballot(u >> 24 != 0x80u) == 0ull
+                     : __ballot(wy < -(int64_t)(1 << 23) || wy >= (int64_t)(1 << 23)) == 0ull;
   // every column's codes fit 7 bits (at most 128 bins)
   const bool codes7 = a.bstride <= 128;
   // every node of the wave weighs below 512: its sums fit 32 bits
   const bool light = __ballot(N >= 512u) == 0ull;
   uint8_t* planes = area;
   uint64_t* s_pv = reinterpret_cast<uint64_t*>(area);
+  SegDigits<W> A;
   if (bytes_ok) {
-    const uint32_t wy32 = (uint32_t)(int32_t)wy;
-    uint8_t* gp = planes + (lane >> 2) * 32 + (lane & 3);
-    gp[0] = (uint8_t)w;
-    gp[4] = (uint8_t)wy32;
-    gp[8] = (uint8_t)(wy32 >> 8);
-    gp[12] = (uint8_t)(wy32 >> 16);
-    gp[16] = (uint8_t)(wy32 >> 24);
+    if constexpr (MX) {
+      const uint32_t dg = u ^ 0x80808080u;
+      planes[lane] = (uint8_t)(0u - w);
+      planes[64 + lane] = (uint8_t)dg;
+      planes[128 + lane] = (uint8_t)(dg >> 8);
+      planes[192 + lane] = (uint8_t)(dg >> 16);
+      planes[256 + lane] = (uint8_t)(dg >> 24);
+    } else {
+      const uint32_t wy32 = (uint32_t)(int32_t)wy;
+      uint8_t* gp = planes + (lane >> 2) * 32 + (lane & 3);
+      gp[0] = (uint8_t)w;
+      gp[4] = (uint8_t)wy32;
+      gp[8] = (uint8_t)(wy32 >> 8);
+      gp[12] = (uint8_t)(wy32 >> 16);
+      gp[16] = (uint8_t)(wy32 >> 24);
+    }
   } else {
     s_pv[lane] = pack_ns(w, wy);
   }
-  const uint8_t* rowp = a.rcodes + (size_t)row * a.rC;
+  if constexpr (MX) {
+    wave_lds_sync();
+    A = seg_digits<W, false>(planes, lane);  // (unused with packed words)
+  }
+  const RowCodes<LC> rowp = x.row(row);
   const uint8_t* cand = x.sc.cand + (size_t)k * cand_stride(mtry);
 
   // each lane keeps its own best split (score, candidate index, bin) over the
@@ -549,7 +729,6 @@ __device__ __forceinline__ void small_task(const Ctx& x, const NodeDesc* list, u
   double best = -1.0;
   uint32_t best_ib = 0xFFFFFFFFu;  // candidate index << 8 | bin
   const uint64_t* seg_pv = s_pv + sbase;
-  const uint8_t* seg_planes = planes + (sbase >> 2) * 32;
   for (int i0 = 0; i0 < mtry; i0 += kWave) {
     const int nc = min(kWave, mtry - i0);
     // gather the row's codes in every candidate column of this chunk at once:
@@ -565,7 +744,7 @@ __device__ __forceinline__ void small_task(const Ctx& x, const NodeDesc* list, u
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
         const uint32_t c = g0 + u < nc ? (cw[u >> 2] >> (8 * (u & 3))) & 0xFFu : 0u;
-        cd[u] = gload(rowp + c);
+        cd[u] = rowp[c];
       }
 #pragma unroll
       for (int u = 0; u < 16; ++u) s_codes[(g0 + u) * kWave + lane] = (uint8_t)cd[u];
@@ -574,17 +753,27 @@ __device__ __forceinline__ void small_task(const Ctx& x, const NodeDesc* list, u
     for (int i = 0; i < nc; ++i) {
       const uint8_t* col_codes = s_codes + i * kWave;
       const uint32_t code = col_codes[lane];
-      const uint32_t* seg_codes = reinterpret_cast<const uint32_t*>(col_codes + sbase);
       // left sums of the split at this lane's code: the segment's rows with a code <= it
       uint32_t NL;
       int64_t SL;
+      const uint32_t* seg_codes = reinterpret_cast<const uint32_t*>(col_codes + sbase);
       if (bytes_ok) {
-        if (codes7)
-          b3 ? byte_plane_sums<W, true, true>(code, seg_codes, seg_planes, NL, SL)
-             : byte_plane_sums<W, true, false>(code, seg_codes, seg_planes, NL, SL);
-        else
-          b3 ? byte_plane_sums<W, false, true>(code, seg_codes, seg_planes, NL, SL)
-             : byte_plane_sums<W, false, false>(code, seg_codes, seg_planes, NL, SL);
+        if constexpr (MX) {
+          if (codes7)
+            b3 ? matrix_sums<W, true, true>(A, planes, col_codes, code, lane, NL, SL, light)
+               : matrix_sums<W, true, false>(A, planes, col_codes, code, lane, NL, SL, light);
+          else
+            b3 ? matrix_sums<W, false, true>(A, planes, col_codes, code, lane, NL, SL, light)
+               : matrix_sums<W, false, false>(A, planes, col_codes, code, lane, NL, SL, light);
+        } else {
+          const uint8_t* seg_planes = planes + (sbase >> 2) * 32;
+          if (codes7)
+            b3 ? byte_plane_sums<W, true, true>(code, seg_codes, seg_planes, NL, SL)
+               : byte_plane_sums<W, true, false>(code, seg_codes, seg_planes, NL, SL);
+          else
+            b3 ? byte_plane_sums<W, false, true>(code, seg_codes, seg_planes, NL, SL)
+               : byte_plane_sums<W, false, false>(code, seg_codes, seg_planes, NL, SL);
+        }
       } else {
         uint64_t acc = 0;  // packed left sums
 #pragma unroll 2
@@ -612,7 +801,7 @@ __device__ __forceinline__ void small_task(const Ctx& x, const NodeDesc* list, u
   const bool split = node_ok && best >= 0.0 && best - parent_score(S, N) > 0.0;
   const uint32_t col = split ? cand[best_ib >> 8] : 0u, bin = best_ib & 0xFF;
   const bool left = split && valid && rowp[col] <= bin;
-  small_finish<W>(x, k, node_ok, r, sbase, split, col, bin, valid, left, e, start);
+  small_finish<W, LC>(x, k, node_ok, r, sbase, split, col, bin, valid, left, e, start);
 }
 
 // Nodes of 33..64 rows: one node per wave, one row per lane.  Per candidate
@@ -625,7 +814,8 @@ __device__ __forceinline__ void small_task(const Ctx& x, const NodeDesc* list, u
 // takes the one at its own code by a cross-lane read; a wider column writes
 // them back to LDS.  Two bin buffers alternate between candidates, so that a
 // wider column's bins are cleared while the next candidate is scanned.
-__device__ __forceinline__ void rank_task(const Ctx& x, const NodeDesc* list, uint32_t t, uint32_t n_list, WaveHist& wl) {
+template <bool LC>
+__device__ __forceinline__ void rank_task(const Ctx<LC>& x, const NodeDesc* list, uint32_t t, uint32_t n_list, WaveHist& wl) {
   const GrowArgs& a = *x.a;
   const int mtry = x.T->mtry;
   const int lane = (int)lane_id();
@@ -639,7 +829,7 @@ __device__ __forceinline__ void rank_task(const Ctx& x, const NodeDesc* list, ui
   const int64_t y = entry_y(e);
   const int64_t wy = (int64_t)w * y;
   const uint64_t pv = pack_ns(w, wy);
-  const uint8_t* rowp = a.rcodes + (size_t)entry_row(e) * a.rC;
+  const RowCodes<LC> rowp = x.row(entry_row(e));
   const uint8_t* cand = x.sc.cand + (size_t)k * cand_stride(mtry);
   uint8_t* area = reinterpret_cast<uint8_t*>(&wl);
   uint64_t* hb = reinterpret_cast<uint64_t*>(area);  // [2][256] packed bins, then prefix sums
@@ -665,14 +855,14 @@ __device__ __forceinline__ void rank_task(const Ctx& x, const NodeDesc* list, ui
   // every lane fetches its code (a lane without a row reads row 0, entry 0, and
   // adds nothing), so that the fetch is not a branch the memory wait must close
   uint32_t c_next = rfl(s_cand[0]);
-  uint32_t code_next = gload(rowp + c_next);
+  uint32_t code_next = rowp[c_next];
   bool prev_in_lds = false;  // the previous candidate left prefix sums in its buffer
   for (int i = 0; i < mtry; ++i) {
     const uint32_t code = code_next;
     const uint32_t B = rfl(s_bm1[i]) + 1u;  // this candidate column's bins
     if (i + 1 < mtry) {  // fetch the next column's codes while this one is scanned
       c_next = rfl(s_cand[i + 1]);
-      code_next = gload(rowp + c_next);
+      code_next = rowp[c_next];
     }
     uint64_t* hv = hb + (i & 1) * 256;
     if (valid) atomicAdd((unsigned long long*)&hv[code], (unsigned long long)pv);
@@ -733,7 +923,7 @@ __device__ __forceinline__ void rank_task(const Ctx& x, const NodeDesc* list, ui
   const bool split = am.score >= 0.0 && am.score - parent_score(S, N) > 0.0;
   const uint32_t col = split ? (uint32_t)s_cand[am.key >> 8] : 0u, bin = (uint32_t)am.key & 0xFF;
   const bool left = split && valid && rowp[col] <= bin;
-  small_finish<kWave>(x, k, true, lane, 0, split, col, bin, valid, left, e, start);
+  small_finish<kWave, LC>(x, k, true, lane, 0, split, col, bin, valid, left, e, start);
 }
 
 // Scan one column's histogram of packed bins (B <= 256 bins) with a wave: lane
@@ -804,7 +994,8 @@ __device__ __forceinline__ ArgMax scan_packed(const uint64_t* hv, int B, uint32_
 // Large nodes: one wave per (node, up to four consecutive candidate columns),
 // one LDS histogram per column: the node's entries are read once for all of
 // them and the columns' code gathers overlap.
-__device__ __forceinline__ void big_task(const Ctx& x, uint32_t j, int ci0, WaveHist& L) {
+template <bool LC>
+__device__ __forceinline__ void big_task(const Ctx<LC>& x, uint32_t j, int ci0, WaveHist& L) {
   constexpr int G = 4;
   const GrowArgs& a = *x.a;
   const int lane = (int)lane_id();
@@ -835,9 +1026,9 @@ __device__ __forceinline__ void big_task(const Ctx& x, uint32_t j, int ci0, Wave
     // past the node's end the entry is 0 (row 0), whose codes are not added
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const uint8_t* rp = a.rcodes + (size_t)entry_row(e[u]) * a.rC;
+      const RowCodes<LC> rp = x.row(entry_row(e[u]));
 #pragma unroll
-      for (int g = 0; g < G; ++g) code[u][g] = g < gn ? gload(rp + c[g]) : 0u;
+      for (int g = 0; g < G; ++g) code[u][g] = g < gn ? rp[(uint32_t)c[g]] : 0u;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -898,21 +1089,27 @@ __device__ __forceinline__ Decision decide_from_recs(const Rec* recs, int mtry, 
 }
 
 constexpr int kWideMax = 8;  // nodes per workgroup-wide batch
+constexpr int kTeams = 16;   // one-wave teams of a workgroup that holds the code matrix
 
-struct Shared {
-  uint16_t nbins[256];  // bin count of every column
-  uint32_t tmp[17];
-  uint64_t tmp64[17];
-  uint64_t red[16];
-  uint32_t cnt[3 + kSegClasses];  // [1] large, [2] wide, [3..] small nodes per segment width
-  uint32_t task;
-  uint32_t next_task;  // the split-search tasks' queue head
+struct SharedWide {
   // two wide batches (the one being searched and the next): node j's first
   // entry, rows, first chunk, weight, sum, and its candidates at
   // j * round_up(mtry, 8) + i
   uint32_t wstart[2][kWideMax], wlen[2][kWideMax], wcpre[2][kWideMax], wN[2][kWideMax];
   int64_t wS[2][kWideMax];
   alignas(8) uint8_t cand[2][256];
+};
+struct SharedNarrow {};
+
+// A team's state in the LDS.
+template <int BLOCK, bool WIDE>
+struct Shared : std::conditional<WIDE, SharedWide, SharedNarrow>::type {
+  uint32_t tmp[BLOCK / kWave + 1];
+  uint64_t tmp64[BLOCK / kWave + 1];
+  uint64_t red[BLOCK / kWave];
+  uint32_t cnt[3 + kSegClasses];  // [1] large, [2] wide, [3..] small nodes per segment width
+  uint32_t task;
+  uint32_t next_task;  // the split-search tasks' queue head
   // the group being grown: its members' task indices, min.node.size, node
   // slots and in-bag bitmaps, and the level at which their trees part (first
   // node id, node count, next free id, entry buffer, levels grown, large and
@@ -931,7 +1128,7 @@ struct Shared {
 
 // Metadata of wide batch `bi` (nodes list[0 .. nb)) into buffer bi & 1.
 template <int BLOCK>
-__device__ __forceinline__ void wide_setup(const Ctx& x, const NodeDesc* list, int nb, int bi, Shared& sh) {
+__device__ __forceinline__ void wide_setup(const Ctx<false>& x, const NodeDesc* list, int nb, int bi, Shared<BLOCK, true>& sh) {
   const int mtry = x.T->mtry, tid = threadIdx.x, q = bi & 1;
   if (tid < nb) {
     const NodeDesc d = list[tid];
@@ -960,8 +1157,8 @@ __device__ __forceinline__ void wide_setup(const Ctx& x, const NodeDesc* list, i
 // column's record (decided with the other nodes' after the phase) and zeroes
 // the bins it read, while the next batch's metadata is staged.
 template <int BLOCK>
-__device__ __forceinline__ void wide_phase(const Ctx& x, const NodeDesc* list, uint32_t n_wide, int nb_max, int hc, uint32_t rec_base,
-                           uint8_t* lds, Shared& sh) {
+__device__ __forceinline__ void wide_phase(const Ctx<false>& x, const NodeDesc* list, uint32_t n_wide, int nb_max, int hc, uint32_t rec_base,
+                           uint8_t* lds, Shared<BLOCK, true>& sh) {
   constexpr int NW = BLOCK / kWave;
   const GrowArgs& a = *x.a;
   const int mtry = x.T->mtry;
@@ -1095,15 +1292,14 @@ __device__ __forceinline__ void wide_phase(const Ctx& x, const NodeDesc* list, u
 // the way.  Rows of leaves are not touched again.  Four chunks per wave are in
 // flight at a time, so that their dependent loads (chunk, entry, code)
 // overlap.  `cur` is in LDS or in global memory (inlined once for each).
-template <int BLOCK, bool WIDE>
-__device__ __forceinline__ void partition_level(const Ctx& x, uint64_t* __restrict__ out, Cursor* cur,
+template <int BLOCK, bool WIDE, bool LC>
+__device__ __forceinline__ void partition_level(const Ctx<LC>& x, uint64_t* __restrict__ out, Cursor* cur,
                                                 uint32_t n_chunks) {
   constexpr int NW = BLOCK / kWave;
   constexpr int UP = 4;
-  const GrowArgs& a = *x.a;
   const int lane = (int)lane_id();
   const size_t sst = (size_t)cand_stride(x.T->mtry);
-  for (uint32_t c0 = threadIdx.x / kWave; c0 < n_chunks; c0 += UP * NW) {
+  for (uint32_t c0 = (uint32_t)team_tid<BLOCK>() / kWave; c0 < n_chunks; c0 += UP * NW) {
     uint32_t rk[UP], col[UP], bin[UP], sci[UP], pos[UP];
     uint64_t e[UP];
     bool mv[UP], go_left[UP];
@@ -1128,9 +1324,9 @@ __device__ __forceinline__ void partition_level(const Ctx& x, uint64_t* __restri
       if (mv[u]) {
         if constexpr (WIDE)
           code = sci[u] ? x.sc.side[(size_t)pos[u] * sst + (sci[u] - 1u)]
-                        : a.rcodes[(size_t)entry_row(e[u]) * a.rC + col[u]];
+                        : x.row(entry_row(e[u]))[col[u]];
         else
-          code = a.rcodes[(size_t)entry_row(e[u]) * a.rC + col[u]];
+          code = x.row(entry_row(e[u]))[col[u]];
       }
       go_left[u] = mv[u] && code <= bin[u];
     }
@@ -1161,9 +1357,9 @@ __device__ __forceinline__ void partition_level(const Ctx& x, uint64_t* __restri
 // bootstrap).  `cnt` is in LDS or in global memory (inlined once for each).
 template <int BLOCK>
 __device__ __forceinline__ void bootstrap_counts(const TreeTask& T, int64_t n, uint32_t* cnt) {
-  const int tid = threadIdx.x;
+  const int tid = team_tid<BLOCK>();
   for (int64_t i = tid; i < n; i += BLOCK) cnt[i] = T.bootstrap ? 0u : 1u;
-  __syncthreads();
+  team_sync<BLOCK>();
   if (T.bootstrap) {
     const int64_t nblk = (n + 3) / 4;
     for (int64_t b = tid; b < nblk; b += BLOCK) {
@@ -1172,7 +1368,7 @@ __device__ __forceinline__ void bootstrap_counts(const TreeTask& T, int64_t n, u
       for (int w = 0; w < 4; ++w)
         if (4 * b + w < n) atomicAdd(&cnt[scale_draw(r.w[w], (uint32_t)n)], 1u);
     }
-    __syncthreads();
+    team_sync<BLOCK>();
   }
 }
 
@@ -1195,10 +1391,13 @@ __device__ __forceinline__ void bootstrap_counts(const TreeTask& T, int64_t n, u
 // keep its leaner register allocation).  GROUPED: the launch has groups (the
 // kernels of launches without compile the group logic out, which keeps their
 // register allocation as it was).
-template <int BLOCK, bool WIDE, bool GROUPED>
-__device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T, const Scratch& sc, uint8_t* lds, Shared& sh) {
+// LC: the code matrix is in the LDS, at lcodes.  nbins: the columns' bin counts,
+// in the LDS.
+template <int BLOCK, bool WIDE, bool GROUPED, bool LC>
+__device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T, const Scratch& sc, uint8_t* lds,
+                                           Shared<BLOCK, WIDE>& sh, const uint16_t* nbins, const uint8_t* lcodes) {
   constexpr int NW = BLOCK / kWave;
-  const int tid = threadIdx.x, wid = tid / kWave, lane = (int)lane_id();
+  const int tid = team_tid<BLOCK>(), wid = tid / kWave, lane = (int)lane_id();
   const int64_t n = T.n_train;
   const int32_t* train = T.train_off >= 0 ? a.train_rows + T.train_off : nullptr;
   const int mtry = T.mtry;
@@ -1272,7 +1471,7 @@ __device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T,
     sh.part = 0;
     sh.resume = 0;
   }
-  __syncthreads();
+  team_sync<BLOCK>();
 
   // threads that draw candidates each own a C-byte row of the LDS union area
   const int n_draw = min(BLOCK, (int)(a.union_bytes / (uint32_t)a.C));
@@ -1286,7 +1485,7 @@ __device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T,
     while (level_cnt > 0) {
       const Level2 C = cur ? sc.L1 : sc.L0;  // this level
       const Level2 X = cur ? sc.L0 : sc.L1;  // the next level
-      const Ctx x{&a, &T, sc, C.buf, X.buf, C.mstart, C.mend, C.mN, C.mS, C.mQ};
+      const Ctx<LC> x{&a, &T, lcodes, sc, C.buf, X.buf, C.mstart, C.mend, C.mN, C.mS, C.mQ};
       // (a) - (c) are skipped by a member that grows on from the parting level
       if (!GROUPED || !sh.resume) {
         ++levels;
@@ -1310,7 +1509,7 @@ __device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T,
               const uint32_t k = qk[e], j1 = qj[e];
               draw_candidates(lds + tid, n_draw, T.seed, level_lo + k, (uint32_t)T.tree, a.C, mtry,
                               sc.cand + (size_t)k * cand_stride(mtry), j1 ? sc.btask + (size_t)(j1 - 1) * mtry : nullptr,
-                              sh.nbins);
+                              nbins);
             }
             q_head += n_q;
           };
@@ -1373,12 +1572,12 @@ __device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T,
               }
             } else if (open) {
               draw_candidates(lds + tid, n_draw, T.seed, level_lo + k, (uint32_t)T.tree, a.C, mtry,
-                              sc.cand + (size_t)k * cand_stride(mtry), bt, sh.nbins);
+                              sc.cand + (size_t)k * cand_stride(mtry), bt, nbins);
             }
           }
           if (queue_draws && q_tail > q_head) draw_queued(q_tail - q_head);
         }
-        __syncthreads();
+        team_sync<BLOCK>();
         const uint32_t n_big = sh.cnt[1], n_huge = sh.cnt[2];
         // (b) wide nodes, in batches, with the whole workgroup
         if (WIDE && n_huge > 0) {
@@ -1389,7 +1588,7 @@ __device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T,
           // (records of wide node j go after the large nodes', at n_big + j)
           else  // column chunks of a multiple of 8 (the LDS holds at least 8 columns)
             hc = max(8, (int)a.union_bytes / (a.bstride * 8) / 8 * 8);
-          wide_phase<BLOCK>(x, sc.huge, n_huge, nb, hc, n_big, lds, sh);
+          if constexpr (WIDE) wide_phase<BLOCK>(x, sc.huge, n_huge, nb, hc, n_big, lds, sh);
         }
         // (c) large-node columns and small-node segments, one wave each; a wave
         // takes its next task from the queue head when it starts one (their costs
@@ -1408,21 +1607,21 @@ __device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T,
             uint32_t t_next = 0;
             if (lane == 0) t_next = atomicAdd(&sh.next_task, 1u);
             if (t < n_big_tasks)
-              big_task(x, t / per_big, (int)(t % per_big) * a.big_cols, wl);
+              big_task<LC>(x, t / per_big, (int)(t % per_big) * a.big_cols, wl);
             else if (t < first[1])
-              small_task<4>(x, sc.seg[0], t - first[0], sh.cnt[3], wl);
+              small_task<4, LC>(x, sc.seg[0], t - first[0], sh.cnt[3], wl);
             else if (t < first[2])
-              small_task<8>(x, sc.seg[1], t - first[1], sh.cnt[4], wl);
+              small_task<8, LC>(x, sc.seg[1], t - first[1], sh.cnt[4], wl);
             else if (t < first[3])
-              small_task<16>(x, sc.seg[2], t - first[2], sh.cnt[5], wl);
+              small_task<16, LC>(x, sc.seg[2], t - first[2], sh.cnt[5], wl);
             else if (t < first[4])
-              small_task<32>(x, sc.seg[3], t - first[3], sh.cnt[6], wl);
+              small_task<32, LC>(x, sc.seg[3], t - first[3], sh.cnt[6], wl);
             else
-              rank_task(x, sc.seg[4], t - first[4], sh.cnt[7], wl);
+              rank_task<LC>(x, sc.seg[4], t - first[4], sh.cnt[7], wl);
             t = read_lane(t_next, 0);
           }
         }
-        __syncthreads();
+        team_sync<BLOCK>();
         if (GROUPED && sh.part) {
           // the members' trees part at this level: put its searched state aside
           // (the open nodes' entries lie in [0, n_inbag)); the first member goes on
@@ -1452,7 +1651,7 @@ __device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T,
             uint4* dst = reinterpret_cast<uint4*>(sc.SN.side);
             for (uint32_t i = tid; i < ni * (uint32_t)cand_stride(mtry) / 16u; i += BLOCK) dst[i] = src[i];
           }
-          __syncthreads();  // (every thread has read the flag)
+          team_sync<BLOCK>();  // (every thread has read the flag)
           if (tid == 0) {
             sh.part = 0;
             sh.vi = 0;
@@ -1555,7 +1754,7 @@ __device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T,
         n_split += total;
         n_chunks += ctotal;
       }
-      __syncthreads();
+      team_sync<BLOCK>();
       if ((int64_t)next_id + 2 * (int64_t)n_split > T.capacity ||
           (int64_t)n_chunks > a.n_cap / 64 + a.n_cap / 2 + 2) {
         // cannot happen for consistent inputs: every child holds an in-bag row
@@ -1565,10 +1764,10 @@ __device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T,
       }
       // (f) partition the entries of split nodes into their children's segments
       if (lds_cur)
-        partition_level<BLOCK, WIDE>(x, X.buf, lcur, n_chunks);
+        partition_level<BLOCK, WIDE, LC>(x, X.buf, lcur, n_chunks);
       else
-        partition_level<BLOCK, WIDE>(x, X.buf, sc.cur, n_chunks);
-      __syncthreads();
+        partition_level<BLOCK, WIDE, LC>(x, X.buf, sc.cur, n_chunks);
+      team_sync<BLOCK>();
       // (g) the boundary between each pair of children, and their sums of w y^2
       for (uint32_t r = tid; r < n_split; r += BLOCK) {
         const Cursor c = lds_cur ? lcur[r] : sc.cur[r];
@@ -1584,7 +1783,7 @@ __device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T,
         sh.next_task = NW;
         if (GROUPED) sh.resume = 0;
       }
-      __syncthreads();
+      team_sync<BLOCK>();
       level_lo = next_id;
       level_cnt = 2 * n_split;
       next_id += 2 * n_split;
@@ -1668,7 +1867,7 @@ __device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T,
         uint4* dst = reinterpret_cast<uint4*>(sc.side);
         for (uint32_t i = tid; i < ni * (uint32_t)cand_stride(mtry) / 16u; i += BLOCK) dst[i] = src[i];
       }
-      __syncthreads();  // (every thread has read the member index)
+      team_sync<BLOCK>();  // (every thread has read the member index)
       if (tid < 3 + kSegClasses) sh.cnt[tid] = tid == 1 ? f_big : tid == 2 ? f_huge : 0u;
     }
     if (tid == 0) {
@@ -1678,9 +1877,39 @@ __device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T,
       sh.vbase = nbase;
       sh.resume = 1;
     }
-    __syncthreads();
+    team_sync<BLOCK>();
   }
   (void)wid;
+}
+
+// A team's loop over the queue of task groups, with scratch area `area`.
+template <int BLOCK, bool WIDE, bool GROUPED, bool LC>
+__device__ __forceinline__ void grow_queue(const GrowArgs& a, uint32_t area, uint8_t* lds, Shared<BLOCK, WIDE>& sh,
+                                           const uint16_t* nbins, const uint8_t* lcodes) {
+  const int tid = team_tid<BLOCK>();
+  Scratch sc;
+  carve(&sc, reinterpret_cast<uintptr_t>(a.scratch) + a.scratch_stride * area, a.n_cap, a.mtry_max, WIDE, GROUPED);
+  for (;;) {
+    if (tid == 0) sh.task = atomicAdd(a.queue, 1u);
+    team_sync<BLOCK>();
+    const uint32_t g = sh.task;
+    if (g >= (uint32_t)a.n_groups) return;
+    // the group's members (the host keeps a group within kGroupMax tasks)
+    const int32_t gf = GROUPED ? a.group_first[g] : (int32_t)g;
+    const int K = GROUPED ? min(a.group_first[g + 1] - gf, kGroupMax) : 1;
+    if (tid == 0) sh.gk = K;
+    if (tid < K) {
+      const int32_t ti = GROUPED ? a.group_task[gf + tid] : (int32_t)g;
+      sh.gtask[tid] = ti;
+      sh.gmin[tid] = a.tasks[ti].min_node;
+      sh.gbase[tid] = a.tasks[ti].node_base;
+      sh.ginbag[tid] = a.tasks[ti].inbag_off;
+    }
+    team_sync<BLOCK>();
+    const TreeTask T = a.tasks[rfl((uint32_t)sh.gtask[0])];
+    grow_group<BLOCK, WIDE, GROUPED, LC>(a, T, sc, lds, sh, nbins, lcodes);
+    team_sync<BLOCK>();
+  }
 }
 
 // OCC waves per SIMD (at most 512 / OCC VGPRs): the persistent kernel is bound
@@ -1689,36 +1918,41 @@ __device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T,
 template <int BLOCK, bool WIDE, int OCC, bool GROUPED>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(OCC))) void k_grow(GrowArgs a) {
   extern __shared__ __align__(16) uint8_t lds[];
-  __shared__ Shared sh;
+  __shared__ Shared<BLOCK, WIDE> sh;
+  __shared__ uint16_t nbins[256];
   // a code at or above its column's bin count (flagged by the prepare kernel,
   // which ran before on this stream) would index past a histogram: grow nothing
   // and let the fit report EINVAL
   if (__atomic_load_n(a.status, __ATOMIC_RELAXED) & kStatusBadCode) return;
-  Scratch sc;
-  carve(&sc, reinterpret_cast<uintptr_t>(a.scratch) + a.scratch_stride * blockIdx.x, a.n_cap, a.mtry_max, WIDE,
-        GROUPED);
-  for (int c = threadIdx.x; c < a.C; c += BLOCK) sh.nbins[c] = (uint16_t)a.n_bins[c];
-  for (;;) {
-    if (threadIdx.x == 0) sh.task = atomicAdd(a.queue, 1u);
-    __syncthreads();
-    const uint32_t g = sh.task;
-    if (g >= (uint32_t)a.n_groups) return;
-    // the group's members (the host keeps a group within kGroupMax tasks)
-    const int32_t gf = GROUPED ? a.group_first[g] : (int32_t)g;
-    const int K = GROUPED ? min(a.group_first[g + 1] - gf, kGroupMax) : 1;
-    if (threadIdx.x == 0) sh.gk = K;
-    if (threadIdx.x < K) {
-      const int32_t ti = GROUPED ? a.group_task[gf + threadIdx.x] : (int32_t)g;
-      sh.gtask[threadIdx.x] = ti;
-      sh.gmin[threadIdx.x] = a.tasks[ti].min_node;
-      sh.gbase[threadIdx.x] = a.tasks[ti].node_base;
-      sh.ginbag[threadIdx.x] = a.tasks[ti].inbag_off;
-    }
-    __syncthreads();
-    const TreeTask T = a.tasks[rfl((uint32_t)sh.gtask[0])];
-    grow_group<BLOCK, WIDE, GROUPED>(a, T, sc, lds, sh);
-    __syncthreads();
-  }
+  for (int c = threadIdx.x; c < a.C; c += BLOCK) nbins[c] = (uint16_t)a.n_bins[c];
+  team_sync<BLOCK>();
+  grow_queue<BLOCK, WIDE, GROUPED, false>(a, blockIdx.x, lds, sh, nbins, nullptr);
+}
+
+// Trees of a deep queue over a small code matrix: a workgroup holds the matrix in
+// its LDS, and each of its waves is a team of its own, growing one tree after the
+// other.  The waves never wait for one another.  Gathering a row's codes from
+// memory took a cache lookup per lane (the tuning grid's launch: 1.3e11, 67 % of
+// the address unit's cycles) and its latency at every candidate; from the LDS
+// the lookups fall to 2.7e10.  One matrix for sixteen waves leaves each 4.9 KB of
+// the 160 KB (2220 rows x 35 columns) and 128 registers at four waves per SIMD,
+// against 96 registers and five waves for one-wave workgroups (twelve teams
+// at 168 registers: 302 ms).  Grid 287 -> 261 ms, leave-one-kernel-out 33.7 ->
+// 32.2 ms, with the small nodes' sums by matrix instructions.
+template <bool GROUPED>
+__global__ __launch_bounds__(kTeams* kWave) __attribute__((amdgpu_waves_per_eu(kTeams / 4))) void k_grow_teams(GrowArgs a) {
+  extern __shared__ __align__(16) uint8_t lds[];
+  if (__atomic_load_n(a.status, __ATOMIC_RELAXED) & kStatusBadCode) return;  // (as in k_grow)
+  const int tid = (int)threadIdx.x, team = (int)rfl((uint32_t)tid / kWave);
+  uint8_t* lcodes = lds;
+  uint16_t* nbins = reinterpret_cast<uint16_t*>(lds + a.lcode_bytes);
+  for (int c = tid; c < a.C; c += kTeams * kWave) nbins[c] = (uint16_t)a.n_bins[c];
+  const uint32_t total = a.lcode_rows * (uint32_t)a.C;
+  for (uint32_t i = (uint32_t)tid; i < total; i += kTeams * kWave) lcodes[i] = a.codes[i];
+  __syncthreads();
+  uint8_t* own = lds + a.lcode_bytes + 512 + (size_t)team * a.team_bytes;
+  auto& sh = *reinterpret_cast<Shared<kWave, false>*>(own + a.union_bytes);
+  grow_queue<kWave, false, GROUPED, true>(a, blockIdx.x * (uint32_t)kTeams + (uint32_t)team, own, sh, nbins, lcodes);
 }
 
 // The grow kernel of this translation unit for a launch shape (block, wide
@@ -1744,7 +1978,11 @@ const void* grow_kernel(bool wide, int occ) {
   }
 }
 
-const void* grow_kernel_block(int block, bool wide, int occ) {
+const void* grow_kernel_block(int block, bool wide, int occ, bool teams) {
+  if (teams) {
+    constexpr bool G = AIWC_GROW_GROUPED != 0;
+    return reinterpret_cast<const void*>(k_grow_teams<G>);
+  }
   switch (block) {
     case 64: return grow_kernel<64>(wide, occ);
     case 128: return grow_kernel<128>(wide, occ);
@@ -1759,7 +1997,9 @@ const void* grow_kernel_block(int block, bool wide, int occ) {
 #if AIWC_GROW_GROUPED
 }  // namespace
 
-const void* grow_kernel_grouped(int block, bool wide, int occ) { return grow_kernel_block(block, wide, occ); }
+const void* grow_kernel_grouped(int block, bool wide, int occ, bool teams) {
+  return grow_kernel_block(block, wide, occ, teams);
+}
 
 }  // namespace aiwc
 #else
@@ -1807,6 +2047,8 @@ __global__ void k_set_i32(int32_t* p, int32_t v) {
 // histograms of a batch of wide nodes, or the candidate-draw rows, whichever is
 // largest (the three are used in different phases of a level).
 struct Layout {
+  uint32_t lds_bytes;    // dynamic LDS of a workgroup
+  uint32_t lcode_bytes, team_bytes;  // with teams: the code matrix, and a team's union and Shared
   uint32_t union_bytes;
   uint32_t wave_bytes;
   int32_t bstride;
@@ -1814,8 +2056,8 @@ struct Layout {
   int32_t big_cols;    // large-node columns per wave task (the wave area holds that many histograms)
 };
 
-Layout grow_layout(const GrowConfig& cfg, int32_t mtry_max, int32_t C) {
-  Layout L;
+Layout grow_layout(const GrowConfig& cfg, int32_t mtry_max, int32_t C, int64_t n) {
+  Layout L{};
   L.bstride = (std::max(cfg.bins_max, 1) + 63) / 64 * 64;
   L.big_stride = (std::max(cfg.bins_max, 1) + 3) / 4 * 4;
   // a wave's histogram, or the staging of its small-node task (the rank task's
@@ -1833,13 +2075,30 @@ Layout grow_layout(const GrowConfig& cfg, int32_t mtry_max, int32_t C) {
     wide = std::max(std::max(waves, want), (size_t)8 * L.bstride * 8);
   }
   L.union_bytes = (uint32_t)std::max(std::max(waves, wide), draw);
+  L.lds_bytes = L.union_bytes;
+  // teams: the one-wave shape of deep queues, when the code matrix and every
+  // team's area fit the LDS together
+  if (cfg.block == kWave && cfg.occupancy == 5 && !grow_has_wide_phase(cfg) && cfg.wg_per_cu == 0) {
+    const size_t lcodes = ((size_t)n * C + 255) / 256 * 256;
+    const size_t uni = ((size_t)L.union_bytes + 15) / 16 * 16;
+    const size_t team = uni + (sizeof(Shared<kWave, false>) + 15) / 16 * 16;
+    const size_t total = lcodes + 512 + kTeams * team;
+    if (total <= device_info().lds_per_block) {
+      L.lds_bytes = (uint32_t)total;
+      L.lcode_bytes = (uint32_t)lcodes;
+      L.union_bytes = (uint32_t)uni;
+      L.team_bytes = (uint32_t)team;
+    }
+  }
   return L;
 }
 
-const void* grow_kernel_for(const GrowConfig& cfg, bool wide, bool grouped) {
-  return grouped ? grow_kernel_grouped(cfg.block, wide, cfg.occupancy)
-                 : grow_kernel_block(cfg.block, wide, cfg.occupancy);
+const void* grow_kernel_for(const GrowConfig& cfg, const Layout& L, bool grouped) {
+  const bool wide = grow_has_wide_phase(cfg), teams = L.team_bytes > 0;
+  return grouped ? grow_kernel_grouped(cfg.block, wide, cfg.occupancy, teams)
+                 : grow_kernel_block(cfg.block, wide, cfg.occupancy, teams);
 }
+int grow_threads(const GrowConfig& cfg, const Layout& L) { return L.team_bytes > 0 ? kTeams * kWave : cfg.block; }
 
 int occupancy(const void* kernel, int block, uint32_t lds) {
   int nb = 0;
@@ -1873,20 +2132,24 @@ void launch_prepare(const uint8_t* codes, int64_t n, int32_t C, const int32_t* d
   AIWC_HIP(hipGetLastError());
 }
 
-int grow_grid_size(const GrowConfig& cfg, int64_t n_tasks, int32_t mtry_max, int32_t C, bool grouped) {
-  const uint32_t lds = grow_layout(cfg, mtry_max, C).union_bytes;
-  if (lds > device_info().lds_per_block) fail(AIWC_RF_EINVAL, "grow kernel LDS exceeds the device limit");
-  int per_cu = occupancy(grow_kernel_for(cfg, grow_has_wide_phase(cfg), grouped), cfg.block, lds);
+int grow_teams(const GrowConfig& cfg, int32_t mtry_max, int32_t C, int64_t n) {
+  return grow_layout(cfg, mtry_max, C, n).team_bytes > 0 ? kTeams : 1;
+}
+
+int grow_grid_size(const GrowConfig& cfg, int64_t n_tasks, int32_t mtry_max, int32_t C, int64_t n, bool grouped) {
+  const Layout L = grow_layout(cfg, mtry_max, C, n);
+  if (L.lds_bytes > device_info().lds_per_block) fail(AIWC_RF_EINVAL, "grow kernel LDS exceeds the device limit");
+  int per_cu = occupancy(grow_kernel_for(cfg, L, grouped), grow_threads(cfg, L), L.lds_bytes);
   if (per_cu < 1) fail(AIWC_RF_ENOMEM, "grow kernel does not fit the device (LDS or registers)");
   if (cfg.wg_per_cu > 0) per_cu = std::min(per_cu, cfg.wg_per_cu);
-  const int64_t slots = (int64_t)device_info().cus * per_cu;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(slots, n_tasks));
+  const int64_t slots = (int64_t)device_info().cus * per_cu, teams = L.team_bytes > 0 ? kTeams : 1;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(slots, (n_tasks + teams - 1) / teams));
 }
 
 namespace {
 
-GrowArgs grow_args(const GrowConfig& cfg, const GrowLaunch& g, int32_t C, const int32_t* d_n_bins, const int64_t* y_fp,
-                   uint32_t* d_status, int32_t mtry_max) {
+GrowArgs grow_args(const GrowConfig& cfg, const Layout& L, const GrowLaunch& g, int32_t C, const int32_t* d_n_bins,
+                   const int64_t* y_fp, uint32_t* d_status, int32_t mtry_max) {
   GrowArgs a;
   a.codes = g.codes;
   a.C = C;
@@ -1916,7 +2179,9 @@ GrowArgs grow_args(const GrowConfig& cfg, const GrowLaunch& g, int32_t C, const 
   a.huge_min = cfg.huge_min;
   a.wide_sums = cfg.wide_sums ? 1 : 0;
   a.scratch_stride = grow_scratch_bytes(g.n_cap, mtry_max, grow_has_wide_phase(cfg), g.group_first != nullptr);
-  const Layout L = grow_layout(cfg, mtry_max, C);
+  a.lcode_rows = (uint32_t)g.n;
+  a.lcode_bytes = L.lcode_bytes;
+  a.team_bytes = L.team_bytes;
   a.union_bytes = L.union_bytes;
   a.wave_bytes = L.wave_bytes;
   a.bstride = L.bstride;
@@ -1977,24 +2242,27 @@ hipKernelNodeParams node_params(const void* fn, int grid, int block, uint32_t ld
 }  // namespace
 
 int effective_big_cols(const GrowConfig& cfg, int32_t mtry_max, int32_t C) {
-  const Layout L = grow_layout(cfg, mtry_max, C);
+  const Layout L = grow_layout(cfg, mtry_max, C, 0);
   return cfg.big_cols > 0 ? std::min(cfg.big_cols, L.big_cols) : L.big_cols;
 }
 
 void launch_grow(const GrowConfig& cfg, const GrowLaunch& g, int32_t C, const int32_t* d_n_bins, const int64_t* y_fp,
                  uint32_t* d_status, int32_t mtry_max, int grid, hipStream_t s) {
-  GrowArgs a = grow_args(cfg, g, C, d_n_bins, y_fp, d_status, mtry_max);
-  const void* kernel = grow_kernel_for(cfg, grow_has_wide_phase(cfg), g.group_first != nullptr);
+  const Layout L = grow_layout(cfg, mtry_max, C, g.n);
+  GrowArgs a = grow_args(cfg, L, g, C, d_n_bins, y_fp, d_status, mtry_max);
+  const void* kernel = grow_kernel_for(cfg, L, g.group_first != nullptr);
   void* args[] = {&a};
-  AIWC_HIP(hipLaunchKernel(kernel, dim3((unsigned)grid), dim3((unsigned)cfg.block), args, a.union_bytes, s));
+  AIWC_HIP(hipLaunchKernel(kernel, dim3((unsigned)grid), dim3((unsigned)grow_threads(cfg, L)), args, L.lds_bytes, s));
   AIWC_HIP(hipGetLastError());
 }
 
 bool launch_fit_graph(const GrowConfig& cfg, const GrowLaunch& g, const uint8_t* codes, int64_t n, int32_t C,
                       const int32_t* d_n_bins, const double* y, int64_t* y_fp, uint32_t* d_status, int32_t mtry_max,
                       int grid, hipStream_t s) {
-  GrowArgs a = grow_args(cfg, g, C, d_n_bins, y_fp, d_status, mtry_max);
-  const void* kernel = grow_kernel_for(cfg, grow_has_wide_phase(cfg), g.group_first != nullptr);
+  const Layout L = grow_layout(cfg, mtry_max, C, g.n);
+  GrowArgs a = grow_args(cfg, L, g, C, d_n_bins, y_fp, d_status, mtry_max);
+  const void* kernel = grow_kernel_for(cfg, L, g.group_first != nullptr);
+  const int threads = grow_threads(cfg, L);
   const int pb = prepare_blocks(n, C);
   int32_t Cp = padded_cols(C);
   uint32_t* queue = g.queue;
@@ -2005,10 +2273,10 @@ bool launch_fit_graph(const GrowConfig& cfg, const GrowLaunch& g, const uint8_t*
   void* grow_args_v[] = {&a};
   const hipKernelNodeParams p_init = node_params(reinterpret_cast<const void*>(k_init), 1, 64, 0, init_args);
   const hipKernelNodeParams p_prep = node_params(reinterpret_cast<const void*>(k_prepare), pb, 256, 0, prep_args);
-  const hipKernelNodeParams p_grow = node_params(kernel, grid, cfg.block, a.union_bytes, grow_args_v);
+  const hipKernelNodeParams p_grow = node_params(kernel, grid, threads, L.lds_bytes, grow_args_v);
   int dev = 0;
   AIWC_HIP(hipGetDevice(&dev));
-  const GraphKey key{dev, kernel, cfg.block, grid, pb, a.union_bytes};
+  const GraphKey key{dev, kernel, threads, grid, pb, L.lds_bytes};
   static uint64_t clock = 0;
   std::lock_guard<std::mutex> lk(graph_mu());
   auto& cache = graph_cache();

@@ -270,9 +270,13 @@ void launch_prepare(const uint8_t* codes, int64_t n, int32_t C, const int32_t* d
 size_t grow_scratch_bytes(int64_t n_cap, int32_t mtry_max, bool wide, bool grouped);
 // Workgroups of a persistent grow launch over n_tasks work items (grouped: the
 // kernel for launches with task groups).
-int grow_grid_size(const GrowConfig& cfg, int64_t n_tasks, int32_t mtry_max, int32_t C, bool grouped = false);
+int grow_grid_size(const GrowConfig& cfg, int64_t n_tasks, int32_t mtry_max, int32_t C, int64_t n,
+                   bool grouped = false);
+// Scratch areas a grow workgroup uses: one per team of it (n: rows of the code
+// matrix, which a workgroup of several teams holds in its LDS).
+int grow_teams(const GrowConfig& cfg, int32_t mtry_max, int32_t C, int64_t n);
 // The grow kernels for launches with task groups (fit_grouped.hip).
-const void* grow_kernel_grouped(int block, bool wide, int occ);
+const void* grow_kernel_grouped(int block, bool wide, int occ, bool teams);
 // The buffers of one grow launch: the codes (dense and row-padded), the
 // training-row lists, the tasks and everything the trees write.
 struct GrowLaunch {
@@ -289,6 +293,7 @@ struct GrowLaunch {
   uint32_t* queue;
   uint8_t* scratch;
   int64_t n_cap;
+  int64_t n;  // rows of the code matrix
   // groups of tasks grown together (null: each task alone)
   const int32_t* group_task = nullptr;
   const int32_t* group_first = nullptr;
