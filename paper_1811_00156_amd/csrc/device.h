@@ -144,15 +144,6 @@ __device__ __forceinline__ double split_score(int64_t SL, uint32_t NL, int64_t S
   const double r = div_pos(b * b, (double)NR);
   return l + r;
 }
-// The same score for a node that weighs below 512: |S_L|, |S_R| < 511 * 2^22 <
-// 2^31, so each converts exactly from 32 bits (one conversion instead of
-// i64_to_f64's three) to the same double.
-__device__ __forceinline__ double split_score32(int32_t SL, uint32_t NL, int32_t SR, uint32_t NR) {
-  const double a = (double)SL, b = (double)SR;
-  const double l = div_pos(a * a, (double)NL);
-  const double r = div_pos(b * b, (double)NR);
-  return l + r;
-}
 __device__ __forceinline__ double parent_score(int64_t S, uint64_t N) {
   const double a = i64_to_f64(S);
   return div_pos(a * a, (double)N);
@@ -250,54 +241,31 @@ __device__ __forceinline__ T wave_sum(T v) {
   return read_lane(wave_incl_scan<T>(v), kWave - 1);
 }
 
-// Arg-max of (score, key) over the wave: the largest score, then the smallest
-// key.  Every lane returns the winner and the lane that holds it (lowest lane
-// among equals).  A prefix arg-max with the scan's DPP pattern leaves the
-// wave's winner in the last lane.
+// A wave's best split: its score, key and lane.
 struct ArgMax {
   double score;
   int32_t key;
   int32_t lane;
 };
-__device__ __forceinline__ bool argmax_better(double s1, int32_t k1, int32_t l1, double s2, int32_t k2, int32_t l2) {
-  if (s1 != s2) return s1 > s2;
-  if (k1 != k2) return k1 < k2;
-  return l1 < l2;
-}
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ void argmax_step(ArgMax& m) {
-  constexpr uint64_t kMinusInf = 0xFFF0000000000000ull;
-  const double s = __builtin_bit_cast(double, dpp64<CTRL, ROW_MASK>(kMinusInf, __builtin_bit_cast(uint64_t, m.score)));
-  const int32_t k = (int32_t)dpp32<CTRL, ROW_MASK>(0x7FFFFFFFu, (uint32_t)m.key);
-  const int32_t l = (int32_t)dpp32<CTRL, ROW_MASK>(0x7FFFFFFFu, (uint32_t)m.lane);
-  if (argmax_better(s, k, l, m.score, m.key, m.lane)) {
-    m.score = s;
-    m.key = k;
-    m.lane = l;
-  }
-}
-__device__ __forceinline__ ArgMax wave_argmax(double score, int32_t key) {
-  ArgMax m{score, key, (int32_t)lane_id()};
-  argmax_step<kDppRowShr1, 0xf>(m);
-  argmax_step<kDppRowShr2, 0xf>(m);
-  argmax_step<kDppRowShr4, 0xf>(m);
-  argmax_step<kDppRowShr8, 0xf>(m);
-  argmax_step<kDppRowBcast15, 0xa>(m);
-  argmax_step<kDppRowBcast31, 0xc>(m);
-  ArgMax r;
-  r.score = __builtin_bit_cast(double, read_lane(__builtin_bit_cast(uint64_t, m.score), kWave - 1));
-  r.key = read_lane(m.key, kWave - 1);
-  r.lane = read_lane(m.lane, kWave - 1);
-  return r;
-}
 
-// The same when lane order is key order (lane l's key below lane l+1's): a wave
-// max of the scores with the scan's DPP pattern, then the lowest lane that holds
+// Arg-max of (score, key) when lane order is key order (lane l's key below lane
+// l+1's): a wave max of the scores with the scan's DPP pattern, then the lowest lane that holds
 // it.  Scores must not be NaN.
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ double max_step(double m) {
   constexpr uint64_t kMinusInf = 0xFFF0000000000000ull;
   const double o = __builtin_bit_cast(double, dpp64<CTRL, ROW_MASK>(kMinusInf, __builtin_bit_cast(uint64_t, m)));
+  return o > m ? o : m;
+}
+// One step of a wave maximum of values of which the largest is not negative: lanes
+// without a source take 0, and a maximum may count a lane twice, so no identity
+// and no row mask are needed.
+template <int CTRL>
+__device__ __forceinline__ double max_step0(double m) {
+  const uint64_t v = __builtin_bit_cast(uint64_t, m);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, 0xf, 0xf, true);
+  const double o = __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
   return o > m ? o : m;
 }
 __device__ __forceinline__ ArgMax wave_argmax_lane_ordered(double score, int32_t key) {

@@ -112,7 +112,7 @@ struct Scratch {
   NodeDesc* seg[kSegClasses];  // small nodes by segment width 4 << class
   NodeDesc* big;
   NodeDesc* huge;
-  Rec* recs;  // large node j's candidate i at j * mtry + i; wide node h's at (n_big + h) * mtry + i
+  Rec* recs;  // large node j's task t at j * mtry + t; wide node h's at (n_big + h) * mtry + i
   // entry p of a wide node: its row's codes in the node's candidate columns, at
   // p * cand_stride(mtry) + i (written by the wide batches, read by the partition
   // instead of the row's code line); null when the launch has no wide phase
@@ -403,6 +403,7 @@ struct Ctx {
   const GrowArgs* a;
   const TreeTask* T;
   const uint8_t* lcodes;  // LC: the code matrix in the LDS, rows of C bytes
+  const double* recip;    // reciprocals of the weights below kRecip, in the LDS
   __device__ __forceinline__ RowCodes<LC> row(uint32_t r) const {
     if constexpr (LC)
       return {(const __attribute__((address_space(3))) uint8_t*)(lcodes + r * (uint32_t)a->C)};
@@ -435,15 +436,69 @@ __device__ __forceinline__ uint64_t pack_ns(uint32_t w, int64_t wy) { return ((u
 __device__ __forceinline__ uint32_t packed_n(uint64_t v) { return (uint32_t)((v + (1ull << 44)) >> 45); }
 __device__ __forceinline__ int64_t packed_s(uint64_t v, uint32_t n) { return (int64_t)(v - ((uint64_t)n << 45)); }
 
-// Inclusive wave scan of packed bins of a node that weighs below 512: every
-// prefix of its weights fits 9 bits and of its sums 32 bits (|y_fp| <= 2^22),
-// so the two are scanned as 32-bit words (one DPP add a step) and packed again.
-__device__ __forceinline__ uint64_t scan_packed_small(uint64_t h) {
-  const uint32_t n = packed_n(h);
-  const int32_t s = (int32_t)packed_s(h, n);
-  const uint32_t pn = wave_incl_scan_u32(n);
-  const int32_t ps = (int32_t)wave_incl_scan_u32((uint32_t)s);
-  return pack_ns(pn, ps);
+// Light nodes weigh below kRecip.  Their split scores divide by multiplying with
+// the correctly rounded reciprocal of the weight, from a table in the LDS, and
+// one correction: with r = RN(1 / b) and q = RN(a r), q is within an ulp of a / b
+// and RN(q + r RN(a - b q)) is the correctly rounded quotient, the value the
+// sequence of div_pos gives.  An LDS read and three instructions stand for a
+// quarter-rate reciprocal and seven.  The table's size is what a workgroup of
+// teams has left beside the paper's frame (2220 x 35 codes).
+constexpr int kRecip = 320;
+
+template <int THREADS>
+__device__ __forceinline__ void fill_recip(double* recip) {
+  for (int i = threadIdx.x; i < kRecip; i += THREADS) recip[i] = i ? 1.0 / (double)i : 0.0;
+}
+
+// The score of a light node's split (|S| < kRecip 2^22 < 2^31: both sides'
+// sums convert exactly; Sd, Nd: the node's sum and weight).  A split that leaves
+// a side empty scores the parent's S^2 / N (the table's entry 0 is 0), which
+// never beats the parent, so callers need not leave it out.
+__device__ __forceinline__ double light_score(const double* recip, int32_t SL, uint32_t NL, uint32_t N, double Sd,
+                                              double Nd) {
+  const double rl = recip[NL], rr = recip[N - NL];
+  const double a = (double)SL, b = Sd - a, nl = (double)NL, nr = Nd - nl;
+  const double aa = a * a, bb = b * b;
+  const double ql = aa * rl, qr = bb * rr;
+  return __builtin_fma(__builtin_fma(-nl, ql, aa), rl, ql) + __builtin_fma(__builtin_fma(-nr, qr, bb), rr, qr);
+}
+
+// A light node's bin: the weight in the high word and the sum of w (y + 2^22) >= 0
+// in the low one (below kRecip 2^23 < 2^32, so no carry), which decode for free
+// and scan as two 32-bit words.
+__device__ __forceinline__ uint64_t light_word(uint32_t w, int64_t wy) {
+  return ((uint64_t)w << 32) | (uint32_t)((int32_t)wy + (int32_t)(w << 22));
+}
+__device__ __forceinline__ uint64_t scan_light(uint64_t h) {
+  return ((uint64_t)wave_incl_scan_u32((uint32_t)(h >> 32)) << 32) | wave_incl_scan_u32((uint32_t)h);
+}
+__device__ __forceinline__ int32_t light_sum(uint32_t n, uint32_t biased) { return (int32_t)(biased - (n << 22)); }
+
+// The wave's best split of (score, key), one per lane: the largest score, then
+// the smallest key; scores are -1 (none) or not negative.  Every lane returns it.
+__device__ __forceinline__ ArgMax wave_best(double score, int32_t key) {
+  double m = score;
+  m = max_step0<kDppRowShr1>(m);
+  m = max_step0<kDppRowShr2>(m);
+  m = max_step0<kDppRowShr4>(m);
+  m = max_step0<kDppRowShr8>(m);
+  m = max_step0<kDppRowBcast15>(m);
+  m = max_step0<kDppRowBcast31>(m);
+  ArgMax r;
+  r.score = __builtin_bit_cast(double, read_lane(__builtin_bit_cast(uint64_t, m), kWave - 1));
+  uint64_t at = __ballot(score == r.score);
+  if (at == 0) return ArgMax{-1.0, INT_MAX, 0};
+  r.lane = __builtin_ctzll(at);
+  r.key = read_lane(key, r.lane);
+  for (at &= at - 1; at; at &= at - 1) {
+    const int l = __builtin_ctzll(at);
+    const int32_t k = read_lane(key, l);
+    if (k < r.key) {
+      r.key = k;
+      r.lane = l;
+    }
+  }
+  return r;
 }
 
 // The end of a small node's search, for the W lanes of its segment (one row
@@ -615,7 +670,7 @@ __device__ __forceinline__ void matrix_sums(const SegDigits<W>& A, const uint8_t
   constexpr uint32_t kTop = 0x80808080u;
   v4i_t acc = {0, 0, 0, 0}, acc4 = {0, 0, 0, 0};
   if constexpr (W <= 16) {
-    const uint32_t kb = code * 0x01010101u, kh = kb | kTop;
+    const uint32_t kb = __builtin_amdgcn_perm(0u, code, 0u), kh = kb | kTop;
     const uint32_t* seg = reinterpret_cast<const uint32_t*>(col_codes + (lane & ~(W - 1)));
     uint32_t c[W / 4];
 #pragma unroll
@@ -636,7 +691,7 @@ __device__ __forceinline__ void matrix_sums(const SegDigits<W>& A, const uint8_t
     if constexpr (!B3) A4 = seg_digits<W, true>(planes, lane);
 #pragma unroll
     for (int h = 0; h < SegDigits<W>::H; ++h) {
-      const uint32_t kb = (uint32_t)col_codes[(lane & 0x20) + 16 * h + (lane & 15)] * 0x01010101u;
+      const uint32_t kb = __builtin_amdgcn_perm(0u, col_codes[(lane & 0x20) + 16 * h + (lane & 15)], 0u);
       const uint32_t kh = kb | kTop;
       const v4i_t bm = {(int)(bytes_le<C7>(c4.x, kb, kh) & kTop), (int)(bytes_le<C7>(c4.y, kb, kh) & kTop),
                         (int)(bytes_le<C7>(c4.z, kb, kh) & kTop), (int)(bytes_le<C7>(c4.w, kb, kh) & kTop)};
@@ -692,8 +747,9 @@ __device__ __forceinline__ void small_task(const Ctx<LC>& x, const NodeDesc* lis
                      : __ballot(wy < -(int64_t)(1 << 23) || wy >= (int64_t)(1 << 23)) == 0ull;
   // every column's codes fit 7 bits (at most 128 bins)
   const bool codes7 = a.bstride <= 128;
-  // every node of the wave weighs below 512: its sums fit 32 bits
-  const bool light = __ballot(N >= 512u) == 0ull;
+  // every node of the wave is light: its sums fit 32 bits
+  const bool light = __ballot(N >= (uint32_t)kRecip) == 0ull;
+  const double Sd = i64_to_f64(S), Nd = (double)N;
   uint8_t* planes = area;
   uint64_t* s_pv = reinterpret_cast<uint64_t*>(area);
   SegDigits<W> A;
@@ -785,13 +841,16 @@ __device__ __forceinline__ void small_task(const Ctx<LC>& x, const NodeDesc* lis
         NL = packed_n(acc);
         SL = packed_s(acc, NL);
       }
-      if (valid && NL < N) {
-        const double sc = light ? split_score32((int32_t)SL, NL, (int32_t)S - (int32_t)SL, N - NL)
-                                : split_score(SL, NL, S - SL, N - NL);
-        if (sc > best) {
-          best = sc;
-          best_ib = ((uint32_t)(i0 + i) << 8) | code;
-        }
+      // (a lane without a row holds row 0's code: a split like any other of its
+      // node, equal to that of the highest code not above it)
+      double sc = -1.0;
+      if (light)
+        sc = light_score(x.recip, (int32_t)SL, NL, N, Sd, Nd);
+      else if (valid && NL < N)
+        sc = split_score(SL, NL, S - SL, N - NL);
+      if (sc > best) {
+        best = sc;
+        best_ib = ((uint32_t)(i0 + i) << 8) | code;
       }
     }
     wave_lds_sync();
@@ -828,7 +887,9 @@ __device__ __forceinline__ void rank_task(const Ctx<LC>& x, const NodeDesc* list
   const uint32_t w = valid ? entry_w(e) : 0u;
   const int64_t y = entry_y(e);
   const int64_t wy = (int64_t)w * y;
-  const uint64_t pv = pack_ns(w, wy);
+  const bool light = N < (uint32_t)kRecip;
+  const uint64_t pv = light ? light_word(w, wy) : pack_ns(w, wy);
+  const double Sd = i64_to_f64(S), Nd = (double)N;
   const RowCodes<LC> rowp = x.row(entry_row(e));
   const uint8_t* cand = x.sc.cand + (size_t)k * cand_stride(mtry);
   uint8_t* area = reinterpret_cast<uint8_t*>(&wl);
@@ -882,7 +943,7 @@ __device__ __forceinline__ void rank_task(const Ctx<LC>& x, const NodeDesc* list
       // and each lane takes the one at its own code by a cross-lane read
       const uint64_t h = lane < (int)B ? hv[lane] : 0ull;
       if (lane < (int)B) hv[lane] = 0ull;
-      const uint64_t v = N < 512u ? scan_packed_small(h) : wave_incl_scan<uint64_t>(h);
+      const uint64_t v = light ? scan_light(h) : wave_incl_scan<uint64_t>(h);
       V = lane_pick64(v, code);
       prev_in_lds = false;
     } else {
@@ -896,7 +957,7 @@ __device__ __forceinline__ void rank_task(const Ctx<LC>& x, const NodeDesc* list
         h[u] = u < q && b0 + u < (int)B ? hv[b0 + u] : 0ull;
         loc += h[u];
       }
-      uint64_t v = wave_incl_scan<uint64_t>(loc) - loc;
+      uint64_t v = (light ? scan_light(loc) : wave_incl_scan<uint64_t>(loc)) - loc;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         v += h[u];
@@ -906,20 +967,23 @@ __device__ __forceinline__ void rank_task(const Ctx<LC>& x, const NodeDesc* list
       V = hv[code];  // code < B for every lane (a lane without a row has row 0's)
       prev_in_lds = true;
     }
-    if (valid) {
+    double sc = -1.0;
+    if (light) {
+      const uint32_t NL = (uint32_t)(V >> 32);
+      sc = light_score(x.recip, light_sum(NL, (uint32_t)V), NL, N, Sd, Nd);
+    } else if (valid) {
       const uint32_t NL = packed_n(V);
       if (NL < N) {
         const int64_t SL = packed_s(V, NL);
-        const double sc = N < 512u ? split_score32((int32_t)SL, NL, (int32_t)S - (int32_t)SL, N - NL)
-                                   : split_score(SL, NL, S - SL, N - NL);
-        if (sc > best) {
-          best = sc;
-          best_ib = (i << 8) | (int32_t)code;
-        }
+        sc = split_score(SL, NL, S - SL, N - NL);
       }
     }
+    if (sc > best) {
+      best = sc;
+      best_ib = (i << 8) | (int32_t)code;
+    }
   }
-  const ArgMax am = wave_argmax(best, best_ib);
+  const ArgMax am = wave_best(best, best_ib);
   const bool split = am.score >= 0.0 && am.score - parent_score(S, N) > 0.0;
   const uint32_t col = split ? (uint32_t)s_cand[am.key >> 8] : 0u, bin = (uint32_t)am.key & 0xFF;
   const bool left = split && valid && rowp[col] <= bin;
@@ -936,7 +1000,7 @@ __device__ __forceinline__ ArgMax scan_packed(const uint64_t* hv, int B, uint32_
   const int lane = (int)lane_id();
   if (B <= kWave) {  // one bin per lane
     const uint64_t h = lane < B ? hv[lane] : 0ull;
-    const uint64_t v = N < 512u ? scan_packed_small(h) : wave_incl_scan<uint64_t>(h);
+    const uint64_t v = wave_incl_scan<uint64_t>(h);
     double lbest = -1.0;
     oNL = 0;
     oSL = 0;
@@ -945,8 +1009,7 @@ __device__ __forceinline__ ArgMax scan_packed(const uint64_t* hv, int B, uint32_
       const uint32_t NL = packed_n(v);
       if (NL < N) {
         const int64_t SL = packed_s(v, NL);
-        lbest = N < 512u ? split_score32((int32_t)SL, NL, (int32_t)S - (int32_t)SL, N - NL)
-                         : split_score(SL, NL, S - SL, N - NL);
+        lbest = split_score(SL, NL, S - SL, N - NL);
         oNL = NL;
         oSL = SL;
       }
@@ -962,7 +1025,7 @@ __device__ __forceinline__ ArgMax scan_packed(const uint64_t* hv, int B, uint32_
     h[u] = u < q && b0 + u < B ? hv[b0 + u] : 0ull;
     loc += h[u];
   }
-  uint64_t v = (N < 512u ? scan_packed_small(loc) : wave_incl_scan<uint64_t>(loc)) - loc;
+  uint64_t v = wave_incl_scan<uint64_t>(loc) - loc;
   double lbest = -1.0;
   int32_t lbin = INT_MAX;
   oNL = 0;
@@ -976,8 +1039,7 @@ __device__ __forceinline__ ArgMax scan_packed(const uint64_t* hv, int B, uint32_
     const uint32_t NL = packed_n(v);
     if (b <= B - 2 && NL < N) {
       const int64_t SL = packed_s(v, NL);
-      const double s = N < 512u ? split_score32((int32_t)SL, NL, (int32_t)S - (int32_t)SL, N - NL)
-                                : split_score(SL, NL, S - SL, N - NL);
+      const double s = split_score(SL, NL, S - SL, N - NL);
       if (s > lbest) {
         lbest = s;
         lbin = b;
@@ -1007,6 +1069,7 @@ __device__ __forceinline__ void big_task(const Ctx<LC>& x, uint32_t j, int ci0, 
   const uint32_t end = start + rfl(d.len);
   const uint32_t N = rfl(d.N);
   const int64_t S = d.S;
+  const bool light = N < (uint32_t)kRecip;
   const uint32_t* bt = x.sc.btask + (size_t)j * mtry + ci0;
   int c[G];
 #pragma unroll
@@ -1034,7 +1097,8 @@ __device__ __forceinline__ void big_task(const Ctx<LC>& x, uint32_t j, int ci0, 
     for (int u = 0; u < U; ++u) {
       if (p0 + u * kWave < end) {
         const uint32_t w = entry_w(e[u]);
-        const uint64_t v = pack_ns(w, (int64_t)w * entry_y(e[u]));
+        const int64_t wy = (int64_t)w * entry_y(e[u]);
+        const uint64_t v = light ? light_word(w, wy) : pack_ns(w, wy);
 #pragma unroll
         for (int g = 0; g < G; ++g)
           if (g < gn) atomicAdd((unsigned long long*)&hv[g * gs + (int)code[u][g]], (unsigned long long)v);
@@ -1042,20 +1106,89 @@ __device__ __forceinline__ void big_task(const Ctx<LC>& x, uint32_t j, int ci0, 
     }
   }
   wave_lds_sync();
+  // each lane keeps the best split of its bins over the task's columns, and the
+  // wave's best of all is the task's record
+  double best = -1.0;
+  int32_t key = INT_MAX;  // column of the task << 8 | bin
+  uint32_t bNL = 0;
+  int64_t bSL = 0;
+  const double Sd = i64_to_f64(S), Nd = (double)N;
 #pragma unroll 1
   for (int g = 0; g < gn; ++g) {
-    const uint32_t t = rfl(bt[g]);
-    uint32_t NL;
-    int64_t SL;
-    const ArgMax am = scan_packed(hv + g * gs, (int)(t >> 8), N, S, NL, SL);
-    if (lane == am.lane) {
-      Rec r;
-      r.score = am.score;
-      r.SL = SL;
-      r.NL = NL;
-      r.colbin = ((t & 0xFFu) << 8) | (uint32_t)(am.score >= 0.0 ? am.key : 0);
-      x.sc.recs[(size_t)j * mtry + ci0 + g] = r;
+    const int B = (int)(rfl(bt[g]) >> 8), q = (B + kWave - 1) / kWave, b0 = lane * q;
+    const uint64_t* hg = hv + g * gs;
+    if (light) {
+      if (q == 1) {
+        const uint64_t v = scan_light(lane < B ? hg[lane] : 0ull);
+        const uint32_t NL = (uint32_t)(v >> 32);
+        const int32_t SL = light_sum(NL, (uint32_t)v);
+        const double sc = light_score(x.recip, SL, NL, N, Sd, Nd);
+        if (sc > best) {
+          best = sc;
+          key = (g << 8) | lane;
+          bNL = NL;
+          bSL = SL;
+        }
+      } else {
+        uint64_t h[4];
+        uint64_t loc = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          h[u] = u < q && b0 + u < B ? hg[b0 + u] : 0ull;
+          loc += h[u];
+        }
+        uint64_t v = scan_light(loc) - loc;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (u >= q) break;
+          v += h[u];
+          const uint32_t NL = (uint32_t)(v >> 32);
+          const int32_t SL = light_sum(NL, (uint32_t)v);
+          const double sc = light_score(x.recip, SL, NL, N, Sd, Nd);
+          if (sc > best) {
+            best = sc;
+            key = (g << 8) | (b0 + u);
+            bNL = NL;
+            bSL = SL;
+          }
+        }
+      }
+    } else {
+      uint64_t h[4];
+      uint64_t loc = 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        h[u] = u < q && b0 + u < B ? hg[b0 + u] : 0ull;
+        loc += h[u];
+      }
+      uint64_t v = wave_incl_scan<uint64_t>(loc) - loc;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        // an empty bin repeats the previous split, which already won any tie
+        if (u >= q || h[u] == 0) continue;
+        v += h[u];
+        const uint32_t NL = packed_n(v);
+        if (NL < N) {
+          const int64_t SL = packed_s(v, NL);
+          const double sc = split_score(SL, NL, S - SL, N - NL);
+          if (sc > best) {
+            best = sc;
+            key = (g << 8) | (b0 + u);
+            bNL = NL;
+            bSL = SL;
+          }
+        }
+      }
     }
+  }
+  const ArgMax am = wave_best(best, key);
+  if (lane == am.lane) {
+    Rec r;
+    r.score = am.score;
+    r.SL = bSL;
+    r.NL = bNL;
+    r.colbin = am.score >= 0.0 ? (bt[am.key >> 8] & 0xFFu) << 8 | (uint32_t)(am.key & 0xFF) : 0u;
+    x.sc.recs[(size_t)j * mtry + (uint32_t)ci0 / (uint32_t)a.big_cols] = r;
   }
   wave_lds_sync();
 }
@@ -1068,12 +1201,12 @@ struct Decision {
   uint32_t cand;  // the split column's position among the node's candidates
 };
 
-// Decide a large or wide node from its per-column records (columns ascending:
-// keep the first strictly greater score).
-__device__ __forceinline__ Decision decide_from_recs(const Rec* recs, int mtry, int64_t S, uint32_t N) {
+// Decide a large or wide node from its records (columns ascending: keep the first
+// strictly greater score).
+__device__ __forceinline__ Decision decide_from_recs(const Rec* recs, int n_recs, int64_t S, uint32_t N) {
   double best = -1.0;
   int bi = -1;
-  for (int i = 0; i < mtry; ++i) {
+  for (int i = 0; i < n_recs; ++i) {
     const double s = recs[i].score;
     if (s > best) {
       best = s;
@@ -1104,9 +1237,10 @@ struct SharedNarrow {};
 // A team's state in the LDS.
 template <int BLOCK, bool WIDE>
 struct Shared : std::conditional<WIDE, SharedWide, SharedNarrow>::type {
-  uint32_t tmp[BLOCK / kWave + 1];
-  uint64_t tmp64[BLOCK / kWave + 1];
-  uint64_t red[BLOCK / kWave];
+  // (one wave scans and sums without them)
+  uint32_t tmp[BLOCK == kWave ? 1 : BLOCK / kWave + 1];
+  uint64_t tmp64[BLOCK == kWave ? 1 : BLOCK / kWave + 1];
+  uint64_t red[BLOCK == kWave ? 1 : BLOCK / kWave];
   uint32_t cnt[3 + kSegClasses];  // [1] large, [2] wide, [3..] small nodes per segment width
   uint32_t task;
   uint32_t next_task;  // the split-search tasks' queue head
@@ -1395,7 +1529,8 @@ __device__ __forceinline__ void bootstrap_counts(const TreeTask& T, int64_t n, u
 // in the LDS.
 template <int BLOCK, bool WIDE, bool GROUPED, bool LC>
 __device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T, const Scratch& sc, uint8_t* lds,
-                                           Shared<BLOCK, WIDE>& sh, const uint16_t* nbins, const uint8_t* lcodes) {
+                                           Shared<BLOCK, WIDE>& sh, const uint16_t* nbins, const double* recip,
+                                           const uint8_t* lcodes) {
   constexpr int NW = BLOCK / kWave;
   const int tid = team_tid<BLOCK>(), wid = tid / kWave, lane = (int)lane_id();
   const int64_t n = T.n_train;
@@ -1485,7 +1620,7 @@ __device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T,
     while (level_cnt > 0) {
       const Level2 C = cur ? sc.L1 : sc.L0;  // this level
       const Level2 X = cur ? sc.L0 : sc.L1;  // the next level
-      const Ctx<LC> x{&a, &T, lcodes, sc, C.buf, X.buf, C.mstart, C.mend, C.mN, C.mS, C.mQ};
+      const Ctx<LC> x{&a, &T, lcodes, recip, sc, C.buf, X.buf, C.mstart, C.mend, C.mN, C.mS, C.mQ};
       // (a) - (c) are skipped by a member that grows on from the parting level
       if (!GROUPED || !sh.resume) {
         ++levels;
@@ -1685,8 +1820,10 @@ __device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T,
         // the partition's chunk word; 0 = read the row's code)
         uint32_t side_ci = 0;
         if (stk == kBig || stk == kHuge) {
+          // a large node has a record per task, a wide one per candidate column
           const uint32_t ri = sc.ridx[k] + (stk == kHuge ? n_big : 0u);
-          dc = decide_from_recs(sc.recs + (size_t)ri * mtry, mtry, x.mS[k], x.mN[k]);
+          const int n_recs = stk == kHuge ? mtry : (mtry + a.big_cols - 1) / a.big_cols;
+          dc = decide_from_recs(sc.recs + (size_t)ri * mtry, n_recs, x.mS[k], x.mN[k]);
           if (WIDE && stk == kHuge) side_ci = dc.cand + 1u;
           stk = dc.split ? kSplit : kLeaf;
         } else if (stk == kSplitDone) {
@@ -1885,7 +2022,7 @@ __device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T,
 // A team's loop over the queue of task groups, with scratch area `area`.
 template <int BLOCK, bool WIDE, bool GROUPED, bool LC>
 __device__ __forceinline__ void grow_queue(const GrowArgs& a, uint32_t area, uint8_t* lds, Shared<BLOCK, WIDE>& sh,
-                                           const uint16_t* nbins, const uint8_t* lcodes) {
+                                           const uint16_t* nbins, const double* recip, const uint8_t* lcodes) {
   const int tid = team_tid<BLOCK>();
   Scratch sc;
   carve(&sc, reinterpret_cast<uintptr_t>(a.scratch) + a.scratch_stride * area, a.n_cap, a.mtry_max, WIDE, GROUPED);
@@ -1907,7 +2044,7 @@ __device__ __forceinline__ void grow_queue(const GrowArgs& a, uint32_t area, uin
     }
     team_sync<BLOCK>();
     const TreeTask T = a.tasks[rfl((uint32_t)sh.gtask[0])];
-    grow_group<BLOCK, WIDE, GROUPED, LC>(a, T, sc, lds, sh, nbins, lcodes);
+    grow_group<BLOCK, WIDE, GROUPED, LC>(a, T, sc, lds, sh, nbins, recip, lcodes);
     team_sync<BLOCK>();
   }
 }
@@ -1920,13 +2057,15 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(OCC))) vo
   extern __shared__ __align__(16) uint8_t lds[];
   __shared__ Shared<BLOCK, WIDE> sh;
   __shared__ uint16_t nbins[256];
+  __shared__ double recip[kRecip];
   // a code at or above its column's bin count (flagged by the prepare kernel,
   // which ran before on this stream) would index past a histogram: grow nothing
   // and let the fit report EINVAL
   if (__atomic_load_n(a.status, __ATOMIC_RELAXED) & kStatusBadCode) return;
   for (int c = threadIdx.x; c < a.C; c += BLOCK) nbins[c] = (uint16_t)a.n_bins[c];
+  fill_recip<BLOCK>(recip);
   team_sync<BLOCK>();
-  grow_queue<BLOCK, WIDE, GROUPED, false>(a, blockIdx.x, lds, sh, nbins, nullptr);
+  grow_queue<BLOCK, WIDE, GROUPED, false>(a, blockIdx.x, lds, sh, nbins, recip, nullptr);
 }
 
 // Trees of a deep queue over a small code matrix: a workgroup holds the matrix in
@@ -1945,14 +2084,17 @@ __global__ __launch_bounds__(kTeams* kWave) __attribute__((amdgpu_waves_per_eu(k
   if (__atomic_load_n(a.status, __ATOMIC_RELAXED) & kStatusBadCode) return;  // (as in k_grow)
   const int tid = (int)threadIdx.x, team = (int)rfl((uint32_t)tid / kWave);
   uint8_t* lcodes = lds;
-  uint16_t* nbins = reinterpret_cast<uint16_t*>(lds + a.lcode_bytes);
+  double* recip = reinterpret_cast<double*>(lds + a.lcode_bytes);
+  uint16_t* nbins = reinterpret_cast<uint16_t*>(recip + kRecip);
   for (int c = tid; c < a.C; c += kTeams * kWave) nbins[c] = (uint16_t)a.n_bins[c];
   const uint32_t total = a.lcode_rows * (uint32_t)a.C;
   for (uint32_t i = (uint32_t)tid; i < total; i += kTeams * kWave) lcodes[i] = a.codes[i];
+  fill_recip<kTeams * kWave>(recip);
   __syncthreads();
-  uint8_t* own = lds + a.lcode_bytes + 512 + (size_t)team * a.team_bytes;
+  uint8_t* own = reinterpret_cast<uint8_t*>(nbins + 256) + (size_t)team * a.team_bytes;
   auto& sh = *reinterpret_cast<Shared<kWave, false>*>(own + a.union_bytes);
-  grow_queue<kWave, false, GROUPED, true>(a, blockIdx.x * (uint32_t)kTeams + (uint32_t)team, own, sh, nbins, lcodes);
+  grow_queue<kWave, false, GROUPED, true>(a, blockIdx.x * (uint32_t)kTeams + (uint32_t)team, own, sh, nbins, recip,
+                                          lcodes);
 }
 
 // The grow kernel of this translation unit for a launch shape (block, wide
@@ -2082,7 +2224,7 @@ Layout grow_layout(const GrowConfig& cfg, int32_t mtry_max, int32_t C, int64_t n
     const size_t lcodes = ((size_t)n * C + 255) / 256 * 256;
     const size_t uni = ((size_t)L.union_bytes + 15) / 16 * 16;
     const size_t team = uni + (sizeof(Shared<kWave, false>) + 15) / 16 * 16;
-    const size_t total = lcodes + 512 + kTeams * team;
+    const size_t total = lcodes + kRecip * sizeof(double) + 512 + kTeams * team;
     if (total <= device_info().lds_per_block) {
       L.lds_bytes = (uint32_t)total;
       L.lcode_bytes = (uint32_t)lcodes;
