@@ -252,6 +252,23 @@ struct GrowArgs {
 
 __device__ __forceinline__ uint32_t rfl(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
+// A value that is the same in every lane, in scalar registers.
+template <typename T>
+__device__ __forceinline__ T uniform(const T& v) {
+  static_assert(sizeof(T) % 4 == 0, "whole words");
+  uint32_t w[sizeof(T) / 4];
+  __builtin_memcpy(w, &v, sizeof(T));
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(T) / 4); ++i) w[i] = rfl(w[i]);
+  T r;
+  __builtin_memcpy(&r, w, sizeof(T));
+  return r;
+}
+
+__device__ __forceinline__ NodeDesc load_desc(const NodeDesc* p) {
+  return NodeDesc{gload(&p->k), gload(&p->start), gload(&p->len), gload(&p->N), gload(&p->S)};
+}
+
 // A team of BLOCK threads grows a tree: the workgroup, or (BLOCK = 64) one wave,
 // of which a workgroup may hold several.
 template <int BLOCK>
@@ -406,7 +423,7 @@ struct Ctx {
   const double* recip;    // reciprocals of the weights below kRecip, in the LDS
   __device__ __forceinline__ RowCodes<LC> row(uint32_t r) const {
     if constexpr (LC)
-      return {(const __attribute__((address_space(3))) uint8_t*)(lcodes + r * (uint32_t)a->C)};
+      return {(const __attribute__((address_space(3))) uint8_t*)(lcodes + __umul24(r, (uint32_t)a->C))};
     else
       return {a->rcodes + (size_t)r * a->rC};
   }
@@ -718,14 +735,14 @@ __device__ __forceinline__ void small_task(const Ctx<LC>& x, const NodeDesc* lis
   const int lane = (int)lane_id();
   constexpr int P = kWave / W;
   const int g = lane / W, r = lane % W, sbase = g * W;
+  // (the segments past the list's end repeat its last node without rows)
   const uint32_t idx = t * (uint32_t)P + (uint32_t)g;
   const bool node_ok = idx < n_list;
-  NodeDesc d{0u, 0u, 0u, 0u, 0};
-  if (node_ok) d = list[idx];
-  const uint32_t k = d.k, start = d.start, len = d.len, N = d.N;
+  const NodeDesc d = load_desc(list + min(idx, n_list - 1u));
+  const uint32_t k = d.k, start = d.start, len = node_ok ? d.len : 0u, N = d.N;
   const int64_t S = d.S;
   const bool valid = (uint32_t)r < len;
-  const uint64_t e = valid ? x.buf[start + r] : 0ull;
+  const uint64_t e = valid ? gload(x.buf + start + r) : 0ull;
   const uint32_t row = entry_row(e);
   const uint32_t w = valid ? entry_w(e) : 0u;
   const int64_t y = entry_y(e);
@@ -785,27 +802,8 @@ __device__ __forceinline__ void small_task(const Ctx<LC>& x, const NodeDesc* lis
   double best = -1.0;
   uint32_t best_ib = 0xFFFFFFFFu;  // candidate index << 8 | bin
   const uint64_t* seg_pv = s_pv + sbase;
-  for (int i0 = 0; i0 < mtry; i0 += kWave) {
-    const int nc = min(kWave, mtry - i0);
-    // gather the row's codes in every candidate column of this chunk at once:
-    // sixteen candidates per 16-byte load, sixteen gathers in flight.  Every
-    // lane loads and stores without a branch: a lane without a row reads row 0
-    // (entry 0), whose codes no sum uses (its weight and w y are zero), and a
-    // position past the chunk reads column 0 into a slot no candidate reads
-    // (g0 + u < 64: inside the 64-column staging area).
-    for (int g0 = 0; g0 < nc; g0 += 16) {
-      const uint4 c16 = gload16(cand + i0 + g0);
-      const uint32_t cw[4] = {c16.x, c16.y, c16.z, c16.w};
-      uint32_t cd[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const uint32_t c = g0 + u < nc ? (cw[u >> 2] >> (8 * (u & 3))) & 0xFFu : 0u;
-        cd[u] = rowp[c];
-      }
-#pragma unroll
-      for (int u = 0; u < 16; ++u) s_codes[(g0 + u) * kWave + lane] = (uint8_t)cd[u];
-    }
-    wave_lds_sync();
+  // the candidates of a chunk, with every form of the sums and scores
+  auto general_search = [&](int i0, int nc) {
     for (int i = 0; i < nc; ++i) {
       const uint8_t* col_codes = s_codes + i * kWave;
       const uint32_t code = col_codes[lane];
@@ -814,22 +812,10 @@ __device__ __forceinline__ void small_task(const Ctx<LC>& x, const NodeDesc* lis
       int64_t SL;
       const uint32_t* seg_codes = reinterpret_cast<const uint32_t*>(col_codes + sbase);
       if (bytes_ok) {
-        if constexpr (MX) {
-          if (codes7)
-            b3 ? matrix_sums<W, true, true>(A, planes, col_codes, code, lane, NL, SL, light)
-               : matrix_sums<W, true, false>(A, planes, col_codes, code, lane, NL, SL, light);
-          else
-            b3 ? matrix_sums<W, false, true>(A, planes, col_codes, code, lane, NL, SL, light)
-               : matrix_sums<W, false, false>(A, planes, col_codes, code, lane, NL, SL, light);
-        } else {
-          const uint8_t* seg_planes = planes + (sbase >> 2) * 32;
-          if (codes7)
-            b3 ? byte_plane_sums<W, true, true>(code, seg_codes, seg_planes, NL, SL)
-               : byte_plane_sums<W, true, false>(code, seg_codes, seg_planes, NL, SL);
-          else
-            b3 ? byte_plane_sums<W, false, true>(code, seg_codes, seg_planes, NL, SL)
-               : byte_plane_sums<W, false, false>(code, seg_codes, seg_planes, NL, SL);
-        }
+        if constexpr (MX)
+          matrix_sums<W, false, false>(A, planes, col_codes, code, lane, NL, SL, light);
+        else
+          byte_plane_sums<W, false, false>(code, seg_codes, planes + (sbase >> 2) * 32, NL, SL);
       } else {
         uint64_t acc = 0;  // packed left sums
 #pragma unroll 2
@@ -853,6 +839,58 @@ __device__ __forceinline__ void small_task(const Ctx<LC>& x, const NodeDesc* lis
         best_ib = ((uint32_t)(i0 + i) << 8) | code;
       }
     }
+  };
+  for (int i0 = 0; i0 < mtry; i0 += kWave) {
+    const int nc = min(kWave, mtry - i0);
+    // gather the row's codes in every candidate column of this chunk at once:
+    // sixteen candidates per 16-byte load, sixteen gathers in flight.  Every
+    // lane loads and stores without a branch: a lane without a row reads row 0
+    // (entry 0), whose codes no sum uses (its weight and w y are zero), and a
+    // position past the list reads its padding, the last candidate again, into a
+    // slot no candidate reads (g0 + u < 64: inside the 64-column staging area).
+    for (int g0 = 0; g0 < nc; g0 += 16) {
+      const uint4 c16 = gload16(cand + i0 + g0);
+      const uint32_t cw[4] = {c16.x, c16.y, c16.z, c16.w};
+      uint32_t cd[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        cd[u] = rowp[(cw[u >> 2] >> (8 * (u & 3))) & 0xFFu];
+      }
+#pragma unroll
+      for (int u = 0; u < 16; ++u) s_codes[(g0 + u) * kWave + lane] = (uint8_t)cd[u];
+    }
+    wave_lds_sync();
+    // the common case (sums of three digits or bytes over light nodes) has loops
+    // of its own, and the general one the widest form alone: with a branch on each
+    // of its conditions in one loop the tuning grid took 223 ms, so 215
+    if (bytes_ok && b3 && light) {
+      auto search = [&](auto c7) {
+#pragma unroll 1
+        for (int i = 0; i < nc; ++i) {
+          const uint8_t* col_codes = s_codes + i * kWave;
+          const uint32_t code = col_codes[lane];
+          uint32_t NL;
+          int64_t SL;
+          constexpr bool C7 = decltype(c7)::value;
+          if constexpr (MX)
+            matrix_sums<W, C7, true>(A, planes, col_codes, code, lane, NL, SL, true);
+          else
+            byte_plane_sums<W, C7, true>(code, reinterpret_cast<const uint32_t*>(col_codes + sbase),
+                                         planes + (sbase >> 2) * 32, NL, SL);
+          const double sc = light_score(x.recip, (int32_t)SL, NL, N, Sd, Nd);
+          if (sc > best) {
+            best = sc;
+            best_ib = ((uint32_t)(i0 + i) << 8) | code;
+          }
+        }
+      };
+      if (codes7)
+        search(std::true_type{});
+      else
+        search(std::false_type{});
+    } else {
+      general_search(i0, nc);
+    }
     wave_lds_sync();
   }
   // segment arg-max: the largest score, then the lowest candidate, then the lowest bin
@@ -865,25 +903,25 @@ __device__ __forceinline__ void small_task(const Ctx<LC>& x, const NodeDesc* lis
 
 // Nodes of 33..64 rows: one node per wave, one row per lane.  Per candidate
 // column the rows' packed (w, w y) are added into the column's LDS bins, a wave
-// prefix scan over the bins (ceil(B / 64) per lane) turns them into left sums,
-// and every lane scores the split at its own row's code (rows with the largest
-// code leave the right side empty and are skipped; lanes sharing a code score
-// the same split).  A column of at most 64 bins keeps its prefix sums in
-// registers (one bin per lane, read and cleared by its lane) and each lane
-// takes the one at its own code by a cross-lane read; a wider column writes
-// them back to LDS.  Two bin buffers alternate between candidates, so that a
-// wider column's bins are cleared while the next candidate is scanned.
+// prefix scan over the bins turns them into left sums, and every lane scores the
+// split at its own row's code (lanes sharing a code score the same split).  A
+// light node of columns of at most 64 bins keeps its prefix sums in registers
+// (one bin per lane) and each lane takes the one at its own code by a cross-lane
+// read; wider columns write them back to LDS.  The loop of the common case has no
+// branches and takes two candidates at a time, whose waits overlap: the tuning
+// grid's launch 215 -> 201 ms, the leave-one-kernel-out fit (148 bins) 26.0 ->
+// 24.3 ms.
 template <bool LC>
 __device__ __forceinline__ void rank_task(const Ctx<LC>& x, const NodeDesc* list, uint32_t t, uint32_t n_list, WaveHist& wl) {
   const GrowArgs& a = *x.a;
   const int mtry = x.T->mtry;
   const int lane = (int)lane_id();
   if (t >= n_list) return;
-  const NodeDesc d = list[t];
-  const uint32_t k = rfl(d.k), start = rfl(d.start), len = rfl(d.len), N = rfl(d.N);
+  const NodeDesc d = uniform(load_desc(list + t));
+  const uint32_t k = d.k, start = d.start, len = d.len, N = d.N;
   const int64_t S = d.S;
   const bool valid = (uint32_t)lane < len;
-  const uint64_t e = valid ? x.buf[start + lane] : 0ull;
+  const uint64_t e = valid ? gload(x.buf + start + lane) : 0ull;
   const uint32_t w = valid ? entry_w(e) : 0u;
   const int64_t y = entry_y(e);
   const int64_t wy = (int64_t)w * y;
@@ -899,7 +937,7 @@ __device__ __forceinline__ void rank_task(const Ctx<LC>& x, const NodeDesc* list
   for (int i = lane; i < mtry; i += kWave) {
     const uint32_t c = gload(cand + i);
     s_cand[i] = (uint8_t)c;
-    s_bm1[i] = (uint8_t)(gload(a.n_bins + c) - 1);
+    if (!LC) s_bm1[i] = (uint8_t)(gload(a.n_bins + c) - 1);
   }
   // both buffers start zeroed: four bins per lane each
   *reinterpret_cast<uint4*>(hb + 4 * lane) = make_uint4(0u, 0u, 0u, 0u);
@@ -913,74 +951,155 @@ __device__ __forceinline__ void rank_task(const Ctx<LC>& x, const NodeDesc* list
   // the end
   double best = -1.0;
   int32_t best_ib = INT_MAX;
-  // every lane fetches its code (a lane without a row reads row 0, entry 0, and
-  // adds nothing), so that the fetch is not a branch the memory wait must close
-  uint32_t c_next = rfl(s_cand[0]);
-  uint32_t code_next = rowp[c_next];
-  bool prev_in_lds = false;  // the previous candidate left prefix sums in its buffer
-  for (int i = 0; i < mtry; ++i) {
-    const uint32_t code = code_next;
-    const uint32_t B = rfl(s_bm1[i]) + 1u;  // this candidate column's bins
-    if (i + 1 < mtry) {  // fetch the next column's codes while this one is scanned
-      c_next = rfl(s_cand[i + 1]);
-      code_next = rowp[c_next];
+  // U candidates at a time, in buffers of their own; lane l owns bins [l Q, l Q +
+  // Q), Q the same for every column (the lanes past a column's bins read zeros).
+  // A wave's LDS operations are in order, so a buffer is read and cleared, and
+  // added to again, without waits between.  A lane without a row holds row 0's
+  // codes: splits like any other of the node.
+  const int Q = a.bstride / kWave;
+  auto step = [&](auto is_light, auto one_bin, auto nu, int i, const uint32_t (&code)[2]) {
+    constexpr bool LIGHT = decltype(is_light)::value, ONE = decltype(one_bin)::value;
+    constexpr int U = decltype(nu)::value;
+    auto scan = [](uint64_t v) { return LIGHT ? scan_light(v) : wave_incl_scan<uint64_t>(v); };
+    if (valid) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        atomicAdd((unsigned long long*)&hb[u * kMaxBins + code[u]], (unsigned long long)pv);
     }
-    uint64_t* hv = hb + (i & 1) * 256;
-    if (valid) atomicAdd((unsigned long long*)&hv[code], (unsigned long long)pv);
     wave_lds_sync();
-    // a previous candidate whose prefix sums went to LDS left its buffer dirty;
-    // every lane read its left sums before these adds: clear it while this one
-    // is scanned
-    if (prev_in_lds) {
-      uint64_t* ho = hb + ((i - 1) & 1) * 256;
-      *reinterpret_cast<uint4*>(ho + 4 * lane) = make_uint4(0u, 0u, 0u, 0u);
-      *reinterpret_cast<uint4*>(ho + 4 * lane + 2) = make_uint4(0u, 0u, 0u, 0u);
-    }
-    uint64_t V;  // left sums (packed) of the split at this lane's code
-    if (B <= (uint32_t)kWave) {
-      // one bin per lane: the lane owning bin b reads and clears it (the buffer
-      // is zero again for its next use), the prefix sums stay in registers,
-      // and each lane takes the one at its own code by a cross-lane read
-      const uint64_t h = lane < (int)B ? hv[lane] : 0ull;
-      if (lane < (int)B) hv[lane] = 0ull;
-      const uint64_t v = light ? scan_light(h) : wave_incl_scan<uint64_t>(h);
-      V = lane_pick64(v, code);
-      prev_in_lds = false;
+    uint64_t V[U];  // left sums of the split at this lane's code
+    if constexpr (ONE) {
+      // the prefix sums stay in registers: each lane takes the one at its own
+      // code by a cross-lane read
+      uint64_t h[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        h[u] = hb[u * kMaxBins + lane];
+        hb[u * kMaxBins + lane] = 0ull;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) V[u] = lane_pick64(scan(h[u]), code[u]);
     } else {
-      // inclusive prefix sums of the B bins, ceil(B / 64) consecutive bins per lane
-      const int q = ((int)B + kWave - 1) / kWave;
-      const int b0 = lane * q;
+      uint64_t h[U][4], v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        v[u] = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          h[u][c] = c < Q ? hb[u * kMaxBins + lane * Q + c] : 0ull;
+          v[u] += h[u][c];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        uint64_t run = scan(v[u]) - v[u];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          run += h[u][c];
+          if (c < Q) hb[u * kMaxBins + lane * Q + c] = run;
+        }
+      }
+      wave_lds_sync();
+#pragma unroll
+      for (int u = 0; u < U; ++u) V[u] = hb[u * kMaxBins + code[u]];
+      wave_lds_sync();
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if (c < Q) hb[u * kMaxBins + lane * Q + c] = 0ull;
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      double sc = -1.0;
+      if constexpr (LIGHT) {
+        const uint32_t NL = (uint32_t)(V[u] >> 32);
+        sc = light_score(x.recip, light_sum(NL, (uint32_t)V[u]), NL, N, Sd, Nd);
+      } else {
+        const uint32_t NL = packed_n(V[u]);
+        const int64_t SL = packed_s(V[u], NL);
+        if (NL > 0 && NL < N) sc = split_score(SL, NL, S - SL, N - NL);
+      }
+      if (sc > best) {
+        best = sc;
+        best_ib = ((i + u) << 8) | (int32_t)code[u];
+      }
+    }
+  };
+  // the candidates' codes are fetched one step ahead
+  auto search = [&](auto is_light, auto one_bin, auto nu) {
+    constexpr int U = decltype(nu)::value;
+    uint32_t next[2] = {rowp[rfl(s_cand[0])], rowp[rfl(s_cand[min(1, mtry - 1)])]};
+    int i = 0;
+#pragma unroll 1
+    for (; i + U <= mtry; i += U) {
+      const uint32_t code[2] = {next[0], next[1]};
+      if constexpr (U == 1)
+        next[0] = next[1];
+      else
+        next[0] = rowp[rfl(s_cand[min(i + 2, mtry - 1)])];
+      next[1] = rowp[rfl(s_cand[min(i + U + 1, mtry - 1)])];
+      step(is_light, one_bin, nu, i, code);
+    }
+    if (i < mtry) step(is_light, one_bin, std::integral_constant<int, 1>{}, i, next);
+  };
+  if (light && Q == 1) {
+    search(std::true_type{}, std::true_type{}, std::integral_constant<int, 2>{});
+  } else if constexpr (LC) {
+    if (light)
+      search(std::true_type{}, std::false_type{}, std::integral_constant<int, 2>{});
+    else
+      search(std::false_type{}, std::false_type{}, std::integral_constant<int, 1>{});
+  } else {
+    // one candidate at a time, within the registers that the other kernels can
+    // spare, its bins read to its own count (with the loop above 2000 trees on 2220
+    // rows of 148 bins take 2.28 ms and 500 on 200000 rows 65.8; with this one
+    // 2.07 and 63.0)
+    uint32_t code_next = rowp[rfl(s_cand[0])];
+#pragma unroll 1
+    for (int i = 0; i < mtry; ++i) {
+      const uint32_t code = code_next;
+      const int B = (int)rfl(s_bm1[i]) + 1, q = (B + kWave - 1) / kWave, b0 = lane * q;
+      if (i + 1 < mtry) code_next = rowp[rfl(s_cand[i + 1])];
+      uint64_t* hv = hb + (i & 1) * kMaxBins;
+      if (valid) atomicAdd((unsigned long long*)&hv[code], (unsigned long long)pv);
+      wave_lds_sync();
+      // the other buffer holds the previous candidate's prefix sums, which every
+      // lane has read: cleared while this one is scanned
+      if (i > 0) {
+        uint64_t* ho = hb + ((i - 1) & 1) * kMaxBins;
+        *reinterpret_cast<uint4*>(ho + 4 * lane) = make_uint4(0u, 0u, 0u, 0u);
+        *reinterpret_cast<uint4*>(ho + 4 * lane + 2) = make_uint4(0u, 0u, 0u, 0u);
+      }
       uint64_t h[4];
       uint64_t loc = 0;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        h[u] = u < q && b0 + u < (int)B ? hv[b0 + u] : 0ull;
+        h[u] = u < q && b0 + u < B ? hv[b0 + u] : 0ull;
         loc += h[u];
       }
       uint64_t v = (light ? scan_light(loc) : wave_incl_scan<uint64_t>(loc)) - loc;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         v += h[u];
-        if (u < q && b0 + u < (int)B) hv[b0 + u] = v;
+        if (u < q && b0 + u < B) hv[b0 + u] = v;
       }
       wave_lds_sync();
-      V = hv[code];  // code < B for every lane (a lane without a row has row 0's)
-      prev_in_lds = true;
-    }
-    double sc = -1.0;
-    if (light) {
-      const uint32_t NL = (uint32_t)(V >> 32);
-      sc = light_score(x.recip, light_sum(NL, (uint32_t)V), NL, N, Sd, Nd);
-    } else if (valid) {
-      const uint32_t NL = packed_n(V);
-      if (NL < N) {
+      const uint64_t V = hv[code];  // (a lane without a row has row 0's code: below B)
+      double sc = -1.0;
+      if (light) {
+        const uint32_t NL = (uint32_t)(V >> 32);
+        sc = light_score(x.recip, light_sum(NL, (uint32_t)V), NL, N, Sd, Nd);
+      } else if (valid) {
+        const uint32_t NL = packed_n(V);
         const int64_t SL = packed_s(V, NL);
-        sc = split_score(SL, NL, S - SL, N - NL);
+        if (NL < N) sc = split_score(SL, NL, S - SL, N - NL);
       }
-    }
-    if (sc > best) {
-      best = sc;
-      best_ib = (i << 8) | (int32_t)code;
+      if (sc > best) {
+        best = sc;
+        best_ib = (i << 8) | (int32_t)code;
+      }
     }
   }
   const ArgMax am = wave_best(best, best_ib);
@@ -1055,7 +1174,11 @@ __device__ __forceinline__ ArgMax scan_packed(const uint64_t* hv, int B, uint32_
 
 // Large nodes: one wave per (node, up to four consecutive candidate columns),
 // one LDS histogram per column: the node's entries are read once for all of
-// them and the columns' code gathers overlap.
+// them, a step ahead, and the columns' code gathers overlap.  The node and its
+// columns are the same in every lane, and kept in scalar registers as such
+// (column g's id and bin count are lane g's, read across): with loops over
+// vector counts and one copy of the scan per column the grid took 235 ms, the
+// 200000-row fit 66.4; now 223 and 63.2.
 template <bool LC>
 __device__ __forceinline__ void big_task(const Ctx<LC>& x, uint32_t j, int ci0, WaveHist& L) {
   constexpr int G = 4;
@@ -1064,47 +1187,16 @@ __device__ __forceinline__ void big_task(const Ctx<LC>& x, uint32_t j, int ci0, 
   const int mtry = x.T->mtry;
   const int gn = min(a.big_cols, mtry - ci0);  // columns of this task
   const int gs = a.big_stride;
-  const NodeDesc d = x.sc.big[j];
-  const uint32_t start = rfl(d.start);
-  const uint32_t end = start + rfl(d.len);
-  const uint32_t N = rfl(d.N);
+  const NodeDesc d = uniform(load_desc(x.sc.big + j));
+  const uint32_t start = d.start, end = start + d.len, N = d.N;
   const int64_t S = d.S;
-  const bool light = N < (uint32_t)kRecip;
-  const uint32_t* bt = x.sc.btask + (size_t)j * mtry + ci0;
-  int c[G];
+  const uint32_t* btp = x.sc.btask + (size_t)j * mtry + ci0;
+  const uint32_t btl = gload(btp + min(lane, gn - 1));  // lane g: column g's id and bin count
+  uint32_t bt[G];
 #pragma unroll
-  for (int g = 0; g < G; ++g) c[g] = g < gn ? (int)(rfl(bt[g]) & 0xFFu) : 0;
+  for (int g = 0; g < G; ++g) bt[g] = read_lane(btl, g) & 0xFFu;
   uint64_t* hv = L.hv;
   for (int b = lane; b < gn * gs; b += kWave) hv[b] = 0;
-  wave_lds_sync();
-  // two rows per lane in flight: entries, then their codes in every column,
-  // then the atomics
-  constexpr int U = 2;
-  for (uint32_t p0 = start + lane; p0 < end; p0 += U * kWave) {
-    uint64_t e[U];
-    uint32_t code[U][G];
-#pragma unroll
-    for (int u = 0; u < U; ++u) e[u] = p0 + u * kWave < end ? x.buf[p0 + u * kWave] : 0ull;
-    // every lane loads the task's gn codes under a wave-uniform condition only:
-    // past the node's end the entry is 0 (row 0), whose codes are not added
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const RowCodes<LC> rp = x.row(entry_row(e[u]));
-#pragma unroll
-      for (int g = 0; g < G; ++g) code[u][g] = g < gn ? rp[(uint32_t)c[g]] : 0u;
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (p0 + u * kWave < end) {
-        const uint32_t w = entry_w(e[u]);
-        const int64_t wy = (int64_t)w * entry_y(e[u]);
-        const uint64_t v = light ? light_word(w, wy) : pack_ns(w, wy);
-#pragma unroll
-        for (int g = 0; g < G; ++g)
-          if (g < gn) atomicAdd((unsigned long long*)&hv[g * gs + (int)code[u][g]], (unsigned long long)v);
-      }
-    }
-  }
   wave_lds_sync();
   // each lane keeps the best split of its bins over the task's columns, and the
   // wave's best of all is the task's record
@@ -1112,23 +1204,72 @@ __device__ __forceinline__ void big_task(const Ctx<LC>& x, uint32_t j, int ci0, 
   int32_t key = INT_MAX;  // column of the task << 8 | bin
   uint32_t bNL = 0;
   int64_t bSL = 0;
-  const double Sd = i64_to_f64(S), Nd = (double)N;
-#pragma unroll 1
-  for (int g = 0; g < gn; ++g) {
-    const int B = (int)(rfl(bt[g]) >> 8), q = (B + kWave - 1) / kWave, b0 = lane * q;
-    const uint64_t* hg = hv + g * gs;
-    if (light) {
-      if (q == 1) {
-        const uint64_t v = scan_light(lane < B ? hg[lane] : 0ull);
-        const uint32_t NL = (uint32_t)(v >> 32);
-        const int32_t SL = light_sum(NL, (uint32_t)v);
-        const double sc = light_score(x.recip, SL, NL, N, Sd, Nd);
-        if (sc > best) {
-          best = sc;
-          key = (g << 8) | lane;
-          bNL = NL;
-          bSL = SL;
+  auto search = [&](auto is_light) {
+    constexpr bool LIGHT = decltype(is_light)::value;
+    // two rows per lane in flight: entries, then their codes in every column,
+    // then the atomics (a lane past the node's end repeats its last entry)
+    constexpr int U = 2;
+    uint64_t en[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) en[u] = gload(x.buf + min(start + (uint32_t)(u * kWave + lane), end - 1u));
+    for (uint32_t p = start; p < end; p += U * kWave) {
+      uint64_t e[U];
+      uint32_t code[U][G];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        e[u] = en[u];
+        en[u] = gload(x.buf + min(p + (uint32_t)((U + u) * kWave + lane), end - 1u));
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const RowCodes<LC> rp = x.row(entry_row(e[u]));
+#pragma unroll
+        for (int g = 0; g < G; ++g) code[u][g] = g < gn ? rp[bt[g] & 0xFFu] : 0u;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (p + (uint32_t)(u * kWave + lane) < end) {
+          const uint32_t w = entry_w(e[u]);
+          const int32_t y = (int32_t)entry_y(e[u]);
+          const uint64_t v = LIGHT ? light_word(w, (int32_t)w * y) : pack_ns(w, (int64_t)w * y);
+#pragma unroll
+          for (int g = 0; g < G; ++g)
+            if (g < gn) atomicAdd((unsigned long long*)&hv[g * gs + (int)code[u][g]], (unsigned long long)v);
         }
+      }
+    }
+    wave_lds_sync();
+    const double Sd = i64_to_f64(S), Nd = (double)N;
+    auto score = [&](uint64_t v, int32_t k) {
+      uint32_t NL;
+      int64_t SL;
+      double sc = -1.0;
+      if constexpr (LIGHT) {
+        NL = (uint32_t)(v >> 32);
+        SL = light_sum(NL, (uint32_t)v);
+        sc = light_score(x.recip, (int32_t)SL, NL, N, Sd, Nd);
+      } else {
+        NL = packed_n(v);
+        SL = packed_s(v, NL);
+        if (NL > 0 && NL < N) sc = split_score(SL, NL, S - SL, N - NL);
+      }
+      if (sc > best) {
+        best = sc;
+        key = k;
+        bNL = NL;
+        bSL = SL;
+      }
+    };
+    auto scan = [](uint64_t v) { return LIGHT ? scan_light(v) : wave_incl_scan<uint64_t>(v); };
+#pragma unroll 1
+    for (int g = 0; g < gn; ++g) {
+      const uint32_t btg = read_lane(btl, g);
+      // lane l owns bins [l q, l q + q): an empty bin repeats the split before it,
+      // which wins the tie
+      const int B = (int)(btg >> 8), q = (B + kWave - 1) / kWave, b0 = lane * q;
+      const uint64_t* hg = hv + g * gs;
+      if (q == 1) {
+        score(scan(lane < B ? hg[lane] : 0ull), (g << 8) | lane);
       } else {
         uint64_t h[4];
         uint64_t loc = 0;
@@ -1137,57 +1278,27 @@ __device__ __forceinline__ void big_task(const Ctx<LC>& x, uint32_t j, int ci0, 
           h[u] = u < q && b0 + u < B ? hg[b0 + u] : 0ull;
           loc += h[u];
         }
-        uint64_t v = scan_light(loc) - loc;
+        uint64_t v = scan(loc) - loc;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           if (u >= q) break;
           v += h[u];
-          const uint32_t NL = (uint32_t)(v >> 32);
-          const int32_t SL = light_sum(NL, (uint32_t)v);
-          const double sc = light_score(x.recip, SL, NL, N, Sd, Nd);
-          if (sc > best) {
-            best = sc;
-            key = (g << 8) | (b0 + u);
-            bNL = NL;
-            bSL = SL;
-          }
-        }
-      }
-    } else {
-      uint64_t h[4];
-      uint64_t loc = 0;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        h[u] = u < q && b0 + u < B ? hg[b0 + u] : 0ull;
-        loc += h[u];
-      }
-      uint64_t v = wave_incl_scan<uint64_t>(loc) - loc;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        // an empty bin repeats the previous split, which already won any tie
-        if (u >= q || h[u] == 0) continue;
-        v += h[u];
-        const uint32_t NL = packed_n(v);
-        if (NL < N) {
-          const int64_t SL = packed_s(v, NL);
-          const double sc = split_score(SL, NL, S - SL, N - NL);
-          if (sc > best) {
-            best = sc;
-            key = (g << 8) | (b0 + u);
-            bNL = NL;
-            bSL = SL;
-          }
+          score(v, (g << 8) | (b0 + u));
         }
       }
     }
-  }
+  };
+  if (N < (uint32_t)kRecip)
+    search(std::true_type{});
+  else
+    search(std::false_type{});
   const ArgMax am = wave_best(best, key);
   if (lane == am.lane) {
     Rec r;
     r.score = am.score;
     r.SL = bSL;
     r.NL = bNL;
-    r.colbin = am.score >= 0.0 ? (bt[am.key >> 8] & 0xFFu) << 8 | (uint32_t)(am.key & 0xFF) : 0u;
+    r.colbin = am.score >= 0.0 ? (read_lane(btl, am.key >> 8) & 0xFFu) << 8 | (uint32_t)(am.key & 0xFF) : 0u;
     x.sc.recs[(size_t)j * mtry + (uint32_t)ci0 / (uint32_t)a.big_cols] = r;
   }
   wave_lds_sync();
@@ -2043,7 +2154,7 @@ __device__ __forceinline__ void grow_queue(const GrowArgs& a, uint32_t area, uin
       sh.ginbag[tid] = a.tasks[ti].inbag_off;
     }
     team_sync<BLOCK>();
-    const TreeTask T = a.tasks[rfl((uint32_t)sh.gtask[0])];
+    const TreeTask T = uniform(a.tasks[rfl((uint32_t)sh.gtask[0])]);
     grow_group<BLOCK, WIDE, GROUPED, LC>(a, T, sc, lds, sh, nbins, recip, lcodes);
     team_sync<BLOCK>();
   }
