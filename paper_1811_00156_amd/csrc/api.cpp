@@ -93,19 +93,15 @@ GrowConfig grow_config(int64_t n_cap, int64_t n_items, const std::vector<int32_t
   return cfg;
 }
 
-// Node arrays of one tree, unpacked from the node words.
-void unpack_nodes(const std::vector<uint64_t>& words, const std::vector<uint32_t>& N, size_t count, uint8_t* col,
-                  uint8_t* bin, int32_t* left, int64_t* q, int32_t* Nout) {
-  for (size_t i = 0; i < count; ++i) {
-    const uint64_t v = words[i];
-    const bool leaf = node_col(v) == kLeafCol;
-    if (col) col[i] = (uint8_t)node_col(v);
-    if (bin) bin[i] = leaf ? 0 : (uint8_t)node_bin(v);
-    if (left) left[i] = leaf ? -1 : (int32_t)node_left(v);
-    if (q) q[i] = leaf ? node_q(v) : 0;
-    if (Nout) Nout[i] = (int32_t)N[i];
+// Makes a device current for a scope.
+struct OnDevice {
+  int prev = 0;
+  explicit OnDevice(int device) {
+    AIWC_HIP(hipGetDevice(&prev));
+    if (prev != device) AIWC_HIP(hipSetDevice(device));
   }
-}
+  ~OnDevice() { (void)hipSetDevice(prev); }
+};
 
 void check_forest(const aiwc_rf_forest* f, int32_t forest_index) {
   require(f != nullptr, "forest is NULL");
@@ -725,20 +721,32 @@ int aiwc_rf_forest_export_host(const aiwc_rf_forest* f, int32_t forest_index, in
     const int64_t t0 = f->first_task[forest_index];
     std::vector<int32_t> nn((size_t)(tree_end - tree_begin));
     AIWC_HIP(hipMemcpy(nn.data(), f->n_nodes.p + t0 + tree_begin, sizeof(int32_t) * nn.size(), hipMemcpyDeviceToHost));
-    size_t out = 0;
-    std::vector<uint64_t> words;
-    std::vector<uint32_t> N;
-    for (int32_t t = tree_begin; t < tree_end; ++t) {
-      const size_t cnt = (size_t)nn[t - tree_begin];
-      const int64_t base = f->tasks[t0 + t].node_base;
-      words.resize(cnt);
-      N.resize(cnt);
-      AIWC_HIP(hipMemcpy(words.data(), f->nodes.p + base, sizeof(uint64_t) * cnt, hipMemcpyDeviceToHost));
-      AIWC_HIP(hipMemcpy(N.data(), f->node_N.p + base, sizeof(uint32_t) * cnt, hipMemcpyDeviceToHost));
-      unpack_nodes(words, N, cnt, col_host ? col_host + out : nullptr, bin_host ? bin_host + out : nullptr,
-                   left_host ? left_host + out : nullptr, q_host ? q_host + out : nullptr,
-                   N_host ? N_host + out : nullptr);
-      out += cnt;
+    // slices of whole trees, of at most 2^20 nodes (18 MiB of device memory) where
+    // a tree is not larger, unpacked on the forest's device
+    constexpr int64_t kSlice = int64_t(1) << 20;
+    const OnDevice on(f->device);
+    int64_t out = 0;
+    for (int32_t a = 0, e = 0; a < (int32_t)nn.size(); a = e) {
+      std::vector<int64_t> off{0};
+      for (e = a; e < (int32_t)nn.size() && (e == a || off.back() + nn[e] <= kSlice); ++e)
+        off.push_back(off.back() + nn[e]);
+      const size_t cnt = (size_t)off.back();
+      DevBuf<int64_t> d_off(off.size(), nullptr);
+      DevBuf<uint8_t> col(col_host ? cnt : 0, nullptr), bin(bin_host ? cnt : 0, nullptr);
+      DevBuf<int32_t> left(left_host ? cnt : 0, nullptr), N(N_host ? cnt : 0, nullptr);
+      DevBuf<int64_t> q(q_host ? cnt : 0, nullptr);
+      AIWC_HIP(hipMemcpy(d_off.p, off.data(), sizeof(int64_t) * off.size(), hipMemcpyHostToDevice));
+      launch_unpack(f->nodes.p, f->node_N.p, f->node_base.p + t0 + tree_begin + a, d_off.p, e - a, col.p, bin.p, left.p,
+                    q.p, N.p, nullptr);
+      auto take = [&](void* dst, const void* src, size_t bytes) {
+        if (src) AIWC_HIP(hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost));
+      };
+      take(col_host ? col_host + out : nullptr, col.p, cnt);
+      take(bin_host ? bin_host + out : nullptr, bin.p, cnt);
+      take(left_host ? left_host + out : nullptr, left.p, sizeof(int32_t) * cnt);
+      take(q_host ? q_host + out : nullptr, q.p, sizeof(int64_t) * cnt);
+      take(N_host ? N_host + out : nullptr, N.p, sizeof(int32_t) * cnt);
+      out += (int64_t)cnt;
     }
   });
 }

@@ -347,6 +347,12 @@ void anneal(const uint8_t* codes, int64_t n, int32_t n_cols, const aiwc_rf_binne
             const aiwc_rf_sa_config& cfg, int32_t* best_params, double* best_objective, aiwc_rf_sa_step* trace,
             hipStream_t s);
 
+// export.hip: the node arrays of n_trees trees (node_base, off: their first node
+// and first place in the arrays, off with one entry more) unpacked into
+// contiguous device arrays, any of which may be null.
+void launch_unpack(const uint64_t* nodes, const uint32_t* node_N, const int64_t* node_base, const int64_t* off,
+                   int32_t n_trees, uint8_t* col, uint8_t* bin, int32_t* left, int64_t* q, int32_t* N, hipStream_t s);
+
 // predict.hip
 // Rows of one allocation-free prediction (aiwc_rf_predict_noalloc): its int64
 // row sums use a fixed device array of this many entries (8 MiB per GPU).
