@@ -47,43 +47,54 @@ int32_t status_to_code(uint32_t st, std::string& msg) {
   return AIWC_RF_OK;
 }
 
-GrowConfig grow_config(int64_t n_cap, int64_t n_items, const std::vector<int32_t>& n_bins) {
+GrowConfig grow_config(int64_t n_cap, int64_t n_items, const std::vector<int32_t>& n_bins, int32_t mtry_max,
+                       int64_t n) {
   GrowConfig cfg;
+  cfg.n_cap = n_cap;
+  cfg.bins_max = 1;
+  for (int32_t b : n_bins) cfg.bins_max = std::max(cfg.bins_max, b);
   // n_items: the launch's work items (trees, or task groups of a fused fit).
   // Large training sets: 1024 threads per tree, nodes above 512 rows in
-  // workgroup-wide batches (the autotuner's choice on 200000 rows, 2 % ahead
-  // of 512 threads with every node above 64 rows in batches).  Small ones, by
-  // work items per CU: below 4, 512 threads per tree; from 4, 192 threads at 6
-  // waves per SIMD (eight resident trees per CU); from 16, 128 threads at 6
-  // waves (twelve); from 64, 64 threads at 5 waves (twenty): a tree's levels
-  // get fewer waves, which pays once the queue is deep enough that the CUs
-  // stay full to the end (the tuning grid, 340 groups per CU: 380 ms against
-  // 395 and 417; one fold of it, 34 per CU: 45 ms against 42 and 43).  A
-  // large-node task takes two candidate columns while trees are few (more
-  // tasks per node for the tree's waves), up to four once the CUs are full.
-  cfg.big_cols = 2;
+  // workgroup-wide batches (the autotuner's choice on 200000 rows: 63.1 ms
+  // against 66.1 with 512 threads and 63.2 to 70 with other limits).
   const int64_t cus = device_info().cus;
   if (n_cap > 16384) {
     cfg.block = 1024;
     cfg.huge_min = 512;
-  } else if (n_items >= 64 * cus) {
-    cfg.block = 64;
-    cfg.occupancy = 5;
-    cfg.big_cols = 4;
-  } else if (n_items >= 16 * cus) {
-    cfg.block = 128;
-    cfg.occupancy = 6;
-    cfg.big_cols = 4;
-  } else if (n_items >= 4 * cus) {
-    cfg.block = 192;
-    cfg.occupancy = 6;
-    cfg.big_cols = 4;
+    cfg.big_cols = 2;
   } else {
-    cfg.block = 512;
+    // Smaller ones: no wide batches, and sixteen waves per CU (four per SIMD:
+    // 128 registers) shared by as many trees as the launch gives a CU at once: a
+    // tree's levels are chains of dependent steps that more waves shorten, but
+    // every tree of the launch wants a place.  Times in ms on 2220 rows of 148
+    // bins, mtry 12, for 1024, 512, 256, 128 threads and one-wave teams:
+    //   100 trees   0.60 0.64 0.80;  500   1.13 0.80 0.91 1.31;  1024  2.17 1.51
+    //   1.18 1.47;  2000  128 threads 1.95 (192 at six waves per SIMD 2.13), teams
+    //   3.18;  4096  3.80 and 3.42;  16000  12.9 and 10.8.
+    // Deep queues without teams (the code matrix does not fit): 6000 rows, 8000
+    // trees 16.4 with 128 threads, 16.5 with 256, 20.3 with 64; 15000 rows 57.6,
+    // 53.2 and 68.9.  Up to 1024 rows a tree does not fill sixteen waves (300 rows:
+    // 0.22 and 0.21 with 512).  A large-node task takes four candidate columns,
+    // two while sixteen waves share one tree's.
+    cfg.huge_min = 16384;
+    cfg.occupancy = 4;
+    cfg.big_cols = 4;
+    GrowConfig team = cfg;
+    team.block = 64;
+    team.occupancy = 5;
+    if (n_items <= cus && n_cap > 1024) {
+      cfg.block = 1024;
+      cfg.big_cols = 2;
+    } else if (n_items <= 2 * cus) {
+      cfg.block = 512;
+    } else if (n_items <= 4 * cus) {
+      cfg.block = 256;
+    } else if (n_items >= 14 * cus && grow_teams(team, mtry_max, (int32_t)n_bins.size(), n) > 1) {
+      cfg = team;
+    } else {
+      cfg.block = n_cap > 8192 ? 256 : 128;
+    }
   }
-  cfg.n_cap = n_cap;
-  cfg.bins_max = 1;
-  for (int32_t b : n_bins) cfg.bins_max = std::max(cfg.bins_max, b);
   if (const char* e = std::getenv("AIWC_RF_GROW_BLOCK")) cfg.block = std::atoi(e);
   if (const char* e = std::getenv("AIWC_RF_GROW_WG_PER_CU")) cfg.wg_per_cu = std::atoi(e);
   if (const char* e = std::getenv("AIWC_RF_HUGE_MIN")) cfg.huge_min = std::atoi(e);
@@ -478,7 +489,7 @@ void fit_common(const uint8_t* codes, int64_t n, int32_t n_cols, const aiwc_rf_b
     n_items = 0;
     for (int32_t f = 0; f < n_forests; ++f) n_items = std::max<int64_t>(n_items, params_host[f].num_trees);
   }
-  GrowConfig cfg = grow_config(n_cap, n_items, binner->n_bins);
+  GrowConfig cfg = grow_config(n_cap, n_items, binner->n_bins, mtry_max, n);
   bool tuned = false;
   if (flags & AIWC_RF_FIT_TUNE) {
     cfg = tune_grow(cfg, n_items, n_cols, mtry_max, F.get(), codes, n, binner, y_log10, y_fp.p, codes_p.p, d_train.p,
