@@ -362,10 +362,12 @@ constexpr int64_t kNoAllocPredictRows = int64_t(1) << 20;
 int64_t* noalloc_predict_scratch();
 void launch_predict(const TreesView& F, int32_t tree_begin, int32_t tree_end, const uint8_t* codes, int64_t n,
                     int32_t C, int64_t* sum, double* y, int32_t num_trees, hipStream_t s);
-// Whether a prediction of n rows goes one workgroup per row: it then writes y
-// itself and needs no row sums (`sum` may be null), and a device selection of
-// as many (kernel, device) rows needs no expanded codes.
-bool predict_by_row(const TreesView& F, int64_t n, int32_t n_trees);
+// How a prediction of n rows by n_trees trees runs: a workgroup per row or lanes of
+// a row, which write the answers themselves and need no row sums (`sum` may be
+// null), or staged rows and chunks of trees.  A device selection whose (kernel,
+// device) rows have a workgroup each needs no expanded codes.
+enum class PredictRoute { kRow, kLanes, kMany };
+PredictRoute predict_route(const TreesView& F, int64_t n, int32_t n_trees);
 // Lets a kernel take all of the device's LDS as dynamic LDS (set once per device).
 void allow_lds(const void* kernel);
 

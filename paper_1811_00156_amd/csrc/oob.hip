@@ -88,7 +88,9 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void k_score(
         row[k] = on[k] ? (OOB ? list[j] : j) : 0u;
         off[k] = row[k] * st;
       }
-      walk_tree<K>(top, kScoreTop, tn, rows, off, on, v);
+      const uint64_t* const tops[K] = {top, top};
+      const uint64_t* const trees[K] = {tn, tn};
+      walk_trees<K>(tops, kScoreTop, trees, rows, off, on, v);
 #pragma unroll
       for (int k = 0; k < K; ++k)
         if (on[k]) {

@@ -23,8 +23,8 @@ __device__ __align__(256) unsigned long long scratch[kNoAllocPredictRows];
 
 // Prediction of many rows.  A workgroup stages its rows' codes in the LDS (one
 // row per thread) and walks its chunk of trees one after the other; each tree's
-// first TP * kPredBlock nodes are staged too, fetched into registers while the
-// previous tree is walked.  Below them a row's reads scatter over the tree, one
+// first TP * kPredBlock nodes are staged too, G trees at a time, fetched into
+// registers while the previous ones are walked.  Below them a row's reads scatter over the tree, one
 // cache line each: with one tree at a time, and the chunks of an XCD taken in
 // turn by all of its workgroups, an XCD's L2 holds the trees in use.  Before,
 // codes and nodes were both gathered from memory (200000 rows x 65 columns, 500
@@ -35,7 +35,7 @@ __device__ __align__(256) unsigned long long scratch[kNoAllocPredictRows];
 // beats two or four rows with fewer waves (2.9 and 4.3 ms).
 constexpr int kPredBlock = 256;
 
-template <int TP>
+template <int TP, int G>
 __global__ __launch_bounds__(kPredBlock) void k_traverse(TreesView F, int32_t tree_begin, int32_t tree_end,
                                                          int32_t chunk, int32_t n_chunks, int32_t n_rb, int32_t R,
                                                          const uint8_t* __restrict__ codes, int64_t n, int32_t C,
@@ -44,7 +44,7 @@ __global__ __launch_bounds__(kPredBlock) void k_traverse(TreesView F, int32_t tr
   extern __shared__ __align__(16) uint8_t lds[];
   constexpr uint32_t M = TP * kPredBlock;
   uint64_t* top = reinterpret_cast<uint64_t*>(lds);
-  uint8_t* rows = lds + 8 * M;
+  uint8_t* rows = lds + 8 * M * G;
   // workgroup b runs on XCD b % 8: with n_chunks a multiple of 8 an XCD's
   // workgroups take the row blocks of one chunk, then those of its next one
   const int32_t b = (int32_t)blockIdx.x;
@@ -62,29 +62,47 @@ __global__ __launch_bounds__(kPredBlock) void k_traverse(TreesView F, int32_t tr
   const int32_t t1 = min(tree_end, t0 + chunk);
   if (nr <= 0 || t0 >= t1) return;
   const uint32_t tid = threadIdx.x;
-  uint64_t pf[TP];
+  uint64_t pf[G][TP];
   auto fetch = [&](int32_t t) {
-    const uint64_t* tn = F.nodes + F.node_base[t];
-    const uint32_t nn = min((uint32_t)F.n_nodes[t], M);
 #pragma unroll
-    for (int u = 0; u < TP; ++u) pf[u] = tid + u * kPredBlock < nn ? tn[tid + u * kPredBlock] : 0ull;
+    for (int g = 0; g < G; ++g) {
+      const bool in = t + g < t1;
+      const uint64_t* tn = F.nodes + (in ? F.node_base[t + g] : 0);
+      const uint32_t nn = in ? min((uint32_t)F.n_nodes[t + g], M) : 0u;
+#pragma unroll
+      for (int u = 0; u < TP; ++u) pf[g][u] = tid + u * kPredBlock < nn ? tn[tid + u * kPredBlock] : 0ull;
+    }
   };
   fetch(t0);
   stage_rows<kPredBlock>(rows, codes, C, nullptr, r0, nr);
-  const bool on[1] = {(int32_t)tid < nr};
-  const uint32_t off[1] = {tid * (uint32_t)staged_stride(C)};
+  const bool in_row = (int32_t)tid < nr;
+  const uint32_t ro = tid * (uint32_t)staged_stride(C);
   int64_t acc = 0;
-  for (int32_t t = t0; t < t1; ++t) {
-    __syncthreads();  // the previous tree is walked (and, at first, the rows are staged)
+  for (int32_t t = t0; t < t1; t += G) {
+    __syncthreads();  // the previous trees are walked (and, at first, the rows are staged)
 #pragma unroll
-    for (int u = 0; u < TP; ++u) top[tid + u * kPredBlock] = pf[u];
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int u = 0; u < TP; ++u) top[g * M + tid + u * kPredBlock] = pf[g][u];
     __syncthreads();
-    if (t + 1 < t1) fetch(t + 1);
-    uint64_t v[1];
-    walk_tree<1>(top, M, F.nodes + F.node_base[t], rows, off, on, v);
-    acc += node_q(v[0]);
+    if (t + G < t1) fetch(t + G);
+    uint64_t v[G];
+    bool on[G];
+    uint32_t off[G];
+    const uint64_t* tops[G];
+    const uint64_t* tn[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      on[g] = in_row && t + g < t1;
+      off[g] = ro;
+      tops[g] = top + g * M;
+      tn[g] = F.nodes + (t + g < t1 ? F.node_base[t + g] : 0);
+    }
+    walk_trees<G>(tops, M, tn, rows, off, on, v);
+#pragma unroll
+    for (int g = 0; g < G; ++g) acc += node_q(v[g]);
   }
-  if (!on[0]) return;
+  if (!in_row) return;
   const int64_t r = r0 + tid;
   if (accumulate) {
     atomicAdd(&sum[r], (unsigned long long)acc);
@@ -164,6 +182,51 @@ __global__ __launch_bounds__(kRowBlock) void k_traverse_row(TreesView F, int32_t
   }
 }
 
+// Prediction in between: 2^lg lanes per row, each with every 2^lg-th tree, codes and
+// nodes where they are, the whole answer in one launch.
+__global__ __launch_bounds__(kPredBlock) void k_traverse_lanes(TreesView F, int32_t tree_begin, int32_t tree_end,
+                                                               int32_t lg, const uint8_t* __restrict__ codes,
+                                                               int64_t n, int32_t C,
+                                                               unsigned long long* __restrict__ sum,
+                                                               double* __restrict__ y, double trees) {
+  const int64_t g = (int64_t)blockIdx.x * kPredBlock + threadIdx.x;
+  const int64_t r = g >> lg;
+  const int32_t slot = (int32_t)(g & ((1 << lg) - 1)), step = 1 << lg;
+  const uint8_t* row = codes + min(r, n - 1) * C;
+  constexpr int K = 2;
+  int64_t acc = 0;
+  for (int32_t t = tree_begin + slot; t < tree_end; t += K * step) {
+    const uint64_t* tn[K];
+    uint64_t v[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const bool in = t + k * step < tree_end;
+      tn[k] = F.nodes + (in ? F.node_base[t + k * step] : 0);
+      v[k] = in ? tn[k][0] : (uint64_t)kLeafCol;
+    }
+    bool open = true;
+    while (open) {
+      open = false;
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const uint32_t c = node_col(v[k]);
+        if (c != kLeafCol) {
+          const NodePair p = *reinterpret_cast<const NodePair*>(tn[k] + node_left(v[k]));
+          v[k] = row[c] > node_bin(v[k]) ? p.r : p.l;
+          open = true;
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) acc += node_q(v[k]);
+  }
+  for (int d = step >> 1; d >= 1; d >>= 1) acc += __shfl_xor((long long)acc, d, kWave);
+  if (slot == 0 && r < n) {
+    if (sum) sum[r] = (unsigned long long)acc;
+    if (y) y[r] = ((double)acc * 0x1p-32) / trees;
+  }
+}
+
 __global__ void k_zero_i64(unsigned long long* p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     p[i] = 0ull;
@@ -238,20 +301,30 @@ void launch_rank_accuracy(const double* times, const double* truth, int64_t m, i
   AIWC_HIP(hipGetLastError());
 }
 
-// A workgroup per row saves the staging and two of three launches, but each of
-// its lanes reads another tree: it wins up to about 450000 (row, tree) pairs
-// on the paper's frame (512 rows x 505 trees 17 us against 25, 768 rows 22, 1024
-// rows 31 against 25) and 150000 on trees that outgrow the L2 (200000 training
-// rows, 500 trees: 256 rows 32 us against 36, 512 rows 53 against 42).
-bool predict_by_row(const TreesView& F, int64_t n, int32_t n_trees) {
-  return n > 0 && n <= 1024 && n * n_trees <= (F.train_rows <= 100000 ? (int64_t)1 << 18 : (int64_t)1 << 17);
+// By (row, tree) pairs, and the size of the trees, from which the reads that share
+// no cache line cost more.  A workgroup per row reads another tree with every
+// lane, one launch: 60 rows x 505 trees of 2220 training rows 9 us against 25
+// with the rows staged, 512 rows 17 and 25, 1024 rows 31 and 25; trees of 200000:
+// 256 rows 32 and 36, 512 rows 53 and 42.  Few trees take lanes of a row, also one
+// launch: 10000 rows x 16 trees of 2220 rows 11 us and 19, 50000 rows 26 and 30,
+// 200000 rows 80 and 57; 2000 rows x 250 trees 22 and 25, 4096 rows 39 and 31; 16
+// trees of 30000: 10000 rows 14 and 24, 50000 rows 42 and 37; of 200000: 10000 rows
+// 16 and 24; 64 trees, 1000 rows 18 and 23, 4096 rows 27 and 26.
+PredictRoute predict_route(const TreesView& F, int64_t n, int32_t n_trees) {
+  const int64_t pairs = n * n_trees, r = F.train_rows;
+  if (n <= 1024 && pairs <= (r <= 100000 ? (int64_t)5 << 16 : (int64_t)1 << 17)) return PredictRoute::kRow;
+  const int64_t lanes = r <= 4096 ? (int64_t)1 << (n_trees <= 64 ? 20 : 19)
+                        : r <= 100000 || n_trees <= 16 ? (int64_t)1 << 18
+                                                       : (int64_t)1 << 17;
+  if (n_trees <= (r <= 4096 ? 256 : 64) && pairs <= lanes) return PredictRoute::kLanes;
+  return PredictRoute::kMany;
 }
 
 void launch_select_device(const TreesView& F, int32_t tree_begin, int32_t tree_end, const uint8_t* feature_codes,
                           int64_t m, int32_t C, int32_t n_devices, int32_t num_trees, uint8_t* expanded, int64_t* sum,
                           double* times, int32_t* best, hipStream_t s) {
   const int64_t rows = m * n_devices;
-  if (predict_by_row(F, rows, tree_end - tree_begin)) {
+  if (predict_route(F, rows, tree_end - tree_begin) == PredictRoute::kRow) {
     k_traverse_row<<<(unsigned)rows, kRowBlock, 0, s>>>(F, tree_begin, tree_end, feature_codes, C, n_devices, nullptr,
                                                         times, (double)num_trees);
     AIWC_HIP(hipGetLastError());
@@ -298,22 +371,26 @@ void allow_lds(const void* kernel) {
 namespace {
 
 // Launch of k_traverse: the row blocks, and the tree chunks that the CUs get
-// through soonest.  A workgroup's time is its chunk's trees and about 1.5 more
-// for staging its rows; `slots` workgroups run at a time.
-template <int TP>
+// through soonest, in times of a tree's walk: a workgroup takes its chunk's trees
+// (four walked together about 1.6) and about 1.5 for staging its rows, `slots`
+// workgroups run at a time, and more than one chunk costs two more launches and
+// an atomic per row and chunk.
+template <int TP, int G>
 void traverse_many(const TreesView& F, int32_t tree_begin, int32_t tree_end, const uint8_t* codes, int64_t n,
                    int32_t C, int64_t* sum, double* y, int32_t num_trees, hipStream_t s) {
   const int32_t T = tree_end - tree_begin;
   const int64_t n_rb = (n + kPredBlock - 1) / kPredBlock;
   const int32_t R = (int32_t)((n + n_rb - 1) / n_rb);
-  const size_t lds = (size_t)8 * TP * kPredBlock + (size_t)R * staged_stride(C);
+  const size_t lds = (size_t)8 * TP * G * kPredBlock + (size_t)R * staged_stride(C);
   const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(2048 / kPredBlock, (int64_t)(device_info().lds_per_block / lds)));
   const int64_t slots = per_cu * device_info().cus;
   int32_t n_chunks = 1;
   double best = 0.0;
   for (int32_t c = 1; c <= std::min(T, 2048); c += c < 8 ? 1 : 8) {
     const double rounds = (double)((n_rb * c + slots - 1) / slots);
-    const double t = rounds * (1.5 + (double)((T + c - 1) / c));
+    const int32_t per = (T + c - 1) / c;
+    const double walks = G == 1 ? (double)per : 1.6 * (double)((per + G - 1) / G);
+    const double t = rounds * (1.5 + walks) + (c > 1 ? 4.0 + 0.004 * c : 0.0);
     if (c == 1 || t < best) {
       best = t;
       n_chunks = c;
@@ -327,8 +404,8 @@ void traverse_many(const TreesView& F, int32_t tree_begin, int32_t tree_end, con
     k_zero_i64<<<zb, 256, 0, s>>>(reinterpret_cast<unsigned long long*>(sum), n);
     AIWC_HIP(hipGetLastError());
   }
-  if (lds > 65536) allow_lds(reinterpret_cast<const void*>(k_traverse<TP>));
-  k_traverse<TP><<<(unsigned)(n_rb * n_chunks), kPredBlock, lds, s>>>(
+  if (lds > 65536) allow_lds(reinterpret_cast<const void*>(k_traverse<TP, G>));
+  k_traverse<TP, G><<<(unsigned)(n_rb * n_chunks), kPredBlock, lds, s>>>(
       F, tree_begin, tree_end, chunk, n_chunks, (int32_t)n_rb, R, codes, n, C,
       reinterpret_cast<unsigned long long*>(sum), y, (double)num_trees, accumulate);
   AIWC_HIP(hipGetLastError());
@@ -344,9 +421,18 @@ void traverse_many(const TreesView& F, int32_t tree_begin, int32_t tree_end, con
 void launch_predict(const TreesView& F, int32_t tree_begin, int32_t tree_end, const uint8_t* codes, int64_t n,
                     int32_t C, int64_t* sum, double* y, int32_t num_trees, hipStream_t s) {
   if (n <= 0) return;
-  if (predict_by_row(F, n, tree_end - tree_begin)) {
+  const PredictRoute route = predict_route(F, n, tree_end - tree_begin);
+  if (route == PredictRoute::kRow) {
     k_traverse_row<<<(unsigned)n, kRowBlock, 0, s>>>(F, tree_begin, tree_end, codes, C, 0,
                                                      reinterpret_cast<unsigned long long*>(sum), y, (double)num_trees);
+    AIWC_HIP(hipGetLastError());
+    return;
+  }
+  if (route == PredictRoute::kLanes) {
+    int32_t lg = 0;
+    while (lg < 6 && (1 << lg) < tree_end - tree_begin) ++lg;
+    k_traverse_lanes<<<(unsigned)(((n << lg) + kPredBlock - 1) / kPredBlock), kPredBlock, 0, s>>>(
+        F, tree_begin, tree_end, lg, codes, n, C, reinterpret_cast<unsigned long long*>(sum), y, (double)num_trees);
     AIWC_HIP(hipGetLastError());
     return;
   }
@@ -354,10 +440,16 @@ void launch_predict(const TreesView& F, int32_t tree_begin, int32_t tree_end, co
   // a CU; trees of a training set above 100000 rows outgrow an XCD's L2, where
   // a level less read from it pays (200000 rows predicted by 200 trees of 64000
   // training rows: 650 us with 256 nodes, 718 with 512; of 128000: 874 and 799).
-  if (F.train_rows <= 100000)
-    traverse_many<1>(F, tree_begin, tree_end, codes, n, C, sum, y, num_trees, s);
+  // Small trees are walked four at a time: a barrier per tree and a short walk
+  // leave little to overlap (200000 rows x 250 trees of 300 training rows: 651 us
+  // one at a time, 500 four; of 2220 rows 567 and 504; of 30000, which share the
+  // L2, 924 and 1141).
+  if (F.train_rows <= 8192)
+    traverse_many<1, 4>(F, tree_begin, tree_end, codes, n, C, sum, y, num_trees, s);
+  else if (F.train_rows <= 100000)
+    traverse_many<1, 1>(F, tree_begin, tree_end, codes, n, C, sum, y, num_trees, s);
   else
-    traverse_many<2>(F, tree_begin, tree_end, codes, n, C, sum, y, num_trees, s);
+    traverse_many<2, 1>(F, tree_begin, tree_end, codes, n, C, sum, y, num_trees, s);
 }
 
 }  // namespace aiwc

@@ -56,23 +56,22 @@ __device__ __forceinline__ void stage_rows(uint8_t* dst, const uint8_t* __restri
   }
 }
 
-// The leaf words that K rows of a tree reach: row k's staged codes at rows +
-// off[k]; a row whose `on` is false gets a leaf of value 0.  top holds the
-// tree's first m nodes (breadth first, so its upper levels), tn all of them in
-// global memory.  The K rows' walks are interleaved, so that their dependent
-// reads overlap: first through the LDS part, then, for the rows that left it,
+// The leaf words that K walks reach: row k's staged codes at rows + off[k], down
+// the tree whose nodes are tn[k] in global memory and whose first m (breadth
+// first, so its upper levels) are at top[k] in the LDS; a walk whose `on` is false
+// gets a leaf of value 0.  The walks are interleaved, so that their dependent
+// reads overlap: first through the LDS part, then, for those that left it,
 // through the rest.
 template <int K>
-__device__ __forceinline__ void walk_tree(const uint64_t* top, uint32_t m, const uint64_t* __restrict__ tn,
-                                          const uint8_t* rows, const uint32_t (&off)[K], const bool (&on)[K],
-                                          uint64_t (&v)[K]) {
+__device__ __forceinline__ void walk_trees(const uint64_t* const (&top)[K], uint32_t m, const uint64_t* const (&tn)[K],
+                                           const uint8_t* rows, const uint32_t (&off)[K], const bool (&on)[K],
+                                           uint64_t (&v)[K]) {
   constexpr uint64_t kNoLeaf = (uint64_t)kLeafCol;  // a leaf of value 0
   uint32_t nx[K];
   bool open = false, deep = false;
-  const uint64_t root = top[0];
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    v[k] = on[k] ? root : kNoLeaf;
+    v[k] = on[k] ? top[k][0] : kNoLeaf;
     nx[k] = 0;
     open |= node_col(v[k]) != kLeafCol;
   }
@@ -84,7 +83,7 @@ __device__ __forceinline__ void walk_tree(const uint64_t* top, uint32_t m, const
       if (c != kLeafCol) {
         const uint32_t next = node_left(v[k]) + (rows[off[k] + c] > node_bin(v[k]) ? 1u : 0u);
         if (next < m) {
-          v[k] = top[next];
+          v[k] = top[k][next];
           open = true;
         } else {
           v[k] = kNoLeaf;
@@ -97,14 +96,14 @@ __device__ __forceinline__ void walk_tree(const uint64_t* top, uint32_t m, const
   if (!deep) return;
 #pragma unroll
   for (int k = 0; k < K; ++k)
-    if (nx[k]) v[k] = tn[nx[k]];
+    if (nx[k]) v[k] = tn[k][nx[k]];
   while (deep) {
     deep = false;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       const uint32_t c = node_col(v[k]);
       if (c != kLeafCol) {
-        v[k] = tn[node_left(v[k]) + (rows[off[k] + c] > node_bin(v[k]) ? 1u : 0u)];
+        v[k] = tn[k][node_left(v[k]) + (rows[off[k] + c] > node_bin(v[k]) ? 1u : 0u)];
         deep = true;
       }
     }

@@ -31,12 +31,15 @@ def _fitted(rf, oracle, C, n, trees, bins, seed, mtry=None):
     return forest, oracle.fit(codes, nb, y, trees, mtry, 2, seed=seed), rng
 
 
-# rows x trees on both sides of the per-row kernel's limit (1024 rows, 2^18 pairs),
-# whole and broken workgroups of 256 rows, one chunk of trees and many; columns
-# with even and odd row strides, and the widest row (255 columns)
+# rows x trees on both sides of the limits of a workgroup per row (1024 rows, 5 x
+# 2^16 pairs) and of lanes per row (2^20 pairs, 2^19 above 64 trees, none above
+# 256), whole and broken workgroups of 256 rows, one chunk of trees and many,
+# trees in and out of fours; columns with even and odd row strides, and the
+# widest row (255 columns)
 @pytest.mark.parametrize("C,trees,rows", [
-    (2, 1, (1, 1024, 1025, 1280)), (35, 9, (1, 255, 1023, 1024, 1025, 5000, 29128)),
-    (64, 300, (3, 873, 874, 1000, 4097)), (65, 1030, (1, 254, 255, 300, 513)), (255, 20, (7, 1024, 1025, 1300)),
+    (2, 1, (1, 1024, 1025, 1280)), (35, 9, (1, 255, 1023, 1024, 1025, 5000, 116508, 116509)),
+    (64, 300, (3, 1000, 1092, 1093, 4097)), (65, 1030, (1, 318, 319, 513)), (255, 20, (7, 1024, 1025, 52429)),
+    (12, 64, (1025, 16384, 16385)), (7, 65, (1025, 8065, 8066)), (5, 256, (1024, 2048, 2049)), (5, 257, (1025, 2049)),
 ])
 def test_predict_paths(rf, oracle, C, trees, rows):
     import torch
