@@ -190,15 +190,18 @@ void aiwc_rf_server::run() {
   try {
     AIWC_HIP(hipSetDevice(device));
     bool head_waited = false;  // the current head request already counted a wait
+    Clock::time_point progress = Clock::now();  // of the last launch or retired batch
     for (;;) {
       // retire finished batches; any status but "done" or "not ready" is an error
       for (Slot& s : slots) {
         if (!s.busy) continue;
         const hipError_t q = hipEventQuery(s.done);
-        if (q == hipSuccess)
+        if (q == hipSuccess) {
           retire(s);
-        else if (q != hipErrorNotReady)
+          progress = Clock::now();
+        } else if (q != hipErrorNotReady) {
           AIWC_HIP(q);
+        }
       }
       // pack a batch for a free stream from the oldest requests that fit
       std::vector<Request> batch;
@@ -236,10 +239,16 @@ void aiwc_rf_server::run() {
           continue;
         }
       }
-      if (!batch.empty())
+      if (!batch.empty()) {
         launch(*free_slot, std::move(batch), first, rows);
-      else  // every stream busy or the head request does not fit yet
+        progress = Clock::now();
+      } else if (Clock::now() - progress < std::chrono::microseconds(500)) {
+        // every stream busy or the head request does not fit yet: a batch takes
+        // some tens of microseconds, and a sleep of 20 takes about 75
+        std::this_thread::yield();
+      } else {
         std::this_thread::sleep_for(std::chrono::microseconds(20));
+      }
     }
   } catch (const Error& e) {
     std::lock_guard<std::mutex> g(mu);
