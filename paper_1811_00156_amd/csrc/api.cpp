@@ -732,6 +732,33 @@ int aiwc_rf_forest_export_host(const aiwc_rf_forest* f, int32_t forest_index, in
     const int64_t t0 = f->first_task[forest_index];
     std::vector<int32_t> nn((size_t)(tree_end - tree_begin));
     AIWC_HIP(hipMemcpy(nn.data(), f->n_nodes.p + t0 + tree_begin, sizeof(int32_t) * nn.size(), hipMemcpyDeviceToHost));
+    int64_t all = 0;
+    for (int32_t v : nn) all += v;
+    if (nn.size() <= 4 && all <= 16384) {
+      // a tree's words and weights taken as they are (one tree 66 us, by the
+      // slices below 144; four trees about as long either way)
+      std::vector<uint64_t> words;
+      std::vector<uint32_t> N;
+      size_t out = 0;
+      for (int32_t t = tree_begin; t < tree_end; ++t) {
+        const size_t cnt = (size_t)nn[t - tree_begin];
+        const int64_t base = f->tasks[t0 + t].node_base;
+        words.resize(cnt);
+        N.resize(cnt);
+        AIWC_HIP(hipMemcpy(words.data(), f->nodes.p + base, sizeof(uint64_t) * cnt, hipMemcpyDeviceToHost));
+        AIWC_HIP(hipMemcpy(N.data(), f->node_N.p + base, sizeof(uint32_t) * cnt, hipMemcpyDeviceToHost));
+        for (size_t i = 0; i < cnt; ++i, ++out) {
+          const uint64_t v = words[i];
+          const bool leaf = node_col(v) == kLeafCol;
+          if (col_host) col_host[out] = (uint8_t)node_col(v);
+          if (bin_host) bin_host[out] = leaf ? 0 : (uint8_t)node_bin(v);
+          if (left_host) left_host[out] = leaf ? -1 : (int32_t)node_left(v);
+          if (q_host) q_host[out] = leaf ? node_q(v) : 0;
+          if (N_host) N_host[out] = (int32_t)N[i];
+        }
+      }
+      return;
+    }
     // slices of whole trees, of at most 2^20 nodes (18 MiB of device memory) where
     // a tree is not larger, unpacked on the forest's device
     constexpr int64_t kSlice = int64_t(1) << 20;

@@ -152,13 +152,42 @@ __device__ __forceinline__ uint32_t block_distinct(const uint32_t* s, int32_t le
   return wave_sum(v);
 }
 
+// A column's thresholds and bin count: its m distinct values (in `all`) but the
+// largest when there are at most max_bins, else its order statistics value(0 ..
+// max_bins - 2), ascending: the first of each run of equal ones, below the
+// column's largest key.
+template <typename Value>
+__device__ __forceinline__ void write_thresholds(uint32_t m, int32_t max_bins, const uint32_t* all, uint32_t vmax,
+                                                 Value value, float* t, int32_t* n_bins, uint32_t* tmp) {
+  const int tid = (int)threadIdx.x, lane = (int)lane_id(), wid = tid / kWave;
+  if (m <= (uint32_t)max_bins) {
+    if (tid < 255) t[tid] = (uint32_t)tid + 1u < m ? key_float(all[tid]) : 0.0f;
+    if (tid == 0) *n_bins = (int32_t)m;
+    return;
+  }
+  const bool in = tid < max_bins - 1;
+  const uint32_t v = in ? value(tid) : 0u;
+  const bool keep = in && v < vmax && (tid == 0 || value(tid - 1) != v);
+  const uint64_t km = __ballot(keep);
+  if (wid < 4 && lane == 0) tmp[wid] = (uint32_t)__popcll(km);
+  __syncthreads();
+  const uint32_t total = tmp[0] + tmp[1] + tmp[2] + tmp[3];
+  uint32_t at = (uint32_t)__popcll(km & ((1ull << lane) - 1ull));
+  for (int w = 0; w < min(wid, 4); ++w) at += tmp[w];
+  if (keep) t[at] = key_float(v);
+  if (tid < 255 && (uint32_t)tid >= total) t[tid] = 0.0f;
+  if (tid == 0) *n_bins = (int32_t)total + 1;
+}
+
 // Sorts chunk blockIdx.x of column blockIdx.y in place and lists its distinct
-// values, up to kMaxDistinct of them.
+// values, up to kMaxDistinct of them; a column of one chunk (ONE) gets its
+// thresholds at once.
 constexpr uint32_t kMaxDistinct = 257;
-template <int K>
+template <int K, bool ONE>
 __global__ __launch_bounds__(kSortBlock) void k_sort_chunks(uint32_t* __restrict__ keys, int64_t n, int64_t n_pad,
-                                                            uint32_t* __restrict__ distinct,
-                                                            uint32_t* __restrict__ n_distinct) {
+                                                            int32_t max_bins, uint32_t* __restrict__ distinct,
+                                                            uint32_t* __restrict__ n_distinct, int32_t* n_bins,
+                                                            float* thresholds) {
   __shared__ uint32_t s[K * kSortBlock];
   __shared__ uint32_t cnt[kCounts];
   __shared__ uint32_t tmp[kSortWaves];
@@ -168,19 +197,39 @@ __global__ __launch_bounds__(kSortBlock) void k_sort_chunks(uint32_t* __restrict
   uint32_t k[K];
 #pragma unroll
   for (int i = 0; i < K; ++i) k[i] = col[wid * K * kWave + i * kWave + lane];
-  block_sort<K>(k, s, cnt, tmp);
-#pragma unroll
-  for (int i = 0; i < K; ++i) col[i * kSortBlock + tid] = s[i * kSortBlock + tid];
   const int32_t len = (int32_t)min((int64_t)K * kSortBlock, n - (int64_t)blockIdx.x * (K * kSortBlock));
-  const uint32_t m = block_distinct<K>(s, len, distinct + c * kMaxDistinct, kMaxDistinct, tmp);
-  if (tid == 0) n_distinct[c] = m;
+  if (K == 1 && ONE && len <= 256) {
+    // few keys: each one's place is the number of keys before it
+    s[tid] = k[0];
+    __syncthreads();
+    uint32_t at = 0;
+    if (tid < len) {
+      for (int32_t j = 0; j < len; ++j) at += (s[j] < k[0] || (s[j] == k[0] && j < tid)) ? 1u : 0u;
+    }
+    __syncthreads();
+    if (tid < len) s[at] = k[0];
+    __syncthreads();
+  } else {
+    block_sort<K>(k, s, cnt, tmp);
+  }
+  if constexpr (ONE) {
+    uint32_t* all = cnt;  // (the sort is done with its counts)
+    const uint32_t m = block_distinct<K>(s, len, all, kMaxDistinct, tmp);
+    __syncthreads();
+    write_thresholds(m, max_bins, all, s[len - 1], [&](int r) { return s[(r + 1) * n / max_bins - 1]; },
+                     thresholds + (int64_t)blockIdx.y * 255, n_bins + blockIdx.y, tmp);
+  } else {
+#pragma unroll
+    for (int i = 0; i < K; ++i) col[i * kSortBlock + tid] = s[i * kSortBlock + tid];
+    const uint32_t m = block_distinct<K>(s, len, distinct + c * kMaxDistinct, kMaxDistinct, tmp);
+    if (tid == 0) n_distinct[c] = m;
+  }
 }
 
 // Order statistics: wave t of column blockIdx.y finds the key of rank floor(k n /
 // B) - 1, k = t + 1, among the column's sorted chunks, lane c holding chunk c.
 // Key bits are decided from the top: the keys below the prefix with the bit set
-// are counted by a bisection of each chunk's remaining range.  (One chunk needs no
-// search: k_thresholds reads its ranks.)  200000 x 64, 255 ranks: 120 us, bound by
+// are counted by a bisection of each chunk's remaining range.   200000 x 64, 255 ranks: 120 us, bound by
 // the address unit (a cache line per chunk and step); it and the chunk sort (132
 // us) take the place of a bitonic sort of the whole columns (1370 us).
 __global__ __launch_bounds__(256) void k_select(const uint32_t* __restrict__ keys, int64_t n, int64_t n_pad,
@@ -243,8 +292,8 @@ __global__ __launch_bounds__(256) void k_select(const uint32_t* __restrict__ key
   if (lane == 0) stat[(int64_t)blockIdx.y * 256 + k - 1] = prefix;
 }
 
-// Thresholds of one column (one workgroup per column) from its chunks' distinct
-// values or its order statistics.
+// Thresholds of one column of several chunks (one workgroup per column) from the
+// chunks' distinct values or the order statistics.
 __global__ __launch_bounds__(kSortBlock) void k_thresholds(const uint32_t* __restrict__ keys, int64_t n, int64_t n_pad,
                                                            int32_t chunk, int32_t n_chunks, int32_t max_bins,
                                                            const uint32_t* __restrict__ distinct,
@@ -256,11 +305,9 @@ __global__ __launch_bounds__(kSortBlock) void k_thresholds(const uint32_t* __res
   __shared__ uint32_t all[kMaxDistinct + 1];
   __shared__ uint32_t tmp[kSortWaves];
   __shared__ uint32_t s_most;
-  const int j = blockIdx.x, tid = (int)threadIdx.x, lane = (int)lane_id(), wid = tid / kWave;
-  float* t = thresholds + (int64_t)j * 255;
+  const int j = blockIdx.x, lane = (int)lane_id(), wid = (int)threadIdx.x / kWave;
   const uint32_t* nd = n_distinct + (int64_t)j * n_chunks;
   const uint32_t* dl = distinct + (int64_t)j * n_chunks * kMaxDistinct;
-  if (tid < 255) t[tid] = 0.0f;
   if (wid == 0) {  // the most distinct values of any chunk
     uint32_t m = lane < n_chunks ? nd[lane] : 0u;
     for (int d = 32; d >= 1; d >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, d, kWave));
@@ -269,82 +316,60 @@ __global__ __launch_bounds__(kSortBlock) void k_thresholds(const uint32_t* __res
   __syncthreads();
   uint32_t m = s_most;  // the column's distinct values, or more than max_bins
   if (m <= (uint32_t)max_bins) {
-    if (n_chunks == 1) {
-      for (uint32_t i = tid; i < m; i += kSortBlock) all[i] = dl[i];
-    } else {
-      // at most 32 x 256 values: sorted again, and their distinct ones listed
-      constexpr int K = kChunk / kSortBlock;
-      uint32_t k[K];
-      uint32_t total = 0;
+    // at most 32 x 256 values: sorted again, and their distinct ones listed
+    constexpr int K = kChunk / kSortBlock;
+    uint32_t k[K];
+    uint32_t total = 0;
 #pragma unroll
-      for (int i = 0; i < K; ++i) k[i] = 0xFFFFFFFFu;
-      for (int c = 0; c < n_chunks; ++c) total += nd[c];
+    for (int i = 0; i < K; ++i) k[i] = 0xFFFFFFFFu;
+    for (int c = 0; c < n_chunks; ++c) total += nd[c];
 #pragma unroll
-      for (int i = 0; i < K; ++i) {
-        uint32_t g = (uint32_t)(wid * K * kWave + i * kWave + lane);
-        if (g < total) {
-          int c = 0;
-          while (g >= nd[c]) g -= nd[c++];
-          k[i] = dl[(int64_t)c * kMaxDistinct + g];
-        }
+    for (int i = 0; i < K; ++i) {
+      uint32_t g = (uint32_t)(wid * K * kWave + i * kWave + lane);
+      if (g < total) {
+        int c = 0;
+        while (g >= nd[c]) g -= nd[c++];
+        k[i] = dl[(int64_t)c * kMaxDistinct + g];
       }
-      block_sort<K>(k, s, cnt, tmp);
-      m = block_distinct<K>(s, (int32_t)total, all, kMaxDistinct, tmp);
     }
+    block_sort<K>(k, s, cnt, tmp);
+    m = block_distinct<K>(s, (int32_t)total, all, kMaxDistinct, tmp);
   }
   __syncthreads();
-  if (m <= (uint32_t)max_bins) {  // every distinct value except the largest
-    for (uint32_t i = tid; i + 1 < m; i += kSortBlock) t[i] = key_float(all[i]);
-    if (tid == 0) n_bins[j] = (int32_t)m;
-    return;
-  }
   // the column's largest key: the last of its chunks' last ones
   uint32_t vmax = 0;
   for (int c = 0; c < n_chunks; ++c) {
     const int64_t last = min((int64_t)(c + 1) * chunk, n) - 1;
     vmax = max(vmax, keys[(int64_t)j * n_pad + last]);
   }
-  // order statistics are ascending: the first of each run of equal ones, below the largest key
-  if (wid < 4) {
-    const bool in = tid < max_bins - 1;
-    auto value = [&](int k) {  // the order statistic of rank floor((k + 1) n / max_bins) - 1
-      return n_chunks > 1 ? stat[(int64_t)j * 256 + k] : keys[(int64_t)j * n_pad + (k + 1) * n / max_bins - 1];
-    };
-    const uint32_t v = in ? value(tid) : 0u;
-    const bool keep = in && v < vmax && (tid == 0 || value(tid - 1) != v);
-    const uint64_t km = __ballot(keep);
-    if (lane == 0) tmp[wid] = (uint32_t)__popcll(km);
-    all[tid] = keep ? (uint32_t)__popcll(km & ((1ull << lane) - 1ull)) : 0xFFFFFFFFu;
-    s[tid] = v;
-  }
-  __syncthreads();
-  if (tid < 256 && all[tid] != 0xFFFFFFFFu) {
-    uint32_t at = all[tid];
-    for (int w = 0; w < wid; ++w) at += tmp[w];
-    t[at] = key_float(s[tid]);
-  }
-  if (tid == 0) n_bins[j] = (int32_t)(tmp[0] + tmp[1] + tmp[2] + tmp[3]) + 1;
+  write_thresholds(m, max_bins, all, vmax, [&](int r) { return stat[(int64_t)j * 256 + r]; },
+                   thresholds + (int64_t)j * 255, n_bins + j, tmp);
 }
 
 // code(x) = #{thresholds < x}; column p = device id.  A workgroup codes R rows in
 // up to kEncodeCols columns, whose thresholds it holds in the LDS, padded with
-// +inf to 255 so that the search takes the same eight steps for every column; the
-// row of 256 words plus one puts a step's reads of neighbouring columns into
-// different banks.
+// +inf to one less than a power of two that holds the largest column's, so that
+// the search takes the same steps for every column; the odd row of words puts a
+// step's reads of neighbouring columns into different banks.
 constexpr int kEncodeCols = 64;
 __global__ __launch_bounds__(256) void k_encode(const float* __restrict__ X, const int32_t* __restrict__ dev,
                                                 int64_t n, int32_t p, int32_t n_devices, int32_t R,
                                                 const int32_t* __restrict__ n_bins,
                                                 const float* __restrict__ thresholds, uint8_t* __restrict__ codes,
                                                 uint32_t* status) {
-  extern __shared__ float s_thr[];  // [columns][257]
+  extern __shared__ float s_thr[];  // [columns][2 top + 1], at most 257 words a row
   const int32_t C = p + 1, j0 = (int32_t)blockIdx.y * kEncodeCols, nc = min(kEncodeCols, p - j0);
   const int64_t i0 = (int64_t)blockIdx.x * R;
   const int32_t nr = (int32_t)min((int64_t)R, n - i0), tid = (int32_t)threadIdx.x;
   uint32_t bad = 0;
-  for (int32_t e = tid; e < nc * 256; e += 256) {
-    const int32_t c = e >> 8, k = e & 255;
-    s_thr[c * 257 + k] = k < n_bins[j0 + c] - 1 ? thresholds[(int64_t)(j0 + c) * 255 + k] : INFINITY;
+  int32_t most = 1;  // bins of the largest column
+  for (int32_t c = 0; c < nc; ++c) most = max(most, n_bins[j0 + c]);
+  int32_t lg = 0;  // a search of lg steps tells 2^lg codes apart
+  while ((1 << lg) < most) ++lg;
+  const int32_t st = (1 << lg) + 1;
+  for (int32_t e = tid; e < nc << lg; e += 256) {
+    const int32_t c = e >> lg, k = e & ((1 << lg) - 1);
+    s_thr[c * st + k] = k < n_bins[j0 + c] - 1 ? thresholds[(int64_t)(j0 + c) * 255 + k] : INFINITY;
   }
   if (blockIdx.y == 0) {
     for (int32_t r = tid; r < nr; r += 256) {
@@ -361,10 +386,9 @@ __global__ __launch_bounds__(256) void k_encode(const float* __restrict__ X, con
     const uint32_t r = nc > 1 ? __umulhi(e, inv) : e, c = e - r * (uint32_t)nc;
     const float x = X[(i0 + r) * p + j0 + c];
     if (isnan(x)) bad |= kStatusBadFeature;
-    const float* t = s_thr + c * 257;
+    const float* t = s_thr + c * (uint32_t)st;
     uint32_t at = 0;
-#pragma unroll
-    for (uint32_t st = 128; st > 0; st >>= 1) at += t[at + st - 1] < x ? st : 0u;
+    for (uint32_t d = 1u << lg >> 1; d > 0; d >>= 1) at += t[at + d - 1] < x ? d : 0u;
     codes[(i0 + r) * C + j0 + c] = (uint8_t)at;
   }
   if (bad) atomicOr(status, bad);
@@ -403,11 +427,11 @@ __global__ __launch_bounds__(256) void k_encode_few(const float* __restrict__ X,
   if (bad) atomicOr(status, bad);
 }
 
-template <int K>
-void sort_chunks(uint32_t* keys, int64_t n, int64_t n_pad, int32_t p, uint32_t* distinct, uint32_t* n_distinct,
-                 hipStream_t s) {
-  k_sort_chunks<K><<<dim3((unsigned)(n_pad / (K * kSortBlock)), (unsigned)p), kSortBlock, 0, s>>>(keys, n, n_pad,
-                                                                                              distinct, n_distinct);
+template <int K, bool ONE>
+void sort_chunks(uint32_t* keys, int64_t n, int64_t n_pad, int32_t p, int32_t max_bins, uint32_t* distinct,
+                 uint32_t* n_distinct, int32_t* n_bins, float* thresholds, hipStream_t s) {
+  k_sort_chunks<K, ONE><<<dim3((unsigned)(n_pad / (K * kSortBlock)), (unsigned)p), kSortBlock, 0, s>>>(
+      keys, n, n_pad, max_bins, distinct, n_distinct, n_bins, thresholds);
   AIWC_HIP(hipGetLastError());
 }
 
@@ -420,19 +444,21 @@ void launch_bin_fit(const float* X, const int32_t* dev, int64_t n, int32_t p, in
   const int32_t chunk = n <= 1024 ? 1024 : n <= 2048 ? 2048 : n <= 4096 ? 4096 : kChunk;
   const int64_t n_chunks = (n + chunk - 1) / chunk, n_pad = n_chunks * chunk;
   DevBuf<uint32_t> keys((size_t)n_pad * p, s);
+  k_make_keys<<<dim3((unsigned)(n_pad / 64), (unsigned)((p + 63) / 64)), 256, 0, s>>>(X, n, p, n_pad, keys.p, d_status);
+  AIWC_HIP(hipGetLastError());
+  if (n_chunks == 1) {
+    const auto sort = chunk == 1024   ? sort_chunks<1, true>
+                      : chunk == 2048 ? sort_chunks<2, true>
+                      : chunk == 4096 ? sort_chunks<4, true>
+                                      : sort_chunks<8, true>;
+    sort(keys.p, n, n_pad, p, max_bins, nullptr, nullptr, d_n_bins, d_thresholds, s);
+    return;
+  }
   DevBuf<uint32_t> distinct((size_t)p * n_chunks * (kMaxDistinct + 1) + (size_t)p * 256, s);
   uint32_t* n_distinct = distinct.p + (size_t)p * n_chunks * kMaxDistinct;
   uint32_t* stat = n_distinct + (size_t)p * n_chunks;
-  k_make_keys<<<dim3((unsigned)(n_pad / 64), (unsigned)((p + 63) / 64)), 256, 0, s>>>(X, n, p, n_pad, keys.p, d_status);
-  AIWC_HIP(hipGetLastError());
-  switch (chunk) {
-    case 1024: sort_chunks<1>(keys.p, n, n_pad, p, distinct.p, n_distinct, s); break;
-    case 2048: sort_chunks<2>(keys.p, n, n_pad, p, distinct.p, n_distinct, s); break;
-    case 4096: sort_chunks<4>(keys.p, n, n_pad, p, distinct.p, n_distinct, s); break;
-    default: sort_chunks<8>(keys.p, n, n_pad, p, distinct.p, n_distinct, s); break;
-  }
-  if (n_chunks > 1)
-    k_select<<<dim3((unsigned)((max_bins + 2) / 4), (unsigned)p), 256, 0, s>>>(keys.p, n, n_pad, chunk, (int32_t)n_chunks,
+  sort_chunks<8, false>(keys.p, n, n_pad, p, max_bins, distinct.p, n_distinct, nullptr, nullptr, s);
+  k_select<<<dim3((unsigned)((max_bins + 2) / 4), (unsigned)p), 256, 0, s>>>(keys.p, n, n_pad, chunk, (int32_t)n_chunks,
                                                                             max_bins, stat);
   AIWC_HIP(hipGetLastError());
   k_thresholds<<<p, kSortBlock, 0, s>>>(keys.p, n, n_pad, chunk, (int32_t)n_chunks, max_bins, distinct.p, n_distinct,
@@ -443,9 +469,10 @@ void launch_bin_fit(const float* X, const int32_t* dev, int64_t n, int32_t p, in
 void launch_bin_encode(const float* X, const int32_t* dev, int64_t n, int32_t p, int32_t n_devices,
                        const int32_t* d_n_bins, const float* d_thresholds, uint8_t* codes, uint32_t* d_status,
                        hipStream_t s) {
-  // below 2^19 values the thresholds' way into every workgroup's LDS costs more
-  // than it saves (2220 x 34 values: 15.8 us against 4.2; 200000 x 64: 84 against 228)
-  if (n * (p + 1) < (int64_t)1 << 19) {
+  // below 2^21 values the thresholds' way into every workgroup's LDS costs more
+  // than it saves (2220 x 34 values: 15.8 us against 4.2, 22015 x 80 about equal, 200000 x 64: 84
+  // against 228)
+  if (n * (p + 1) < (int64_t)1 << 21) {
     k_encode_few<<<(unsigned)((n * (p + 1) + 255) / 256), 256, 0, s>>>(X, dev, n, p, n_devices, d_n_bins, d_thresholds,
                                                                      codes, d_status);
     AIWC_HIP(hipGetLastError());

@@ -17,7 +17,7 @@ __global__ __launch_bounds__(256) void k_unpack(const uint64_t* __restrict__ nod
                                                 int32_t* __restrict__ N) {
   const int32_t t = (int32_t)blockIdx.x;
   const int64_t o = off[t], cnt = off[t + 1] - o, base = node_base[t];
-  for (int64_t i = threadIdx.x; i < cnt; i += 256) {
+  for (int64_t i = (int64_t)blockIdx.y * 256 + threadIdx.x; i < cnt; i += (int64_t)gridDim.y * 256) {
     const uint64_t v = nodes[base + i];
     const bool leaf = node_col(v) == kLeafCol;
     if (col) col[o + i] = (uint8_t)node_col(v);
@@ -32,7 +32,9 @@ __global__ __launch_bounds__(256) void k_unpack(const uint64_t* __restrict__ nod
 
 void launch_unpack(const uint64_t* nodes, const uint32_t* node_N, const int64_t* node_base, const int64_t* off,
                    int32_t n_trees, uint8_t* col, uint8_t* bin, int32_t* left, int64_t* q, int32_t* N, hipStream_t s) {
-  k_unpack<<<(unsigned)n_trees, 256, 0, s>>>(nodes, node_N, node_base, off, col, bin, left, q, N);
+  // a few workgroups per CU, however few the trees
+  const unsigned per_tree = (unsigned)std::max(1, 4 * device_info().cus / n_trees);
+  k_unpack<<<dim3((unsigned)n_trees, per_tree), 256, 0, s>>>(nodes, node_N, node_base, off, col, bin, left, q, N);
   AIWC_HIP(hipGetLastError());
 }
 

@@ -314,9 +314,9 @@ PredictRoute predict_route(const TreesView& F, int64_t n, int32_t n_trees) {
   const int64_t pairs = n * n_trees, r = F.train_rows;
   if (n <= 1024 && pairs <= (r <= 100000 ? (int64_t)5 << 16 : (int64_t)1 << 17)) return PredictRoute::kRow;
   const int64_t lanes = r <= 4096 ? (int64_t)1 << (n_trees <= 64 ? 20 : 19)
-                        : r <= 100000 || n_trees <= 16 ? (int64_t)1 << 18
-                                                       : (int64_t)1 << 17;
-  if (n_trees <= (r <= 4096 ? 256 : 64) && pairs <= lanes) return PredictRoute::kLanes;
+                        : (r <= 100000 && n_trees <= 64) || n_trees <= 16 ? (int64_t)1 << 18
+                                                                          : (int64_t)1 << 17;
+  if (n_trees <= (r <= 4096 ? 512 : 128) && pairs <= lanes) return PredictRoute::kLanes;
   return PredictRoute::kMany;
 }
 

@@ -45,7 +45,7 @@ def _frame(n, p, seed):
 
 @pytest.mark.parametrize("n,p,max_bins", [
     (1, 3, 2), (255, 9, 256), (1024, 8, 256), (1025, 9, 255), (2048, 8, 2), (2049, 65, 256), (4097, 8, 17),
-    (8192, 8, 256), (8193, 16, 256), (16385, 70, 254), (70001, 8, 256), (262144, 8, 256),
+    (8192, 8, 256), (8193, 16, 256), (16385, 70, 254), (33000, 70, 100), (70001, 8, 256), (262144, 8, 256),
 ])
 def test_thresholds_and_codes(rf, oracle, n, p, max_bins):
     log(f"binning n={n} p={p} max_bins={max_bins}")

@@ -33,13 +33,13 @@ def _fitted(rf, oracle, C, n, trees, bins, seed, mtry=None):
 
 # rows x trees on both sides of the limits of a workgroup per row (1024 rows, 5 x
 # 2^16 pairs) and of lanes per row (2^20 pairs, 2^19 above 64 trees, none above
-# 256), whole and broken workgroups of 256 rows, one chunk of trees and many,
+# 512), whole and broken workgroups of 256 rows, one chunk of trees and many,
 # trees in and out of fours; columns with even and odd row strides, and the
 # widest row (255 columns)
 @pytest.mark.parametrize("C,trees,rows", [
     (2, 1, (1, 1024, 1025, 1280)), (35, 9, (1, 255, 1023, 1024, 1025, 5000, 116508, 116509)),
     (64, 300, (3, 1000, 1092, 1093, 4097)), (65, 1030, (1, 318, 319, 513)), (255, 20, (7, 1024, 1025, 52429)),
-    (12, 64, (1025, 16384, 16385)), (7, 65, (1025, 8065, 8066)), (5, 256, (1024, 2048, 2049)), (5, 257, (1025, 2049)),
+    (12, 64, (1025, 16384, 16385)), (7, 65, (1025, 8065, 8066)), (5, 512, (1024, 1025)), (5, 513, (1025, 2049)),
 ])
 def test_predict_paths(rf, oracle, C, trees, rows):
     import torch
@@ -133,3 +133,14 @@ def test_heldout_paths(rf, oracle, sizes, trees):
         # n non-negative terms summed in two orders: within 2 n 2^-53 of each other
         assert abs(res.mse[k] - (e * e).mean()) <= 2 * (size + 1) * 2.0 ** -53 * (e * e).mean()
         at += size
+
+
+# node arrays taken tree by tree (up to four trees) and unpacked on the device
+def test_export_few_and_many(rf, oracle):
+    log("export few and many trees")
+    forest, of, _ = _fitted(rf, oracle, 9, 400, 7, 30, 2)
+    for a, b in ((0, 1), (2, 6), (1, 6), (0, 7)):
+        for t, tree in zip(range(a, b), forest.export(0, a, b)):
+            ot = of.tree(t)
+            for k in ("col", "bin", "left", "q", "N"):
+                assert np.array_equal(tree[k], ot[k]), (a, b, t, k)
