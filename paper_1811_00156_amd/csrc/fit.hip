@@ -1,6 +1,6 @@
-// Forest fitting on gfx950: one workgroup grows one tree at a time, level by
-// level, pulling trees from a device-side queue until every tree of every
-// forest in the launch is grown.
+// Forest fitting on gfx950: one workgroup (k_grow) or one wave of a workgroup of
+// sixteen (k_grow_teams) grows one tree at a time, level by level, pulling trees
+// from a device-side queue until every tree of every forest in the launch is grown.
 //
 // Per tree (Sec. III-B: a random-forest regression tree with num.trees, mtry and
 // min.node.size; the readings of the unspecified steps are listed in the public
@@ -13,9 +13,10 @@
 //      node's number of in-bag rows:
 //        - small (<= 64 rows): one row per lane in a segment of 4..64 lanes,
 //          every candidate column's codes gathered at once, the left sums of
-//          each lane's split found from the segment's rows staged in LDS;
-//        - large (<= huge limit): one wave per (node, column), LDS histogram of
-//          (N, S, Q) per bin and a wave prefix scan over bins;
+//          each lane's split found from the segment's rows staged in LDS (by matrix
+//          instructions in k_grow_teams), the rows of a split placed at once;
+//        - large (<= huge limit): one wave per (node, up to four columns), one LDS
+//          histogram of packed (N, S) per column and a wave prefix scan over bins;
 //        - wide (above a tuned size): the whole workgroup takes a batch of such
 //          nodes at once; each row's entry is read once and its codes in all
 //          candidate columns are gathered by one thread, into packed (N, S)
@@ -95,7 +96,7 @@ struct Cursor {
 };
 
 struct Scratch {
-  uint32_t* cnt;
+  uint32_t* draws;
   Level2 L0, L1;
   uint8_t* status;
   uint8_t* cand;     // level node k's candidate columns at k * cand_stride(mtry), ascending, padded
@@ -145,7 +146,7 @@ __host__ __device__ inline size_t carve(Scratch* s, uintptr_t base, int64_t n_ca
   const size_t n = (size_t)n_cap;
   // large and huge nodes hold more than kSegMax rows each
   const size_t n_large = n / (kSegMax + 1) + 1;
-  s->cnt = reinterpret_cast<uint32_t*>(take(4 * n));
+  s->draws = reinterpret_cast<uint32_t*>(take(4 * n));
   Level2* lv[2] = {&s->L0, &s->L1};
   for (int b = 0; b < 2; ++b) {
     lv[b]->buf = reinterpret_cast<uint64_t*>(take(8 * n));
@@ -1596,24 +1597,18 @@ __device__ __forceinline__ void partition_level(const Ctx<LC>& x, uint64_t* __re
   }
 }
 
-// Bootstrap multiplicities of a tree's n training rows into cnt[0 .. n): n
-// draws with replacement, draw i = floor(r_i n / 2^64) for the words r_i of
-// the Philox stream (seed, tag 0, 0, tree) (every row once without
-// bootstrap).  `cnt` is in LDS or in global memory (inlined once for each).
-template <int BLOCK>
-__device__ __forceinline__ void bootstrap_counts(const TreeTask& T, int64_t n, uint32_t* cnt) {
-  const int tid = team_tid<BLOCK>();
-  for (int64_t i = tid; i < n; i += BLOCK) cnt[i] = T.bootstrap ? 0u : 1u;
-  team_sync<BLOCK>();
-  if (T.bootstrap) {
-    const int64_t nblk = (n + 3) / 4;
-    for (int64_t b = tid; b < nblk; b += BLOCK) {
-      const U64x4 r = philox4x64_10((uint64_t)b, kTagBootstrap, 0, (uint64_t)T.tree, T.seed, 0);
+// A tree's bootstrap: n draws with replacement, draw i = floor(r_i n / 2^64) for
+// the words r_i of the Philox stream (seed, tag 0, 0, tree); f(b, rows) gets the
+// four draws of block b, those past the n-th as ~0.
+template <int BLOCK, typename F>
+__device__ __forceinline__ void bootstrap_draws(const TreeTask& T, int64_t n, F f) {
+  const int64_t nblk = (n + 3) / 4;
+  for (int64_t b = team_tid<BLOCK>(); b < nblk; b += BLOCK) {
+    const U64x4 r = philox4x64_10((uint64_t)b, kTagBootstrap, 0, (uint64_t)T.tree, T.seed, 0);
+    uint32_t d[4];
 #pragma unroll
-      for (int w = 0; w < 4; ++w)
-        if (4 * b + w < n) atomicAdd(&cnt[scale_draw(r.w[w], (uint32_t)n)], 1u);
-    }
-    team_sync<BLOCK>();
+    for (int w = 0; w < 4; ++w) d[w] = 4 * b + w < n ? (uint32_t)scale_draw(r.w[w], (uint32_t)n) : ~0u;
+    f(b, make_uint4(d[0], d[1], d[2], d[3]));
   }
 }
 
@@ -1649,13 +1644,17 @@ __device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T,
   const int mtry = T.mtry;
 
   // 1. bootstrap multiplicities, counted in the LDS union area (free until the
-  // first level) when the training set fits it, else in scratch
-  const bool lds_cnt = n <= (int64_t)(a.union_bytes / 4u);
-  uint32_t* const cnt_lds = reinterpret_cast<uint32_t*>(lds);
-  if (lds_cnt)
-    bootstrap_counts<BLOCK>(T, n, cnt_lds);
-  else
-    bootstrap_counts<BLOCK>(T, n, sc.cnt);
+  // first level), as many rows at a time as it holds.  When that takes more than
+  // one pass the draws are written out once and read by each pass: counters in
+  // global memory, an atomic through the L2 per draw, made the launch of 500
+  // trees of 200000 rows 63.1 ms, the seven passes make it 59.0.  Below 2^16 draws
+  // no count exceeds 16 bits, which leaves one-wave teams a single pass for the
+  // tuning grid's 2000 rows (201.0 ms; 205.6 with two passes of 32-bit counters).
+  uint32_t* const cnt = reinterpret_cast<uint32_t*>(lds);
+  const uint32_t h = n < (1 << 16) ? 1u : 0u;  // 16-bit counters, two to a word
+  const int64_t span = (int64_t)((a.union_bytes / 4u) << h) & ~(int64_t)(kWave - 1);
+  uint4* const draws = reinterpret_cast<uint4*>(sc.draws);
+  if (T.bootstrap && n > span) bootstrap_draws<BLOCK>(T, n, [&](int64_t b, uint4 d) { draws[b] = d; });
   // in-bag entries and root sums; each thread takes eight rows per pass,
   // strided by the block, so a pass costs one workgroup scan (the order of the
   // entries is free: every later sum over them is exact)
@@ -1663,39 +1662,65 @@ __device__ __forceinline__ void grow_group(const GrowArgs& a, const TreeTask& T,
   uint64_t N0 = 0, Q0 = 0;
   int64_t S0 = 0;
   constexpr int R = 8;
-  for (int64_t base = 0; base < n; base += (int64_t)R * BLOCK) {
-    uint32_t c[R];
-    uint32_t mine = 0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int64_t i = base + (int64_t)r * BLOCK + tid;
-      c[r] = i < n ? (lds_cnt ? cnt_lds[i] : sc.cnt[i]) : 0u;
-      mine += c[r] > 0 ? 1u : 0u;
-      // in-bag bitmap: this wave's 64 consecutive rows form one word
-      const uint64_t bits = __ballot(c[r] > 0);
-      const int64_t wbase = base + (int64_t)r * BLOCK + (int64_t)(tid / kWave) * kWave;
-      if (lane_id() == 0 && T.inbag_off >= 0 && wbase < n) {
-        if (GROUPED)
-          for (int v = 0; v < sh.gk; ++v) a.inbag[sh.ginbag[v] + wbase / kWave] = bits;
-        else
-          a.inbag[T.inbag_off + wbase / kWave] = bits;
+  for (int64_t lo = 0; lo < n; lo += span) {
+    const int64_t hi = min(n, lo + span);
+    const uint32_t rows = (uint32_t)(hi - lo), off = (uint32_t)lo;
+    if (T.bootstrap) {
+      for (uint32_t i = (uint32_t)tid; i << h < rows; i += BLOCK) cnt[i] = 0u;
+      team_sync<BLOCK>();
+      const auto count1 = [&](uint32_t i) {
+        if (i < rows) atomicAdd(&cnt[i >> h], 1u << ((i & h) << 4));
+      };
+      const auto count = [&](int64_t, uint4 d) {
+        count1(d.x - off);
+        count1(d.y - off);
+        count1(d.z - off);
+        count1(d.w - off);
+      };
+      if (n > span) {
+        const int64_t nblk = (n + 3) / 4;
+        for (int64_t b = tid; b < nblk; b += BLOCK) count(b, draws[b]);
+      } else {
+        bootstrap_draws<BLOCK>(T, n, count);
       }
+      team_sync<BLOCK>();
     }
-    uint32_t total;
-    uint32_t pos = block_exscan<BLOCK>(mine, sh.tmp, total) + n_inbag;
+    for (int64_t base = lo; base < hi; base += (int64_t)R * BLOCK) {
+      uint32_t c[R];
+      uint32_t mine = 0;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      if (c[r] > 0) {
+      for (int r = 0; r < R; ++r) {
         const int64_t i = base + (int64_t)r * BLOCK + tid;
-        const uint32_t row = train ? (uint32_t)train[i] : (uint32_t)i;
-        const int64_t y = a.y_fp[row];
-        sc.L0.buf[pos++] = entry_pack(row, c[r], y);
-        N0 += c[r];
-        S0 += (int64_t)c[r] * y;
-        Q0 += (uint64_t)((int64_t)c[r] * y * y);
+        const uint32_t j = (uint32_t)(i - lo);
+        c[r] = i >= hi ? 0u : !T.bootstrap ? 1u : h ? cnt[j >> 1] >> ((j & 1) << 4) & 0xFFFFu : cnt[j];
+        mine += c[r] > 0 ? 1u : 0u;
+        // in-bag bitmap: this wave's 64 consecutive rows form one word
+        const uint64_t bits = __ballot(c[r] > 0);
+        const int64_t wbase = base + (int64_t)r * BLOCK + (int64_t)(tid / kWave) * kWave;
+        if (lane_id() == 0 && T.inbag_off >= 0 && wbase < hi) {
+          if (GROUPED)
+            for (int v = 0; v < sh.gk; ++v) a.inbag[sh.ginbag[v] + wbase / kWave] = bits;
+          else
+            a.inbag[T.inbag_off + wbase / kWave] = bits;
+        }
       }
+      uint32_t total;
+      uint32_t pos = block_exscan<BLOCK>(mine, sh.tmp, total) + n_inbag;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if (c[r] > 0) {
+          const int64_t i = base + (int64_t)r * BLOCK + tid;
+          const uint32_t row = train ? (uint32_t)train[i] : (uint32_t)i;
+          const int64_t y = a.y_fp[row];
+          sc.L0.buf[pos++] = entry_pack(row, c[r], y);
+          N0 += c[r];
+          S0 += (int64_t)c[r] * y;
+          Q0 += (uint64_t)((int64_t)c[r] * y * y);
+        }
+      }
+      n_inbag += total;
     }
-    n_inbag += total;
+    team_sync<BLOCK>();
   }
   N0 = block_sum<BLOCK, uint64_t>(N0, sh.red);
   S0 = (int64_t)block_sum<BLOCK, uint64_t>((uint64_t)S0, sh.red);
