@@ -55,13 +55,16 @@ GrowConfig grow_config(int64_t n_cap, int64_t n_items, const std::vector<int32_t
   for (int32_t b : n_bins) cfg.bins_max = std::max(cfg.bins_max, b);
   // n_items: the launch's work items (trees, or task groups of a fused fit).
   // Large training sets: 1024 threads per tree, nodes above 512 rows in
-  // workgroup-wide batches (the autotuner's choice on 200000 rows: 63.1 ms
-  // against 66.1 with 512 threads and 63.2 to 70 with other limits).
+  // workgroup-wide batches (500 trees of 200000 rows 60.2 ms, 62.8 with 512
+  // threads, 60.3 to 64.9 with limits of 256 to 2048; up to 65536 rows, 1024: 600
+  // trees of 20000 rows 5.44 ms and 5.58, 256 of 40000 rows 2.08 and 2.17), and as
+  // many columns per large-node task as its area holds: of 256 bins two; of 64 bins
+  // four, 300 trees of 60000 rows 10.4 ms and 10.9 with two.
   const int64_t cus = device_info().cus;
   if (n_cap > 16384) {
     cfg.block = 1024;
-    cfg.huge_min = 512;
-    cfg.big_cols = 2;
+    cfg.huge_min = n_cap > 65536 ? 512 : 1024;
+    cfg.big_cols = 4;
   } else {
     // Smaller ones: no wide batches, and sixteen waves per CU (four per SIMD:
     // 128 registers) shared by as many trees as the launch gives a CU at once: a
