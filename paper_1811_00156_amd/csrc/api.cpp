@@ -815,8 +815,7 @@ int aiwc_rf_predict(const aiwc_rf_forest* f, int32_t forest_index, const uint8_t
     const int32_t nt = f->params[forest_index].num_trees;
     const int64_t t0 = f->first_task[forest_index];
     require_fitted(f);
-    const bool many = predict_route(trees_of(f, forest_index), n, nt) == PredictRoute::kMany;
-    DevBuf<int64_t> sum(many ? (size_t)n : 0, s);
+    DevBuf<int64_t> sum(needs_sums(predict_route(trees_of(f, forest_index), n, nt)) ? (size_t)n : 0, s);
     launch_predict(trees_of(f, forest_index), (int32_t)t0, (int32_t)(t0 + nt), codes, n, f->n_cols, sum.p,
                    y_log10_out, nt, s);
   });
@@ -994,7 +993,7 @@ int aiwc_rf_select_device(const aiwc_rf_forest* f, int32_t forest_index, const u
     const int64_t rows = m * D;
     const PredictRoute route = predict_route(trees_of(f, forest_index), rows, nt);
     DevBuf<uint8_t> expanded(route == PredictRoute::kRow ? 0 : (size_t)(rows * f->n_cols), s);
-    DevBuf<int64_t> sum(route == PredictRoute::kMany ? (size_t)rows : 0, s);
+    DevBuf<int64_t> sum(needs_sums(route) ? (size_t)rows : 0, s);
     DevBuf<double> times_tmp(times_out ? 0 : (size_t)rows, s);
     launch_select_device(trees_of(f, forest_index), (int32_t)t0, (int32_t)(t0 + nt), feature_codes, m, f->n_cols, D,
                          nt, expanded.p, sum.p, times_out ? times_out : times_tmp.p, best_out, s);

@@ -364,9 +364,10 @@ void launch_predict(const TreesView& F, int32_t tree_begin, int32_t tree_end, co
                     int32_t C, int64_t* sum, double* y, int32_t num_trees, hipStream_t s);
 // How a prediction of n rows by n_trees trees runs: a workgroup per row or lanes of
 // a row, which write the answers themselves and need no row sums (`sum` may be
-// null), or staged rows and chunks of trees.  A device selection whose (kernel,
-// device) rows have a workgroup each needs no expanded codes.
-enum class PredictRoute { kRow, kLanes, kMany };
+// null), several workgroups per row, or staged rows and chunks of trees.  A device
+// selection whose (kernel, device) rows have a workgroup each needs no expanded codes.
+enum class PredictRoute { kRow, kLanes, kRowParts, kMany };
+inline bool needs_sums(PredictRoute r) { return r == PredictRoute::kRowParts || r == PredictRoute::kMany; }
 PredictRoute predict_route(const TreesView& F, int64_t n, int32_t n_trees);
 // Lets a kernel take all of the device's LDS as dynamic LDS (set once per device).
 void allow_lds(const void* kernel);

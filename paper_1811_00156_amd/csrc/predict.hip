@@ -117,12 +117,15 @@ __global__ __launch_bounds__(kPredBlock) void k_traverse(TreesView F, int32_t tr
 // fetched together as soon as the node is known, while its column's code is
 // looked up: a level costs one memory latency.  With D > 0 the rows are the
 // (kernel, device) pairs of a device selection: row r has kernel r / D's C - 1
-// feature codes and the device code r % D.
+// feature codes and the device code r % D.  A thread walks K trees at a time; when
+// gridDim.y workgroups share a row its trees are dealt out among them, and their
+// sums meet in sum[r], which starts at 0.
 constexpr int kRowBlock = 512;
 struct alignas(8) NodePair {
   uint64_t l, r;
 };
 
+template <int K>
 __global__ __launch_bounds__(kRowBlock) void k_traverse_row(TreesView F, int32_t tree_begin, int32_t tree_end,
                                                             const uint8_t* __restrict__ codes, int32_t C, int32_t D,
                                                             unsigned long long* __restrict__ sum,
@@ -131,7 +134,6 @@ __global__ __launch_bounds__(kRowBlock) void k_traverse_row(TreesView F, int32_t
   __shared__ int64_t part[kRowBlock / kWave];
   const int64_t r = blockIdx.x;
   const int32_t tid = (int32_t)threadIdx.x;
-  constexpr int K = 2;
   int64_t acc = 0;
   const uint64_t* tn[K];
   uint64_t v[K];
@@ -143,7 +145,7 @@ __global__ __launch_bounds__(kRowBlock) void k_traverse_row(TreesView F, int32_t
       v[k] = in ? tn[k][0] : (uint64_t)kLeafCol;
     }
   };
-  int32_t t = tree_begin + tid;
+  int32_t t = tree_begin + (int32_t)blockIdx.y * (K * kRowBlock) + tid;
   open_trees(t);
   if (tid < C) {
     if (D > 0)
@@ -168,7 +170,7 @@ __global__ __launch_bounds__(kRowBlock) void k_traverse_row(TreesView F, int32_t
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) acc += node_q(v[k]);
-    t += K * kRowBlock;
+    t += K * kRowBlock * (int32_t)gridDim.y;
     open_trees(t);
   }
   acc = (int64_t)wave_sum((uint64_t)acc);
@@ -177,8 +179,12 @@ __global__ __launch_bounds__(kRowBlock) void k_traverse_row(TreesView F, int32_t
   if (tid == 0) {
     int64_t s = 0;
     for (int w = 0; w < kRowBlock / kWave; ++w) s += part[w];
-    if (sum) sum[r] = (unsigned long long)s;
-    if (y) y[r] = ((double)s * 0x1p-32) / trees;
+    if (gridDim.y > 1) {
+      atomicAdd(&sum[r], (unsigned long long)s);
+    } else {
+      if (sum) sum[r] = (unsigned long long)s;
+      if (y) y[r] = ((double)s * 0x1p-32) / trees;
+    }
   }
 }
 
@@ -304,30 +310,62 @@ void launch_rank_accuracy(const double* times, const double* truth, int64_t m, i
 // By (row, tree) pairs, and the size of the trees, from which the reads that share
 // no cache line cost more.  A workgroup per row reads another tree with every
 // lane, one launch: 60 rows x 505 trees of 2220 training rows 9 us against 25
-// with the rows staged, 512 rows 17 and 25, 1024 rows 31 and 25; trees of 200000:
-// 256 rows 32 and 36, 512 rows 53 and 42.  Few trees take lanes of a row, also one
-// launch: 10000 rows x 16 trees of 2220 rows 11 us and 19, 50000 rows 26 and 30,
-// 200000 rows 80 and 57; 2000 rows x 250 trees 22 and 25, 4096 rows 39 and 31; 16
-// trees of 30000: 10000 rows 14 and 24, 50000 rows 42 and 37; of 200000: 10000 rows
-// 16 and 24; 64 trees, 1000 rows 18 and 23, 4096 rows 27 and 26.
+// with the rows staged, 512 rows 17 and 25, 1000 rows x 130 trees of 30000 28 and
+// 40, x 250 trees of 12000 37 and 35; trees of 200000: 256 rows 32 and 36, 512 rows
+// 53 and 42.  More trees than it walks at once, or large ones, are more than one CU
+// fetches soon: several workgroups share the row, two launches more (1600 trees of
+// 2220 rows: 1 row 41 us by one workgroup, 16 by several, 26 with the rows staged;
+// 150 rows 53, 43, 45; 250 rows 58, 56, 47; 700 trees of 60000: 60 rows 43, 36, 46;
+// 250 rows 61, 64, 55).  Few trees take lanes of a row, also one
+// launch: 10000 rows x 16 trees of 2220 rows 11 us and 19, 20000 x 30 trees of 1000
+// 26 and 35, 40000 45 and 40, x 40 trees of 100 rows 41 and 42; 2000 rows x 250
+// trees 22 and 25, 4096 rows 39 and 31; 16 trees of 30000: 10000 rows 14 and 24,
+// 50000 rows 42 and 37; of 200000: 10000 rows 16 and 24; 64 trees, 1000 rows 18 and
+// 23, 4096 rows 27 and 26.
 PredictRoute predict_route(const TreesView& F, int64_t n, int32_t n_trees) {
   const int64_t pairs = n * n_trees, r = F.train_rows;
-  if (n <= 1024 && pairs <= (r <= 100000 ? (int64_t)5 << 16 : (int64_t)1 << 17)) return PredictRoute::kRow;
-  const int64_t lanes = r <= 4096 ? (int64_t)1 << (n_trees <= 64 ? 20 : 19)
+  const bool small = r <= 8192;
+  if (n <= 1024 && n_trees <= (small ? 2 * kRowBlock : kRowBlock)) {
+    if (pairs <= (small ? (int64_t)5 << 16 : (int64_t)1 << 17)) return PredictRoute::kRow;
+  } else if (pairs <= (small ? (int64_t)1 << 18 : (int64_t)1 << 17) && n_trees > kRowBlock) {
+    return PredictRoute::kRowParts;
+  }
+  const int64_t lanes = r <= 4096 ? (n_trees > 64 ? (int64_t)1 << 19 : r <= 256 ? (int64_t)3 << 19 : (int64_t)3 << 18)
                         : (r <= 100000 && n_trees <= 64) || n_trees <= 16 ? (int64_t)1 << 18
                                                                           : (int64_t)1 << 17;
   if (n_trees <= (r <= 4096 ? 512 : 128) && pairs <= lanes) return PredictRoute::kLanes;
   return PredictRoute::kMany;
 }
 
+namespace {
+void launch_row(const TreesView& F, int32_t tree_begin, int32_t tree_end, const uint8_t* codes, int64_t n, int32_t C,
+                int32_t D, int64_t* sum, double* y, int32_t num_trees, int32_t parts, hipStream_t s) {
+  const auto k = parts > 1 ? k_traverse_row<1> : k_traverse_row<2>;
+  k<<<dim3((unsigned)n, (unsigned)parts), kRowBlock, 0, s>>>(F, tree_begin, tree_end, codes, C, D,
+                                                             reinterpret_cast<unsigned long long*>(sum), y,
+                                                             (double)num_trees);
+  AIWC_HIP(hipGetLastError());
+}
+
+void zero_sums(int64_t* sum, int64_t n, hipStream_t s) {
+  const int zb = (int)std::min<int64_t>(1024, (n + 255) / 256);
+  k_zero_i64<<<zb, 256, 0, s>>>(reinterpret_cast<unsigned long long*>(sum), n);
+  AIWC_HIP(hipGetLastError());
+}
+
+void finalize_sums(const int64_t* sum, int64_t n, int32_t num_trees, double* y, hipStream_t s) {
+  const int fb = (int)std::min<int64_t>(1024, (n + 255) / 256);
+  k_finalize<<<fb, 256, 0, s>>>(sum, n, (double)num_trees, y);
+  AIWC_HIP(hipGetLastError());
+}
+}  // namespace
+
 void launch_select_device(const TreesView& F, int32_t tree_begin, int32_t tree_end, const uint8_t* feature_codes,
                           int64_t m, int32_t C, int32_t n_devices, int32_t num_trees, uint8_t* expanded, int64_t* sum,
                           double* times, int32_t* best, hipStream_t s) {
   const int64_t rows = m * n_devices;
   if (predict_route(F, rows, tree_end - tree_begin) == PredictRoute::kRow) {
-    k_traverse_row<<<(unsigned)rows, kRowBlock, 0, s>>>(F, tree_begin, tree_end, feature_codes, C, n_devices, nullptr,
-                                                        times, (double)num_trees);
-    AIWC_HIP(hipGetLastError());
+    launch_row(F, tree_begin, tree_end, feature_codes, rows, C, n_devices, nullptr, times, num_trees, 1, s);
   } else {
     const int eb = (int)std::max<int64_t>(1, std::min<int64_t>(4096, (rows * C + 255) / 256));
     k_expand_devices<<<eb, 256, 0, s>>>(feature_codes, m, C, n_devices, expanded);
@@ -399,21 +437,13 @@ void traverse_many(const TreesView& F, int32_t tree_begin, int32_t tree_end, con
   const int32_t chunk = (T + n_chunks - 1) / n_chunks;
   if (n_chunks % 8 != 0) n_chunks = (T + chunk - 1) / chunk;
   const int accumulate = n_chunks > 1 ? 1 : 0;
-  if (accumulate) {
-    const int zb = (int)std::min<int64_t>(1024, (n + 255) / 256);
-    k_zero_i64<<<zb, 256, 0, s>>>(reinterpret_cast<unsigned long long*>(sum), n);
-    AIWC_HIP(hipGetLastError());
-  }
+  if (accumulate) zero_sums(sum, n, s);
   if (lds > 65536) allow_lds(reinterpret_cast<const void*>(k_traverse<TP, G>));
   k_traverse<TP, G><<<(unsigned)(n_rb * n_chunks), kPredBlock, lds, s>>>(
       F, tree_begin, tree_end, chunk, n_chunks, (int32_t)n_rb, R, codes, n, C,
       reinterpret_cast<unsigned long long*>(sum), y, (double)num_trees, accumulate);
   AIWC_HIP(hipGetLastError());
-  if (accumulate && y) {
-    const int fb = (int)std::min<int64_t>(1024, (n + 255) / 256);
-    k_finalize<<<fb, 256, 0, s>>>(sum, n, (double)num_trees, y);
-    AIWC_HIP(hipGetLastError());
-  }
+  if (accumulate && y) finalize_sums(sum, n, num_trees, y, s);
 }
 
 }  // namespace
@@ -423,9 +453,14 @@ void launch_predict(const TreesView& F, int32_t tree_begin, int32_t tree_end, co
   if (n <= 0) return;
   const PredictRoute route = predict_route(F, n, tree_end - tree_begin);
   if (route == PredictRoute::kRow) {
-    k_traverse_row<<<(unsigned)n, kRowBlock, 0, s>>>(F, tree_begin, tree_end, codes, C, 0,
-                                                     reinterpret_cast<unsigned long long*>(sum), y, (double)num_trees);
-    AIWC_HIP(hipGetLastError());
+    launch_row(F, tree_begin, tree_end, codes, n, C, 0, sum, y, num_trees, 1, s);
+    return;
+  }
+  if (route == PredictRoute::kRowParts) {
+    zero_sums(sum, n, s);
+    launch_row(F, tree_begin, tree_end, codes, n, C, 0, sum, nullptr, num_trees,
+               (tree_end - tree_begin + kRowBlock - 1) / kRowBlock, s);
+    if (y) finalize_sums(sum, n, num_trees, y, s);
     return;
   }
   if (route == PredictRoute::kLanes) {

@@ -32,14 +32,14 @@ def _fitted(rf, oracle, C, n, trees, bins, seed, mtry=None):
 
 
 # rows x trees on both sides of the limits of a workgroup per row (1024 rows, 5 x
-# 2^16 pairs) and of lanes per row (2^20 pairs, 2^19 above 64 trees, none above
-# 512), whole and broken workgroups of 256 rows, one chunk of trees and many,
+# 2^16 pairs), of several (above 1024 trees, 2^18 pairs) and of lanes per row (3 x
+# 2^18 pairs, 2^19 above 64 trees, none above 512), whole and broken workgroups of 256 rows, one chunk of trees and many,
 # trees in and out of fours; columns with even and odd row strides, and the
 # widest row (255 columns)
 @pytest.mark.parametrize("C,trees,rows", [
-    (2, 1, (1, 1024, 1025, 1280)), (35, 9, (1, 255, 1023, 1024, 1025, 5000, 116508, 116509)),
-    (64, 300, (3, 1000, 1092, 1093, 4097)), (65, 1030, (1, 318, 319, 513)), (255, 20, (7, 1024, 1025, 52429)),
-    (12, 64, (1025, 16384, 16385)), (7, 65, (1025, 8065, 8066)), (5, 512, (1024, 1025)), (5, 513, (1025, 2049)),
+    (2, 1, (1, 1024, 1025, 1280)), (35, 9, (1, 255, 1023, 1024, 1025, 5000, 87381, 87382)),
+    (64, 300, (3, 1000, 1092, 1093, 4097)), (65, 1030, (1, 254, 255, 513)), (255, 20, (7, 1024, 1025, 39322)),
+    (12, 64, (1025, 12288, 12289)), (9, 1024, (1, 320, 321)), (9, 2100, (1, 124, 125)), (7, 65, (1025, 8065, 8066)), (5, 512, (1024, 1025)), (5, 513, (1025, 2049)),
 ])
 def test_predict_paths(rf, oracle, C, trees, rows):
     import torch
@@ -64,17 +64,17 @@ def test_predict_paths(rf, oracle, C, trees, rows):
 
 
 # (kernel, device) rows below and above the per-row kernel's limit
-@pytest.mark.parametrize("D,m", [(1, 5), (15, 4), (15, 68), (15, 69), (32, 100)])
-def test_select_paths(rf, oracle, D, m):
-    log(f"select paths D={D} m={m}")
+@pytest.mark.parametrize("D,m,trees", [(1, 5, 30), (15, 4, 30), (15, 68, 30), (15, 69, 30), (32, 100, 30), (15, 4, 1100)])
+def test_select_paths(rf, oracle, D, m, trees):
+    log(f"select paths D={D} m={m} trees={trees}")
     rng = np.random.default_rng(D + m)
     n, C = 600, 12
     codes = rng.integers(0, 40, (n, C)).astype(np.uint8)
     codes[:, -1] = rng.integers(0, D, n)
     nb = np.array([40] * (C - 1) + [D], np.int32)
     y = rng.normal(0.0, 1.0, n)
-    forest = rf.aiwc_rf_fit(to_dev(codes), rf.aiwc_rf_binner_from_counts(nb), to_dev(y), rf.make_params(30, 5, 3, True, 4))
-    of = oracle.fit(codes, nb, y, 30, 5, 3, seed=4)
+    forest = rf.aiwc_rf_fit(to_dev(codes), rf.aiwc_rf_binner_from_counts(nb), to_dev(y), rf.make_params(trees, 5, 3, True, 4))
+    of = oracle.fit(codes, nb, y, trees, 5, 3, seed=4)
     feat = rng.integers(0, 40, (m, C - 1)).astype(np.uint8)
     best, times = rf.aiwc_rf_select_device(forest, to_dev(feat), n_devices=D)
     rows = np.concatenate([np.repeat(feat, D, axis=0), np.tile(np.arange(D, dtype=np.uint8), m)[:, None]], axis=1)
