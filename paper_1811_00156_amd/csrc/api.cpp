@@ -737,9 +737,10 @@ int aiwc_rf_forest_export_host(const aiwc_rf_forest* f, int32_t forest_index, in
     AIWC_HIP(hipMemcpy(nn.data(), f->n_nodes.p + t0 + tree_begin, sizeof(int32_t) * nn.size(), hipMemcpyDeviceToHost));
     int64_t all = 0;
     for (int32_t v : nn) all += v;
-    if (nn.size() <= 4 && all <= 16384) {
-      // a tree's words and weights taken as they are (one tree 66 us, by the
-      // slices below 144; four trees about as long either way)
+    if (nn.size() == 1 || all <= (nn.size() == 2 ? 49152 : nn.size() <= 4 ? 16384 : 0)) {
+      // a tree's words and weights taken as they are (one tree 66 us, by the slices
+      // below 144, of 27000 nodes 105 and 143; two of 12000 118 and 141, of 27000
+      // equal; three of 12000 154 and 150, of 2000 nodes about as long either way)
       std::vector<uint64_t> words;
       std::vector<uint32_t> N;
       size_t out = 0;
