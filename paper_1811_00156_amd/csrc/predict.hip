@@ -318,7 +318,8 @@ void launch_rank_accuracy(const double* times, const double* truth, int64_t m, i
 // 150 rows 53, 43, 45; 250 rows 58, 56, 47; 700 trees of 60000: 60 rows 43, 36, 46;
 // 250 rows 61, 64, 55).  Few trees take lanes of a row, also one
 // launch: 10000 rows x 16 trees of 2220 rows 11 us and 19, 20000 x 30 trees of 1000
-// 26 and 35, 40000 45 and 40, x 40 trees of 100 rows 41 and 42; 2000 rows x 250
+// 26 and 35, 40000 45 and 40, x 40 trees of 100 rows 41 and 42, 8000 x 122 of 77 rows
+// 21 and 27; 3000 x 120 of 1000 rows 19 and 33, 8000 50 and 37; 2000 rows x 250
 // trees 22 and 25, 4096 rows 39 and 31; 16 trees of 30000: 10000 rows 14 and 24,
 // 50000 rows 42 and 37; of 200000: 10000 rows 16 and 24; 64 trees, 1000 rows 18 and
 // 23, 4096 rows 27 and 26.
@@ -330,7 +331,10 @@ PredictRoute predict_route(const TreesView& F, int64_t n, int32_t n_trees) {
   } else if (pairs <= (small ? (int64_t)1 << 18 : (int64_t)1 << 17) && n_trees > kRowBlock) {
     return PredictRoute::kRowParts;
   }
-  const int64_t lanes = r <= 4096 ? (n_trees > 64 ? (int64_t)1 << 19 : r <= 256 ? (int64_t)3 << 19 : (int64_t)3 << 18)
+  const int64_t lanes = r <= 256    ? (int64_t)3 << 19
+                        : r <= 4096 ? (n_trees <= 64  ? (int64_t)3 << 18
+                                       : r <= 1024    ? (int64_t)5 << 17
+                                                      : (int64_t)1 << 19)
                         : (r <= 100000 && n_trees <= 64) || n_trees <= 16 ? (int64_t)1 << 18
                                                                           : (int64_t)1 << 17;
   if (n_trees <= (r <= 4096 ? 512 : 128) && pairs <= lanes) return PredictRoute::kLanes;
