@@ -48,12 +48,13 @@ int32_t status_to_code(uint32_t st, std::string& msg) {
 }
 
 GrowConfig grow_config(int64_t n_cap, int64_t n_items, const std::vector<int32_t>& n_bins, int32_t mtry_max,
-                       int64_t n) {
+                       int64_t n, bool shared) {
   GrowConfig cfg;
   cfg.n_cap = n_cap;
   cfg.bins_max = 1;
   for (int32_t b : n_bins) cfg.bins_max = std::max(cfg.bins_max, b);
-  // n_items: the launch's work items (trees, or task groups of a fused fit).
+  // n_items: the launch's work items (trees, or task groups of a fused fit; shared:
+  // some groups hold several trees).
   // Large training sets: 1024 threads per tree, nodes above 512 rows in
   // workgroup-wide batches (500 trees of 200000 rows 60.2 ms, 62.8 with 512
   // threads, 60.3 to 64.9 with limits of 256 to 2048; up to 65536 rows, 1024: 600
@@ -77,7 +78,9 @@ GrowConfig grow_config(int64_t n_cap, int64_t n_items, const std::vector<int32_t
     // Deep queues without teams (the code matrix does not fit): 6000 rows, 8000
     // trees 16.4 with 128 threads, 16.5 with 256, 20.3 with 64; 15000 rows 57.6,
     // 53.2 and 68.9.  Up to 1024 rows a tree does not fill sixteen waves (300 rows:
-    // 0.22 and 0.21 with 512).  A large-node task takes four candidate columns,
+    // 0.22 and 0.21 with 512), nor up to 4096 the members of a group, which grow one
+    // after the other the levels of small nodes only (132 groups of five, 2220 rows:
+    // 1.61 with 512, 1.66 with 1024; 128 of 6000 rows 2.54 and 2.43).  A large-node task takes four candidate columns,
     // two while sixteen waves share one tree's.
     cfg.huge_min = 16384;
     cfg.occupancy = 4;
@@ -85,7 +88,7 @@ GrowConfig grow_config(int64_t n_cap, int64_t n_items, const std::vector<int32_t
     GrowConfig team = cfg;
     team.block = 64;
     team.occupancy = 5;
-    if (n_items <= cus && n_cap > 1024) {
+    if (n_items <= cus && n_cap > (shared ? 4096 : 1024)) {
       cfg.block = 1024;
       cfg.big_cols = 2;
     } else if (n_items <= 2 * cus) {
@@ -492,7 +495,7 @@ void fit_common(const uint8_t* codes, int64_t n, int32_t n_cols, const aiwc_rf_b
     n_items = 0;
     for (int32_t f = 0; f < n_forests; ++f) n_items = std::max<int64_t>(n_items, params_host[f].num_trees);
   }
-  GrowConfig cfg = grow_config(n_cap, n_items, binner->n_bins, mtry_max, n);
+  GrowConfig cfg = grow_config(n_cap, n_items, binner->n_bins, mtry_max, n, n_groups < n_tasks);
   bool tuned = false;
   if (flags & AIWC_RF_FIT_TUNE) {
     cfg = tune_grow(cfg, n_items, n_cols, mtry_max, F.get(), codes, n, binner, y_log10, y_fp.p, codes_p.p, d_train.p,
