@@ -136,7 +136,7 @@ void aiwc_rf_binner_free(aiwc_rf_binner* binner);
                                 the choice is cached per problem shape (and in the file named by
                                 AIWC_RF_TUNE_CACHE, if set); results never depend on it.
                                 Without it the shape follows the problem size; the environment
-                                variables AIWC_RF_GROW_BLOCK (192, 256, 512 or 1024 threads),
+                                variables AIWC_RF_GROW_BLOCK (64 to 1024 threads),
                                 AIWC_RF_HUGE_MIN (rows above which a node is searched by the
                                 whole workgroup), AIWC_RF_GROW_OCC (4, 5 or 6 waves per SIMD),
                                 AIWC_RF_GROW_WG_PER_CU and AIWC_RF_BIG_COLS (1 to 4 columns per
