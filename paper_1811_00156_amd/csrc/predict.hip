@@ -317,12 +317,12 @@ void launch_rank_accuracy(const double* times, const double* truth, int64_t m, i
 // 2220 rows: 1 row 41 us by one workgroup, 16 by several, 26 with the rows staged;
 // 150 rows 53, 43, 45; 250 rows 58, 56, 47; 700 trees of 60000: 60 rows 43, 36, 46;
 // 250 rows 61, 64, 55).  Few trees take lanes of a row, also one
-// launch: 10000 rows x 16 trees of 2220 rows 11 us and 19, 20000 x 30 trees of 1000
-// 26 and 35, 40000 45 and 40, x 40 trees of 100 rows 41 and 42, 8000 x 122 of 77 rows
-// 21 and 27; 3000 x 120 of 1000 rows 19 and 33, 8000 50 and 37; 2000 rows x 250
-// trees 22 and 25, 4096 rows 39 and 31; 16 trees of 30000: 10000 rows 14 and 24,
-// 50000 rows 42 and 37; of 200000: 10000 rows 16 and 24; 64 trees, 1000 rows 18 and
-// 23, 4096 rows 27 and 26.
+// launch: 8000 rows x 60 trees of 300 training rows 18 us against 25, 9030 x 71 28 and
+// 35, 16000 x 60 33 and 31; 4000 x 200 trees of 100 rows 19 and 27, 8000 39 and 32; 4000 x 120 trees of
+// 1000 25 and 27, 8000 49 and 34, 1100 x 300 31 and 25; 16000 x 30 trees of 2220 23
+// and 27, 8000 x 60 28 and 27, 1100 x 300 54 and 27; 4000 x 64 trees of 8000 22 and 24,
+// 8000 43 and 30; 1100 x 64 trees of 30000 22 and 21; 10000 x 16 trees of 200000 16
+// and 24, 16000 x 16 of 100000 31 and 28.
 PredictRoute predict_route(const TreesView& F, int64_t n, int32_t n_trees) {
   const int64_t pairs = n * n_trees, r = F.train_rows;
   const bool small = r <= 8192;
@@ -331,13 +331,14 @@ PredictRoute predict_route(const TreesView& F, int64_t n, int32_t n_trees) {
   } else if (pairs <= (small ? (int64_t)1 << 18 : (int64_t)1 << 17) && n_trees > kRowBlock) {
     return PredictRoute::kRowParts;
   }
-  const int64_t lanes = r <= 256    ? (int64_t)3 << 19
-                        : r <= 4096 ? (n_trees <= 64  ? (int64_t)3 << 18
-                                       : r <= 1024    ? (int64_t)5 << 17
-                                                      : (int64_t)1 << 19)
-                        : (r <= 100000 && n_trees <= 64) || n_trees <= 16 ? (int64_t)1 << 18
-                                                                          : (int64_t)1 << 17;
-  if (n_trees <= (r <= 4096 ? 512 : 128) && pairs <= lanes) return PredictRoute::kLanes;
+  const int64_t lanes = r <= 256                                    ? (int64_t)5 << 18
+                        : r <= 512                                  ? (int64_t)5 << 17
+                        : r <= 1024 || (r <= 4096 && n_trees <= 32) ? (int64_t)1 << 19
+                        : r <= 4096                                 ? (int64_t)3 << 17
+                        : r <= 16384                                ? (int64_t)1 << 18
+                                                                    : (int64_t)3 << 16;
+  const int32_t most = r <= 256 ? 512 : r <= 4096 ? 128 : r <= 16384 ? 64 : 16;
+  if (n_trees <= most && pairs <= lanes) return PredictRoute::kLanes;
   return PredictRoute::kMany;
 }
 
@@ -482,8 +483,10 @@ void launch_predict(const TreesView& F, int32_t tree_begin, int32_t tree_end, co
   // Small trees are walked four at a time: a barrier per tree and a short walk
   // leave little to overlap (200000 rows x 250 trees of 300 training rows: 651 us
   // one at a time, 500 four; of 2220 rows 567 and 504; of 30000, which share the
-  // L2, 924 and 1141).
-  if (F.train_rows <= 8192)
+  // L2, 924 and 1141), but for few pairs one at a time leaves more workgroups
+  // (3000 rows x 175 trees of 7669 rows 28 us, 34 four; 6000 x 200 of 3500 37 and
+  // 41; 6000 x 300 of 2220 46 and 45).
+  if (F.train_rows <= 8192 && n * (tree_end - tree_begin) > (int64_t)1 << 20)
     traverse_many<1, 4>(F, tree_begin, tree_end, codes, n, C, sum, y, num_trees, s);
   else if (F.train_rows <= 100000)
     traverse_many<1, 1>(F, tree_begin, tree_end, codes, n, C, sum, y, num_trees, s);

@@ -32,14 +32,14 @@ def _fitted(rf, oracle, C, n, trees, bins, seed, mtry=None):
 
 
 # rows x trees on both sides of the limits of a workgroup per row (1024 rows, 5 x
-# 2^16 pairs), of several (above 1024 trees, 2^18 pairs) and of lanes per row (3 x
-# 2^18 pairs, 5 x 2^17 above 64 trees, none above 512), whole and broken workgroups of 256 rows, one chunk of trees and many,
-# trees in and out of fours; columns with even and odd row strides, and the
-# widest row (255 columns)
+# 2^16 pairs), of several (above 1024 trees, 2^18 pairs), of lanes per row (2^19
+# pairs, up to 128 trees) and of trees walked one at a time (2^20 pairs), whole and
+# broken workgroups of 256 rows, one chunk of trees and many, trees in and out of
+# fours; columns with even and odd row strides, and the widest row (255 columns)
 @pytest.mark.parametrize("C,trees,rows", [
-    (2, 1, (1, 1024, 1025, 1280)), (35, 9, (1, 255, 1023, 1024, 1025, 5000, 87381, 87382)),
-    (64, 300, (3, 1000, 1092, 1093, 4097)), (65, 1030, (1, 254, 255, 513)), (255, 20, (7, 1024, 1025, 39322)),
-    (12, 64, (1025, 12288, 12289)), (9, 1024, (1, 320, 321)), (9, 2100, (1, 124, 125)), (7, 65, (1025, 10082, 10083)), (5, 512, (1024, 1025)), (5, 513, (1025, 2049)),
+    (2, 1, (1, 1024, 1025, 1280)), (35, 9, (1, 255, 1023, 1024, 1025, 5000, 58254, 58255)),
+    (64, 300, (3, 1000, 1092, 1093, 3495, 3496, 4097)), (65, 1030, (1, 254, 255, 513)), (255, 20, (7, 1024, 1025, 26215)),
+    (12, 64, (1025, 8192, 8193)), (9, 1024, (1, 320, 321)), (9, 2100, (1, 124, 125)), (7, 128, (1025, 4096, 4097)), (7, 129, (1025, 4064)), (5, 512, (1024, 1025)), (5, 513, (1025, 2049)),
 ])
 def test_predict_paths(rf, oracle, C, trees, rows):
     import torch
