@@ -101,12 +101,16 @@ GrowConfig grow_config(int64_t n_cap, int64_t n_items, const std::vector<int32_t
       cfg.block = n_cap > 8192 ? 256 : 128;
     }
   }
-  if (const char* e = std::getenv("AIWC_RF_GROW_BLOCK")) cfg.block = std::atoi(e);
+  const char* block = std::getenv("AIWC_RF_GROW_BLOCK");
+  if (block) cfg.block = std::atoi(block);
   if (const char* e = std::getenv("AIWC_RF_GROW_WG_PER_CU")) cfg.wg_per_cu = std::atoi(e);
   if (const char* e = std::getenv("AIWC_RF_HUGE_MIN")) cfg.huge_min = std::atoi(e);
   if (const char* e = std::getenv("AIWC_RF_GROW_OCC")) cfg.occupancy = std::atoi(e);
   if (const char* e = std::getenv("AIWC_RF_BIG_COLS")) cfg.big_cols = std::atoi(e);
   if (const char* e = std::getenv("AIWC_RF_WIDE_SUMS")) cfg.wide_sums = std::atoi(e) != 0;
+  // workgroups of one or two waves have no wide phase: where the limit alone asks for
+  // it, the default shape is the smallest that has it
+  if (!block && grow_has_wide_phase(cfg)) cfg.block = std::max(cfg.block, 192);
   return cfg;
 }
 

@@ -290,3 +290,28 @@ def test_small_node_sums_wide_responses(setup, bins, block, occ):
     log(f"wide responses bins={bins} block={block}")
     for t, tree in enumerate(f.export()):
         assert_tree_equal(tree, ofb.tree(t), f"wide responses bins {bins} block {block} tree {t}")
+
+
+@pytest.mark.parametrize("trees", [1, 400, 800, 1100, 3700, 16500])
+@pytest.mark.parametrize("huge_min", ["90", "150"])
+def test_wide_limit_alone(oracle, trees, huge_min):
+    """A wide limit below the training set, with the workgroup size left to the
+    default, is taken whatever the number of trees."""
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1811_00156_amd import rf
+
+    log(f"wide limit {huge_min} alone, {trees} trees")
+    ds = synth.small(n_vec=50, n_devices=4, p_ln=3, p_u=2, seed=5)  # 200 rows
+    ob = oracle.bin(ds.X, ds.device, ds.n_devices, 32)
+    # (a forest has at most 16384 trees: beyond that a grid of two)
+    params = [rf.make_params(-(-trees // 2), m, 4, True, 9) for m in (3, 2)] if trees > 16384 else \
+        rf.make_params(trees, 3, 4, True, 9)
+    f = fit_with(rf, ds, ob, {"AIWC_RF_HUGE_MIN": huge_min}, params=params)
+    li = f.launch()
+    assert li["wide_phase"] == 1 and li["wide_limit"] == int(huge_min) and li["block"] >= 192
+    of = oracle.fit(ob.codes, ob.n_bins, ds.y, min(trees, 4), 3, 4, seed=9)
+    for t, tree in enumerate(f.export(0, 0, min(trees, 4))):
+        assert_tree_equal(tree, of.tree(t), f"tree {t}")
