@@ -744,16 +744,14 @@ int aiwc_rf_forest_export_host(const aiwc_rf_forest* f, int32_t forest_index, in
     AIWC_HIP(hipMemcpy(nn.data(), f->n_nodes.p + t0 + tree_begin, sizeof(int32_t) * nn.size(), hipMemcpyDeviceToHost));
     int64_t all = 0;
     for (int32_t v : nn) all += v;
-    if (nn.size() == 1 || all <= (nn.size() == 2 ? 49152 : nn.size() <= 4 ? 16384 : 0)) {
-      // a tree's words and weights taken as they are (one tree 66 us, by the slices
-      // below 144, of 27000 nodes 105 and 143; two of 12000 118 and 141, of 27000
-      // equal; three of 12000 154 and 150, of 2000 nodes about as long either way)
+    // trees [a, e) of nn to the host arrays from node `out` on, their words and
+    // weights taken as they are
+    auto take_trees = [&](int32_t a, int32_t e, int64_t out) {
       std::vector<uint64_t> words;
       std::vector<uint32_t> N;
-      size_t out = 0;
-      for (int32_t t = tree_begin; t < tree_end; ++t) {
-        const size_t cnt = (size_t)nn[t - tree_begin];
-        const int64_t base = f->tasks[t0 + t].node_base;
+      for (int32_t t = a; t < e; ++t) {
+        const size_t cnt = (size_t)nn[t];
+        const int64_t base = f->tasks[t0 + tree_begin + t].node_base;
         words.resize(cnt);
         N.resize(cnt);
         AIWC_HIP(hipMemcpy(words.data(), f->nodes.p + base, sizeof(uint64_t) * cnt, hipMemcpyDeviceToHost));
@@ -768,10 +766,17 @@ int aiwc_rf_forest_export_host(const aiwc_rf_forest* f, int32_t forest_index, in
           if (N_host) N_host[out] = (int32_t)N[i];
         }
       }
+    };
+    if (nn.size() == 1 || all <= (nn.size() == 2 ? 49152 : nn.size() <= 4 ? 16384 : 0)) {
+      // (one tree 66 us, by the slices below 144, of 27000 nodes 105 and 143; two of
+      // 12000 118 and 141, of 27000 equal; three of 12000 154 and 150, of 2000 nodes
+      // about as long either way)
+      take_trees(0, (int32_t)nn.size(), 0);
       return;
     }
     // slices of whole trees, of at most 2^20 nodes (18 MiB of device memory) where
-    // a tree is not larger, unpacked on the forest's device
+    // a tree is not larger, unpacked on the forest's device; a slice that finds no
+    // device memory is taken tree by tree, which needs none
     constexpr int64_t kSlice = int64_t(1) << 20;
     const OnDevice on(f->device);
     int64_t out = 0;
@@ -780,10 +785,26 @@ int aiwc_rf_forest_export_host(const aiwc_rf_forest* f, int32_t forest_index, in
       for (e = a; e < (int32_t)nn.size() && (e == a || off.back() + nn[e] <= kSlice); ++e)
         off.push_back(off.back() + nn[e]);
       const size_t cnt = (size_t)off.back();
-      DevBuf<int64_t> d_off(off.size(), nullptr);
-      DevBuf<uint8_t> col(col_host ? cnt : 0, nullptr), bin(bin_host ? cnt : 0, nullptr);
-      DevBuf<int32_t> left(left_host ? cnt : 0, nullptr), N(N_host ? cnt : 0, nullptr);
-      DevBuf<int64_t> q(q_host ? cnt : 0, nullptr);
+      DevBuf<int64_t> d_off, q;
+      DevBuf<uint8_t> col, bin;
+      DevBuf<int32_t> left, N;
+      bool room = true;
+      try {
+        d_off.reset(off.size(), nullptr);
+        col.reset(col_host ? cnt : 0, nullptr);
+        bin.reset(bin_host ? cnt : 0, nullptr);
+        left.reset(left_host ? cnt : 0, nullptr);
+        q.reset(q_host ? cnt : 0, nullptr);
+        N.reset(N_host ? cnt : 0, nullptr);
+      } catch (const Error& err) {
+        if (err.code != AIWC_RF_ENOMEM) throw;
+        room = false;
+      }
+      if (!room) {
+        take_trees(a, e, out);
+        out += (int64_t)cnt;
+        continue;
+      }
       AIWC_HIP(hipMemcpy(d_off.p, off.data(), sizeof(int64_t) * off.size(), hipMemcpyHostToDevice));
       launch_unpack(f->nodes.p, f->node_N.p, f->node_base.p + t0 + tree_begin + a, d_off.p, e - a, col.p, bin.p, left.p,
                     q.p, N.p, nullptr);
