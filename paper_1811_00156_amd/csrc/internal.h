@@ -331,6 +331,15 @@ struct OobForest {
   int64_t train_off;  // -1 = rows 0 .. n_train-1
   int64_t row_off;    // first slot of this forest's rows in the per-row outputs
 };
+// How the scores of n_forests forests, the largest of max_n rows and max_trees
+// trees, are shared out: rows per workgroup, workgroups per forest's rows, chunks of
+// a forest's trees, and waves that share a tree's rows.
+struct ScoreShape {
+  int32_t rows, row_blocks, chunks, split;
+  size_t lds;
+};
+ScoreShape score_shape(bool oob, int64_t n_forests, int64_t max_n, int64_t max_trees, int32_t C, int64_t cus,
+                       size_t lds_per_block);
 void launch_oob(const TreesView& T, const TreeTask* tasks, const uint64_t* inbag, const int32_t* train_rows,
                 const OobForest* forests, int32_t n_forests, int32_t max_n_train, int32_t max_trees, int64_t total,
                 const uint8_t* codes, int32_t C, const double* y, int64_t* sum, int32_t* count, double* partial,

@@ -18,7 +18,8 @@ constexpr int kOobBlock = 256;
 // Leaf sums and tree counts of a forest's rows: its training rows, each under
 // the trees that left it out (OOB), or its held-out rows under every tree.
 // A workgroup takes R rows of a forest and a chunk of its trees: the rows' codes
-// and their running sums lie in the LDS, and each wave takes trees of its own.
+// and their running sums lie in the LDS, and each wave takes trees of its own, or
+// `split` waves (a power of two) each tree, a part of the rows each.
 // It lists the rows that the tree left out (a bitmap word per 64 rows), so that
 // every lane walks a row of it, K rows per lane at a time, with the tree's first
 // nodes in the wave's part of the LDS.  One thread per row and forest walking
@@ -35,7 +36,7 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void k_score(
     const uint64_t* __restrict__ nodes, const TreeTask* __restrict__ tasks, const int64_t* __restrict__ node_base,
     const int32_t* __restrict__ n_nodes, const uint64_t* __restrict__ inbag, const int32_t* __restrict__ row_list,
     const OobForest* __restrict__ forests, const uint8_t* __restrict__ codes, int32_t C, int32_t R, int32_t n_chunks,
-    unsigned long long* __restrict__ sum, int32_t* __restrict__ count) {
+    int32_t split, unsigned long long* __restrict__ sum, int32_t* __restrict__ count) {
   extern __shared__ __align__(16) uint8_t lds[];
   constexpr int BLOCK = kScoreWaves * kWave, K = 2;
   const OobForest F = forests[blockIdx.y];
@@ -57,16 +58,18 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void k_score(
     s_cnt[i] = 0;
   }
   __syncthreads();
-  const int nw = (nr + kWave - 1) / kWave;  // bitmap words of these rows (at most 64)
-  for (int32_t t = t0 + wid; t < t1; t += kScoreWaves) {
+  // bitmap words of these rows (at most 64), and this wave's part of them
+  const int nw = (nr + kWave - 1) / kWave, per = (nw + split - 1) / split;
+  const int w0 = min(nw, wid % split * per), w1 = min(nw, w0 + per);
+  for (int32_t t = t0 + wid / split; t < t1; t += kScoreWaves / split) {
     const int64_t task = F.first_task + t;
-    uint32_t n_rows = (uint32_t)nr;
+    uint32_t n_rows = (uint32_t)max(0, min(nr, kWave * w1) - kWave * w0);
     if constexpr (OOB) {
       const int64_t bits = tasks[task].inbag_off;
       if (bits < 0) continue;  // no bootstrap: every row is in bag
       const uint64_t word = lane < nw ? inbag[bits + r0 / kWave + lane] : ~0ull;
       n_rows = 0;
-      for (int i = 0; i < nw; ++i) {
+      for (int i = w0; i < w1; ++i) {
         uint64_t out = ~read_lane(word, i);
         if (64 * i + 64 > nr) out &= ~0ull >> (64 * i + 64 - nr);
         if ((out >> lane) & 1ull) list[n_rows + (uint32_t)__popcll(out & ((1ull << lane) - 1ull))] = (uint16_t)(64 * i + lane);
@@ -85,7 +88,7 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void k_score(
       for (int k = 0; k < K; ++k) {
         const uint32_t j = j0 + (uint32_t)(k * kWave + lane);
         on[k] = j < n_rows;
-        row[k] = on[k] ? (OOB ? list[j] : j) : 0u;
+        row[k] = on[k] ? (OOB ? list[j] : (uint32_t)(kWave * w0) + j) : 0u;
         off[k] = row[k] * st;
       }
       const uint64_t* const tops[K] = {top, top};
@@ -199,37 +202,58 @@ void launch_errors(const int32_t* row_list, const OobForest* forests, int32_t n_
 }
 
 // Launch of k_score over `total` rows of n_forests forests, the largest of max_n
-// rows: R rows per workgroup, and enough tree chunks to fill the CUs when the
-// forests and row blocks alone do not.
+// rows and max_trees trees.
 template <bool OOB>
 void launch_score(const TreesView& T, const TreeTask* tasks, const uint64_t* inbag, const int32_t* row_list,
                   const OobForest* forests, int32_t n_forests, int32_t max_n, int32_t max_trees, int64_t total,
                   const uint8_t* codes, int32_t C, int64_t* sum, int32_t* count, hipStream_t s) {
-  const int64_t st = staged_stride(C);
-  const int64_t row_bytes = st + 12 + (OOB ? 2 * kScoreWaves : 0), tops = (int64_t)kScoreWaves * kScoreTop * 8;
-  // up to 512 rows, so that three workgroups (24 waves) fit a CU: the tuning
-  // grid's out-of-bag scores take 5.6 ms with 512 rows, 6.6 with 256 (each
-  // tree's first nodes serve fewer rows) and 8.3 with 1024 (two workgroups)
-  const int64_t room = (int64_t)device_info().lds_per_block / 3 - tops;
-  const int64_t most = std::min<int64_t>(512, room / row_bytes) / kWave * kWave;
-  const int64_t n_rb = (max_n + most - 1) / most;
-  const int64_t R = ((max_n + n_rb - 1) / n_rb + kWave - 1) / kWave * kWave;
-  const size_t lds = (size_t)(R * row_bytes + tops);
-  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(32 / kScoreWaves, (int64_t)(device_info().lds_per_block / lds)));
-  const int64_t slots = per_cu * device_info().cus, wgs = n_rb * n_forests;
-  int64_t n_chunks = std::min<int64_t>((2 * slots + wgs - 1) / wgs, (max_trees + kScoreWaves - 1) / kScoreWaves);
-  n_chunks = std::max<int64_t>(1, n_chunks);
+  const ScoreShape S = score_shape(OOB, n_forests, max_n, max_trees, C, device_info().cus, device_info().lds_per_block);
+  const int32_t n_chunks = S.chunks;
   if (n_chunks > 1) {
     const int zb = (int)std::max<int64_t>(1, std::min<int64_t>(1024, (total + 255) / 256));
     k_zero_scores<<<zb, 256, 0, s>>>(reinterpret_cast<unsigned long long*>(sum), OOB ? count : nullptr, total);
     AIWC_HIP(hipGetLastError());
   }
-  k_score<OOB><<<dim3((unsigned)n_rb, (unsigned)n_forests, (unsigned)n_chunks), kScoreWaves * kWave, lds, s>>>(
-      T.nodes, tasks, T.node_base, T.n_nodes, inbag, row_list, forests, codes, C, (int32_t)R, (int32_t)n_chunks,
+  k_score<OOB><<<dim3((unsigned)S.row_blocks, (unsigned)n_forests, (unsigned)n_chunks), kScoreWaves * kWave, S.lds, s>>>(
+      T.nodes, tasks, T.node_base, T.n_nodes, inbag, row_list, forests, codes, C, S.rows, n_chunks, S.split,
       reinterpret_cast<unsigned long long*>(sum), count);
   AIWC_HIP(hipGetLastError());
 }
 }  // namespace
+
+// A wave walks its rows 128 at a time (two per lane): a workgroup takes 128 held-out
+// rows, or 512 training rows, of which a tree left a third out (the tuning grid's
+// out-of-bag scores: 5.6 ms with 512 rows, 6.6 with 256, 8.3 with 1024).  Waves
+// that would have no tree of their own share one: eight waves a single tree's rows,
+// four the rows of two.  And while the launch has less than eight waves per CU
+// with a tree to walk, a workgroup takes half the rows.  Always 512 rows and a wave
+// per tree left most of the chip idle for few trees (the whole call: 10000 held-out
+// rows x 1 tree 111 us, so 77; x 40 trees 118 and 88; 100000 x 1 154 and 121; 100000
+// x 16 241 and 196; out of bag 10000 x 1 92 and 77).
+// More chunks of the trees fill the CUs when forests and row blocks do not.
+ScoreShape score_shape(bool oob, int64_t n_forests, int64_t max_n, int64_t max_trees, int32_t C, int64_t cus,
+                       size_t lds_per_block) {
+  ScoreShape S;
+  const int64_t row_bytes = staged_stride(C) + 12 + (oob ? 2 * kScoreWaves : 0), tops = (int64_t)kScoreWaves * kScoreTop * 8;
+  // at most a third of the LDS, so that three workgroups (24 waves) fit a CU
+  const int64_t room = ((int64_t)lds_per_block / 3 - tops) / row_bytes / kWave * kWave;
+  S.split = 1;
+  while (S.split < kScoreWaves && 2 * S.split * max_trees <= kScoreWaves) S.split *= 2;
+  int64_t most = std::min<int64_t>(oob ? 512 : std::min(512, 128 * S.split), room);
+  while (most > kWave && (max_n + most - 1) / most * n_forests * max_trees * S.split < 8 * cus)
+    most = (most / 2 + kWave - 1) / kWave * kWave;
+  while (S.split * kWave > most) S.split /= 2;
+  const int64_t n_rb = (max_n + most - 1) / most;
+  const int64_t R = ((max_n + n_rb - 1) / n_rb + kWave - 1) / kWave * kWave;
+  S.rows = (int32_t)R;
+  S.row_blocks = (int32_t)n_rb;
+  S.lds = (size_t)(R * row_bytes + tops);
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(32 / kScoreWaves, (int64_t)(lds_per_block / S.lds)));
+  const int64_t slots = per_cu * cus, wgs = n_rb * n_forests;
+  int64_t n_chunks = std::min<int64_t>((2 * slots + wgs - 1) / wgs, (max_trees + kScoreWaves - 1) / kScoreWaves);
+  S.chunks = (int32_t)std::max<int64_t>(1, n_chunks);
+  return S;
+}
 
 void launch_oob(const TreesView& T, const TreeTask* tasks, const uint64_t* inbag, const int32_t* train_rows,
                 const OobForest* forests, int32_t n_forests, int32_t max_n_train, int32_t max_trees, int64_t total,

@@ -135,6 +135,37 @@ def test_heldout_paths(rf, oracle, sizes, trees):
         at += size
 
 
+# few trees: waves that share a tree's rows (8, 4 and 2 of them, some without rows),
+# and workgroups of few rows
+@pytest.mark.parametrize("n,forests,trees", [(2200, 130, 1), (2200, 130, 2), (1500, 100, 3), (2200, 130, 5), (300, 3, 1),
+                                             (9000, 1, 1), (9000, 1, 4), (9000, 2, 11)])
+def test_scores_of_few_trees(rf, oracle, n, forests, trees):
+    log(f"scores of few trees n={n} forests={forests} trees={trees}")
+    rng = np.random.default_rng(n + trees)
+    C = 13
+    codes = rng.integers(0, 61, (n, C)).astype(np.uint8)
+    y = rng.normal(0.0, 1.0, n)
+    nb = np.full(C, 61, np.int32)
+    fold = rng.integers(0, 2, n).astype(np.int8)
+    dc, dy = to_dev(codes), to_dev(y)
+    forest = rf.aiwc_rf_fit(dc, rf.aiwc_rf_binner_from_counts(nb), dy,
+                            [rf.make_params(trees, 4, 3, True, 20 + k) for k in range(forests)], to_dev(fold),
+                            [k % 2 for k in range(forests)])
+    sums, counts, held = [], [], []
+    for k in range(forests):
+        rows = np.nonzero(fold != k % 2)[0]
+        of = oracle.fit(codes, nb, y, trees, 4, 3, seed=20 + k, train_rows=rows)
+        P, cnt, _ = oracle.oob(of, codes, y, 4, 3, seed=20 + k, train_rows=rows)
+        sums.append(P)
+        counts.append(cnt)
+        held.append(oracle.predict(of, codes[fold == k % 2])[0])
+    res = rf.aiwc_rf_oob_error(forest, dc, dy, n_train=sum(len(P) for P in sums))
+    assert np.array_equal(res.sums.cpu().numpy(), np.concatenate(sums))
+    assert np.array_equal(res.counts.cpu().numpy(), np.concatenate(counts))
+    res = rf.aiwc_rf_heldout_error(forest, dc, dy, n_heldout=sum(len(P) for P in held))
+    assert np.array_equal(res.sums.cpu().numpy(), np.concatenate(held))
+
+
 # node arrays taken tree by tree (up to four trees) and unpacked on the device
 def test_export_few_and_many(rf, oracle):
     log("export few and many trees")
