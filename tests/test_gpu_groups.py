@@ -130,3 +130,32 @@ def test_groups_wide_kernel(rf, oracle):
         trees = forest.export(k)
         for t in range(nt):
             assert_tree_equal(trees[t], of.tree(t), f"wide forest {k} {WIDE_FORESTS[k]} tree {t}")
+
+
+# every kernel for launches with groups: with the wide phase (a limit below the
+# training set), and without it at each number of waves per SIMD
+@pytest.fixture(scope="module")
+def shapes_setup(oracle):
+    rng = np.random.default_rng(77)
+    codes = rng.integers(0, 150, (2600, 18)).astype(np.uint8)
+    y = np.clip(0.01 * codes[:, 0] + 0.005 * codes[:, 9] + rng.normal(0.0, 0.3, 2600), -64.0, 64.0)
+    nb = np.full(18, 150, np.int32)
+    forests = [(5, 5, mn) for mn in (1, 9, 300)] + [(5, 11, 5)]
+    return codes, y, nb, forests, [oracle.fit(codes, nb, y, nt, m, mn, seed=5, n_threads=0) for nt, m, mn in forests]
+
+
+@pytest.mark.parametrize("block,limit,occ", [(b, h, 4) for b in (192, 256, 512, 1024) for h in (200, 1000)]
+                         + [(b, 100000, o) for b in (64, 128, 192, 256, 512, 1024) for o in (4, 5, 6)])
+def test_groups_every_kernel(rf, monkeypatch, shapes_setup, block, limit, occ):
+    log(f"groups block={block} limit={limit} occ={occ}")
+    codes, y, nb, forests, ofs = shapes_setup
+    monkeypatch.setenv("AIWC_RF_GROW_BLOCK", str(block))
+    monkeypatch.setenv("AIWC_RF_HUGE_MIN", str(limit))
+    monkeypatch.setenv("AIWC_RF_GROW_OCC", str(occ))
+    forest = rf.aiwc_rf_fit(to_dev(codes), rf.aiwc_rf_binner_from_counts(nb), to_dev(y),
+                            [rf.make_params(nt, m, mn, True, 5) for nt, m, mn in forests])
+    li = forest.launch()
+    assert (li["block"], li["wide_phase"], li["graph"], li["task_groups"]) == (block, limit < 2600, 1, 5 + 5)
+    for k, of in enumerate(ofs):
+        for t, tree in enumerate(forest.export(k)):
+            assert_tree_equal(tree, of.tree(t), f"forest {k} {forests[k]} tree {t}")
