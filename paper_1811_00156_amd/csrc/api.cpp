@@ -47,7 +47,9 @@ int32_t status_to_code(uint32_t st, std::string& msg) {
   return AIWC_RF_OK;
 }
 
-GrowConfig grow_config(int64_t n_cap, int64_t n_items, const std::vector<int32_t>& n_bins, int32_t mtry_max,
+}  // namespace
+
+GrowConfig aiwc::grow_config(int64_t n_cap, int64_t n_items, const std::vector<int32_t>& n_bins, int32_t mtry_max,
                        int64_t n, bool shared) {
   GrowConfig cfg;
   cfg.n_cap = n_cap;
@@ -113,6 +115,8 @@ GrowConfig grow_config(int64_t n_cap, int64_t n_items, const std::vector<int32_t
   if (!block && grow_has_wide_phase(cfg)) cfg.block = std::max(cfg.block, 192);
   return cfg;
 }
+
+namespace {
 
 // Makes a device current for a scope.
 struct OnDevice {
@@ -183,12 +187,13 @@ GrowConfig tune_grow(const GrowConfig& base, int64_t n_items, int32_t n_cols, in
   float best_ms = -1.0f;
   for (const GrowConfig& c : tune_candidates(base)) {
     int grid = 0;
+    DevBuf<uint8_t> scratch;
     try {
       grid = grow_grid_size(c, trial, mtry_max, n_cols, n);
+      scratch.reset(per_wg * (size_t)grid * grow_teams(c, mtry_max, n_cols, n), s);
     } catch (const Error&) {
-      continue;  // the shape does not fit this device
+      continue;  // the shape, or its scratch, does not fit this device
     }
-    DevBuf<uint8_t> scratch(per_wg * (size_t)grid * grow_teams(c, mtry_max, n_cols, n), s);
     // each shape is timed twice and keeps its faster run
     float ms = -1.0f;
     for (int rep = 0; rep < 2; ++rep) {

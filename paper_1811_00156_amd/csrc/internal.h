@@ -226,6 +226,10 @@ struct GrowConfig {
   int bins_max = 256;    // largest bin count of any column
   int64_t n_cap = 0;     // largest training set of any tree
 };
+// api.cpp: the untuned launch shape of trees on up to n_cap of n rows, n_items work
+// items (shared: some of them groups of several trees), and the environment's changes.
+GrowConfig grow_config(int64_t n_cap, int64_t n_items, const std::vector<int32_t>& n_bins, int32_t mtry_max,
+                       int64_t n, bool shared);
 // Autotuning of the grow kernel's launch shape.  A shape is keyed by the
 // device, the training-set size class, the columns, the largest bin count,
 // the largest mtry and the task-count class; the tuned config is cached in

@@ -347,18 +347,35 @@ void tune_store(const TuneKey& key, const GrowConfig& cfg) {
 }
 
 std::vector<GrowConfig> tune_candidates(const GrowConfig& base) {
-  // workgroup size x wide-node limit; a limit at or above the largest training
-  // set means no wide nodes, timed once per workgroup size at 4, 5 and 6 waves
-  // per SIMD.  Where large-node tasks exist (limit above 64 rows) each shape is
-  // timed with two and with four candidate columns per task.
-  // One- and two-wave workgroups are timed without wide nodes only.
+  // the default shape first, then workgroup size x wide-node limit; a limit at or
+  // above the largest training set means no wide nodes, timed once per workgroup
+  // size at 4, 5 and 6 waves per SIMD (training sets above 16384 rows always have
+  // wide nodes: their largest nodes keep one wave too long).  Where large-node tasks
+  // exist (limit above 64 rows) each shape is timed with two and with four candidate
+  // columns per task.  One- and two-wave workgroups are timed without wide nodes only.
   std::vector<GrowConfig> out;
+  auto add = [&](const GrowConfig& c) {
+    for (const GrowConfig& o : out)
+      if (o.block == c.block && o.occupancy == c.occupancy && o.big_cols == c.big_cols &&
+          grow_has_wide_phase(o) == grow_has_wide_phase(c) && (!grow_has_wide_phase(c) || o.huge_min == c.huge_min))
+        return;
+    out.push_back(c);
+  };
+  // (a choice is kept for training sets up to the next power of two: so far a limit
+  // that means no wide nodes has to reach)
+  GrowConfig first = base;
+  if (!grow_has_wide_phase(first)) {
+    int reach = 1;
+    while (reach < base.n_cap) reach *= 2;
+    first.huge_min = std::max(first.huge_min, reach);
+  }
+  add(first);
   for (int block : {64, 128, 192, 256, 512, 1024}) {
     bool narrow_done = false;
-    for (int h : {64, 512, 4096}) {
+    for (int h : {64, 512, 1024, 4096, 16384}) {
       const bool narrow = base.n_cap <= h;
       if (narrow && narrow_done) continue;
-      if (!narrow && block < 192) continue;
+      if (!narrow && (block < 192 || h == 16384)) continue;
       narrow_done = narrow_done || narrow;
       for (int occ : {4, 5, 6}) {
         if (!narrow && occ != 4) continue;
@@ -369,7 +386,7 @@ std::vector<GrowConfig> tune_candidates(const GrowConfig& base) {
           c.huge_min = h;
           c.occupancy = occ;
           c.big_cols = bc;
-          out.push_back(c);
+          add(c);
         }
       }
     }

@@ -1,7 +1,9 @@
 """Rules that share work out over the chip, on the CPU: pure functions of the sizes."""
 import itertools
 
-from tests._native import run_host
+import pytest
+
+from tests._native import build_host, run_exe, run_host
 
 SCORES = r"""
 #include <cstdio>
@@ -38,3 +40,60 @@ def test_score_shapes(tmp_path):
     for oob, n, t in itertools.product((0, 1), (10000, 262144), (1, 2, 4)):
         rows, blocks, chunks, split, _ = map(int, few[(oob, 1, n, t, 21)].split())
         assert blocks * t * split >= min(8 * 256, n // 64 * t), (oob, n, t, rows, blocks, split)
+
+
+# the default launch shape of a fit (256 CUs of 160 KB LDS, the program's own device
+# queries), and the autotuner's candidates
+TUNER = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "internal.h"
+extern "C" {
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
+  *v = a == hipDeviceAttributeMultiprocessorCount ? 256 : 163840;
+  return hipSuccess;
+}
+}
+int main(int argc, char** argv) {
+  const int n = std::atoi(argv[1]), items = std::atoi(argv[2]), bins = std::atoi(argv[3]);
+  const aiwc::GrowConfig base = aiwc::grow_config(n, items, std::vector<int32_t>(35, bins), 12, n, false);
+  std::vector<aiwc::GrowConfig> all = aiwc::tune_candidates(base);
+  all.insert(all.begin(), base);
+  for (const auto& c : all) std::printf("%d %d %d %d\n", c.block, c.huge_min, c.occupancy, c.big_cols);
+}
+"""
+
+
+@pytest.mark.parametrize("n", [60, 700, 1024, 2220, 4097, 6000, 16384, 16385, 40000, 200000])
+def test_tuner_times_the_default_shape(tmp_path, n):
+    exe = build_host(tmp_path, TUNER)
+    for items in (1, 300, 900, 2000, 20000):
+        shapes = [tuple(map(int, v.split())) for v in run_exe(exe, [n, items, 64]).splitlines()]
+        base, shapes = shapes[0], shapes[1:]
+        form = [(b, h if n > h else None, occ, bc) for b, h, occ, bc in shapes]
+        assert (base[0], base[1] if n > base[1] else None, *base[2:]) == form[0], (items, base, shapes[0])
+        assert len(set(form)) == len(form)
+        for b, h, occ, bc in shapes:
+            # a limit without wide nodes holds for every training set that shares the
+            # choice (up to the next power of two), as one- and two-wave workgroups need
+            if n <= h:
+                assert h >= 1 << (n - 1).bit_length(), (items, b, h)
+            else:
+                assert b >= 192
+        # no wide nodes up to 16384 rows: every workgroup size at every occupancy
+        narrow = {(b, occ) for b, h, occ, _ in form if h is None}
+        every = {(b, occ) for b in (64, 128, 192, 256, 512, 1024) for occ in (4, 5, 6)}
+        assert narrow == (every if n <= 16384 else set())
+        limits = {h for _, h, _, _ in form if h is not None}
+        assert limits >= {h for h in (64, 512, 1024, 4096) if h < n}
+
+
+@pytest.mark.parametrize("items", [1, 300, 900, 2000, 20000])
+def test_wide_limit_alone_finds_a_shape(tmp_path, monkeypatch, items):
+    monkeypatch.setenv("AIWC_RF_HUGE_MIN", "1000")
+    exe = build_host(tmp_path, TUNER)
+    for n in (1001, 2220, 9000, 100000):
+        block, limit = map(int, run_exe(exe, [n, items, 64]).split()[:2])
+        assert limit == 1000 and block >= 192
+    assert int(run_exe(exe, [1000, 20000, 64]).split()[0]) == 64
