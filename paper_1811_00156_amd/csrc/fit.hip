@@ -459,9 +459,12 @@ __device__ __forceinline__ int64_t packed_s(uint64_t v, uint32_t n) { return (in
 // one correction: with r = RN(1 / b) and q = RN(a r), q is within an ulp of a / b
 // and RN(q + r RN(a - b q)) is the correctly rounded quotient, the value the
 // sequence of div_pos gives.  An LDS read and three instructions stand for a
-// quarter-rate reciprocal and seven.  The table's size is what a workgroup of
-// teams has left beside the paper's frame (2220 x 35 codes).
-constexpr int kRecip = 320;
+// quarter-rate reciprocal and seven.  Most of the gain comes with the first
+// entries, and each takes 8 bytes of every workgroup's LDS from the code matrix or
+// from the resident one-wave workgroups (128, 192, 256, 320 entries: the tuning grid
+// 205.0 202.3 201.1 200.7 ms, 2000 trees on 2220 rows 2.06 2.00 1.95 1.95, 500 on
+// 200000 rows 60.6 59.6 59.2 59.1; with 320 a CU held 19 one-wave workgroups, not 20).
+constexpr int kRecip = 256;
 
 template <int THREADS>
 __device__ __forceinline__ void fill_recip(double* recip) {

@@ -69,3 +69,37 @@ def test_teams_task_groups(rf, oracle):
         of = oracle.fit(codes, nb, y, 20, m, k, seed=6, train_rows=rows)
         for t, tree in enumerate(forest.export(i)):
             assert_tree_equal(tree, of.tree(t), f"forest {i} tree {t}")
+
+
+# which kernel ran: a launch of teams has a workgroup per sixteen trees, one of
+# one-wave workgroups one per tree.  Around the largest code matrix that fits the
+# LDS beside sixteen teams' areas: 163840 - 16 x 5184 - 2560 = 78336 bytes
+@pytest.mark.parametrize("C,n,trees,teams", [
+    (35, 2220, 40, True), (35, 2238, 17, True), (35, 2239, 17, False), (3, 16000, 33, True),
+    (36, 2176, 5, True), (36, 2177, 5, False), (65, 1205, 16, True), (65, 1206, 16, False), (200, 300, 5, False),
+])
+def test_teams_edge(rf, oracle, C, n, trees, teams):
+    log(f"teams edge C={C} n={n} trees={trees} teams={teams}")
+    codes, y, nb = _data(C, n, 40, 2.0, n + C)
+    mtry = max(1, C // 4)
+    params = rf.make_params(trees, mtry, 30, True, 8)
+    forest = rf.aiwc_rf_fit(to_dev(codes), rf.aiwc_rf_binner_from_counts(nb), to_dev(y), params)
+    li = forest.launch()
+    assert (li["block"], li["waves_per_simd"], li["wide_phase"]) == (64, 5, 0)
+    assert li["grid"] == (-(-trees // 16) if teams else trees)
+    of = oracle.fit(codes, nb, y, trees, mtry, 30, seed=8)
+    for t, tree in enumerate(forest.export()):
+        assert_tree_equal(tree, of.tree(t), f"tree {t}")
+
+
+# one-wave workgroups of five waves per SIMD: twenty fit a CU
+def test_one_wave_workgroups_per_cu(rf):
+    import torch
+
+    log("one-wave workgroups per CU")
+    codes, y, nb = _data(40, 2500, 64, 2.0, 1)
+    forest = rf.aiwc_rf_fit(to_dev(codes), rf.aiwc_rf_binner_from_counts(nb), to_dev(y),
+                            rf.make_params(6000, 1, 2000, True, 8))
+    li = forest.launch()
+    assert (li["block"], li["waves_per_simd"], li["wide_phase"]) == (64, 5, 0)
+    assert li["grid"] == 20 * torch.cuda.get_device_properties(0).multi_processor_count
