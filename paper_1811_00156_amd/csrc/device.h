@@ -137,6 +137,27 @@ __device__ __forceinline__ double div_pos(double a, double b) {
   return __builtin_fma(rem, r, q);
 }
 
+// a / b, correctly rounded, for an integer b in [1, 511], a zero or in [1, 2^62], and
+// r = RN(1 / b) (r = 0 for a side without rows: a zero gives zero).  An LDS read of r
+// and three instructions stand for div_pos's quarter-rate reciprocal and seven.
+// r and a r are off by half an ulp each, so q is within 1.5 ulp u of a / b, and
+// a - b q, a multiple of u of at most 1.5 b of them, is exact.  Adding RN((a - b q) / b)
+// to q then misses a / b by 1.5 x 2^-53 u at most before the last rounding, and a / b
+// is no midpoint of two doubles (b times one has more than 53 bits, unless b is a
+// power of two and the quotient itself exact) but at least u / (4 b) away from any.
+__host__ __device__ __forceinline__ double div_recip(double a, double b, double r) {
+  const double q = a * r;
+  return __builtin_fma(__builtin_fma(-b, q, a), r, q);
+}
+
+// A bin of a node that weighs below 512: the weight in the high word and the sum of
+// w (y + 2^22) >= 0 in the low one (|y| <= 2^22: below 2^32, so no carry out of any
+// sum of them), which decode for free.
+__host__ __device__ __forceinline__ uint64_t light_word(uint32_t w, int64_t wy) {
+  return ((uint64_t)w << 32) | ((uint32_t)wy + (w << 22));
+}
+__host__ __device__ __forceinline__ int32_t light_sum(uint32_t n, uint32_t biased) { return (int32_t)(biased - (n << 22)); }
+
 // (|S| < 2^41 and N < 2^19 by the fixed-point budget: S^2 < 2^82.)
 __device__ __forceinline__ double split_score(int64_t SL, uint32_t NL, int64_t SR, uint32_t NR) {
   const double a = i64_to_f64(SL), b = i64_to_f64(SR);

@@ -454,16 +454,12 @@ __device__ __forceinline__ uint64_t pack_ns(uint32_t w, int64_t wy) { return ((u
 __device__ __forceinline__ uint32_t packed_n(uint64_t v) { return (uint32_t)((v + (1ull << 44)) >> 45); }
 __device__ __forceinline__ int64_t packed_s(uint64_t v, uint32_t n) { return (int64_t)(v - ((uint64_t)n << 45)); }
 
-// Light nodes weigh below kRecip.  Their split scores divide by multiplying with
-// the correctly rounded reciprocal of the weight, from a table in the LDS, and
-// one correction: with r = RN(1 / b) and q = RN(a r), q is within an ulp of a / b
-// and RN(q + r RN(a - b q)) is the correctly rounded quotient, the value the
-// sequence of div_pos gives.  An LDS read and three instructions stand for a
-// quarter-rate reciprocal and seven.  Most of the gain comes with the first
-// entries, and each takes 8 bytes of every workgroup's LDS from the code matrix or
-// from the resident one-wave workgroups (128, 192, 256, 320 entries: the tuning grid
-// 205.0 202.3 201.1 200.7 ms, 2000 trees on 2220 rows 2.06 2.00 1.95 1.95, 500 on
-// 200000 rows 60.6 59.6 59.2 59.1; with 320 a CU held 19 one-wave workgroups, not 20).
+// Light nodes weigh below kRecip: their split scores divide by reciprocals from a
+// table in the LDS (div_recip).  Most of the gain comes with the first entries, and
+// each takes 8 bytes of every workgroup's LDS from the code matrix or from the
+// resident one-wave workgroups (128, 192, 256, 320 entries: the tuning grid 205.0
+// 202.3 201.1 200.7 ms, 2000 trees on 2220 rows 2.06 2.00 1.95 1.95, 500 on 200000
+// rows 60.6 59.6 59.2 59.1; with 320 a CU held 19 one-wave workgroups, not 20).
 constexpr int kRecip = 256;
 
 template <int THREADS>
@@ -479,21 +475,13 @@ __device__ __forceinline__ double light_score(const double* recip, int32_t SL, u
                                               double Nd) {
   const double rl = recip[NL], rr = recip[N - NL];
   const double a = (double)SL, b = Sd - a, nl = (double)NL, nr = Nd - nl;
-  const double aa = a * a, bb = b * b;
-  const double ql = aa * rl, qr = bb * rr;
-  return __builtin_fma(__builtin_fma(-nl, ql, aa), rl, ql) + __builtin_fma(__builtin_fma(-nr, qr, bb), rr, qr);
+  return div_recip(a * a, nl, rl) + div_recip(b * b, nr, rr);
 }
 
-// A light node's bin: the weight in the high word and the sum of w (y + 2^22) >= 0
-// in the low one (below kRecip 2^23 < 2^32, so no carry), which decode for free
-// and scan as two 32-bit words.
-__device__ __forceinline__ uint64_t light_word(uint32_t w, int64_t wy) {
-  return ((uint64_t)w << 32) | (uint32_t)((int32_t)wy + (int32_t)(w << 22));
-}
+// Prefix sums of a light node's bins (light_word), as two 32-bit words.
 __device__ __forceinline__ uint64_t scan_light(uint64_t h) {
   return ((uint64_t)wave_incl_scan_u32((uint32_t)(h >> 32)) << 32) | wave_incl_scan_u32((uint32_t)h);
 }
-__device__ __forceinline__ int32_t light_sum(uint32_t n, uint32_t biased) { return (int32_t)(biased - (n << 22)); }
 
 // The wave's best split of (score, key), one per lane: the largest score, then
 // the smallest key; scores are -1 (none) or not negative.  Every lane returns it.
