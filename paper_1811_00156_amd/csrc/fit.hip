@@ -569,6 +569,7 @@ __device__ __forceinline__ void small_finish(const Ctx<LC>& x, uint32_t k, bool 
 template <int W, bool C7, bool B3>
 __device__ __forceinline__ void byte_plane_sums(uint32_t code, const uint32_t* seg_codes, const uint8_t* seg_planes,
                                                 uint32_t& NL, int64_t& SL) {
+  static_assert(!C7 || B3, "the search with four byte planes takes any code");
   const uint32_t kk = C7 ? (code + 0x80u) * 0x01010101u : code * 0x00010001u + 0x01000100u;
   uint32_t aN = 0, a0 = 0, a1 = 0;
   int32_t a2 = 0, a3 = 0;
@@ -601,10 +602,7 @@ __device__ __forceinline__ void byte_plane_sums(uint32_t code, const uint32_t* s
     // plane j's sum times 2^(8 j) is a_j / 128 * 2^(8 j), the signed top
     // plane's negated
     NL = aN >> 7;
-    if constexpr (B3)
-      SL = (int64_t)(a0 >> 7) + ((int64_t)a1 << 1) - ((int64_t)a2 << 9);
-    else
-      SL = (int64_t)(a0 >> 7) + ((int64_t)a1 << 1) + ((int64_t)(uint32_t)a2 << 9) - ((int64_t)a3 << 17);
+    SL = (int64_t)(a0 >> 7) + ((int64_t)a1 << 1) - ((int64_t)a2 << 9);
   } else {
     NL = aN;
     if constexpr (B3)
@@ -673,9 +671,11 @@ __device__ __forceinline__ SegDigits<W> seg_digits(const uint8_t* planes, int la
   return d;
 }
 
+// B3: three digits of w y, and light nodes only (`light` is not looked at).
 template <int W, bool C7, bool B3>
 __device__ __forceinline__ void matrix_sums(const SegDigits<W>& A, const uint8_t* planes, const uint8_t* col_codes,
                                             uint32_t code, int lane, uint32_t& NL, int64_t& SL, bool light) {
+  static_assert(!C7 || B3, "the search with four digits takes any code");
   constexpr uint32_t kTop = 0x80808080u;
   v4i_t acc = {0, 0, 0, 0}, acc4 = {0, 0, 0, 0};
   if constexpr (W <= 16) {
@@ -710,13 +710,12 @@ __device__ __forceinline__ void matrix_sums(const SegDigits<W>& A, const uint8_t
   }
   // every accumulator is a multiple of 128
   NL = (uint32_t)(acc[0] >> 7);
-  if (light) {  // the sum fits 32 bits (its terms need not: they wrap)
+  if (B3 || light) {  // the sum fits 32 bits (its terms need not: they wrap)
     uint32_t v = (uint32_t)(acc[1] >> 7) + ((uint32_t)acc[2] << 1) + ((uint32_t)acc[3] << 9);
     if constexpr (!B3) v += (uint32_t)acc4[0] << 17;
     SL = (int32_t)v;
   } else {
-    SL = (int64_t)(acc[1] >> 7) + (int64_t)acc[2] * 2 + (int64_t)acc[3] * 512;
-    if constexpr (!B3) SL += (int64_t)acc4[0] * 131072;
+    SL = (int64_t)(acc[1] >> 7) + (int64_t)acc[2] * 2 + (int64_t)acc[3] * 512 + (int64_t)acc4[0] * 131072;
   }
 }
 
