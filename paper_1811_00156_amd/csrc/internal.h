@@ -315,15 +315,19 @@ bool launch_fit_graph(const GrowConfig& cfg, const GrowLaunch& g, const uint8_t*
                       int grid, hipStream_t s);
 
 // The grown trees of a fit, as traversal reads them: the node pool, and per task
-// its first node and node count; train_rows: the rows they were grown on.
+// its first node and node count; train_rows: the rows they were grown on; leaves:
+// about how many a tree has, one per in-bag row or per half min.node.size of weight
+// (0: the root alone).
 struct TreesView {
   const uint64_t* nodes;
   const int64_t* node_base;
   const int32_t* n_nodes;
-  int32_t train_rows;
+  int32_t train_rows, leaves;
 };
 inline TreesView trees_of(const aiwc_rf_forest* f, int32_t forest_index) {
-  return {f->nodes.p, f->node_base.p, f->n_nodes.p, f->n_train[(size_t)forest_index]};
+  const double n = f->n_train[(size_t)forest_index], k = f->params[(size_t)forest_index].min_node_size;
+  return {f->nodes.p, f->node_base.p, f->n_nodes.p, (int32_t)n,
+          n <= k ? 0 : 1 + (int32_t)(n * (k < 2.0 ? 0.632 : 1.5 / (k + 1.0)))};
 }
 
 // oob.hip: out-of-bag sums of every training row of forests [f0, f1), then
@@ -377,11 +381,12 @@ void launch_predict(const TreesView& F, int32_t tree_begin, int32_t tree_end, co
                     int32_t C, int64_t* sum, double* y, int32_t num_trees, hipStream_t s);
 // How a prediction of n rows by n_trees trees runs: a workgroup per row or lanes of
 // a row, which write the answers themselves and need no row sums (`sum` may be
-// null), several workgroups per row, or staged rows and chunks of trees.  A device
+// null), several workgroups per row, or a row per thread and chunks of trees, with
+// rows and upper levels staged or not.  A device
 // selection whose (kernel, device) rows have a workgroup each needs no expanded codes.
-enum class PredictRoute { kRow, kLanes, kRowParts, kMany };
-inline bool needs_sums(PredictRoute r) { return r == PredictRoute::kRowParts || r == PredictRoute::kMany; }
-PredictRoute predict_route(const TreesView& F, int64_t n, int32_t n_trees);
+enum class PredictRoute { kRow, kLanes, kRowParts, kDirect, kMany };
+inline bool needs_sums(PredictRoute r) { return r != PredictRoute::kRow && r != PredictRoute::kLanes; }
+PredictRoute predict_route(const TreesView& F, int64_t n, int32_t n_trees, int32_t C);
 // Lets a kernel take all of the device's LDS as dynamic LDS (set once per device).
 void allow_lds(const void* kernel);
 

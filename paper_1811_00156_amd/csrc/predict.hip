@@ -233,6 +233,54 @@ __global__ __launch_bounds__(kPredBlock) void k_traverse_lanes(TreesView F, int3
   }
 }
 
+// Prediction of some rows by trees that are small, or too few pairs of rows and trees
+// to pay for staging: a row per thread and a chunk of the trees per workgroup, codes
+// and nodes where they are, two trees at a time.  (700 rows x 1100 trees of 34 leaves:
+// 23 us, 35 with the rows and upper levels staged; 8000 x 122 of 75: 25 and 29.)
+__global__ __launch_bounds__(kPredBlock) void k_traverse_direct(TreesView F, int32_t tree_begin, int32_t tree_end,
+                                                                int32_t chunk, int32_t n_chunks,
+                                                                const uint8_t* __restrict__ codes, int64_t n,
+                                                                int32_t C, unsigned long long* __restrict__ sum,
+                                                                double* __restrict__ y, double trees) {
+  const int32_t t0 = tree_begin + (int32_t)(blockIdx.x % (unsigned)n_chunks) * chunk, t1 = min(tree_end, t0 + chunk);
+  const int64_t r = (int64_t)(blockIdx.x / (unsigned)n_chunks) * kPredBlock + threadIdx.x;
+  if (r >= n || t0 >= t1) return;
+  const uint8_t* row = codes + r * C;
+  constexpr int K = 2;
+  int64_t acc = 0;
+  for (int32_t t = t0; t < t1; t += K) {
+    const uint64_t* tn[K];
+    uint64_t v[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const bool in = t + k < t1;
+      tn[k] = F.nodes + (in ? F.node_base[t + k] : 0);
+      v[k] = in ? tn[k][0] : (uint64_t)kLeafCol;
+    }
+    bool open = true;
+    while (open) {
+      open = false;
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const uint32_t c = node_col(v[k]);
+        if (c != kLeafCol) {
+          const NodePair p = *reinterpret_cast<const NodePair*>(tn[k] + node_left(v[k]));
+          v[k] = row[c] > node_bin(v[k]) ? p.r : p.l;
+          open = true;
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) acc += node_q(v[k]);
+  }
+  if (n_chunks > 1) {
+    atomicAdd(&sum[r], (unsigned long long)acc);
+  } else {
+    if (sum) sum[r] = (unsigned long long)acc;
+    if (y) y[r] = ((double)acc * 0x1p-32) / trees;
+  }
+}
+
 __global__ void k_zero_i64(unsigned long long* p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     p[i] = 0ull;
@@ -307,39 +355,61 @@ void launch_rank_accuracy(const double* times, const double* truth, int64_t m, i
   AIWC_HIP(hipGetLastError());
 }
 
-// By (row, tree) pairs, and the size of the trees, from which the reads that share
-// no cache line cost more.  A workgroup per row reads another tree with every
-// lane, one launch: 60 rows x 505 trees of 2220 training rows 9 us against 25
-// with the rows staged, 512 rows 17 and 25, 1000 rows x 130 trees of 30000 28 and
-// 40, x 250 trees of 12000 37 and 35; trees of 200000: 256 rows 32 and 36, 512 rows
-// 53 and 42.  More trees than it walks at once, or large ones, are more than one CU
-// fetches soon: several workgroups share the row, two launches more (1600 trees of
-// 2220 rows: 1 row 41 us by one workgroup, 16 by several, 26 with the rows staged;
-// 150 rows 53, 43, 45; 250 rows 58, 56, 47; 700 trees of 60000: 60 rows 43, 36, 46;
-// 250 rows 61, 64, 55).  Few trees take lanes of a row, also one
-// launch: 8000 rows x 60 trees of 300 training rows 18 us against 25, 9030 x 71 28 and
-// 35, 16000 x 60 33 and 31; 4000 x 200 trees of 100 rows 19 and 27, 8000 39 and 32; 4000 x 120 trees of
-// 1000 25 and 27, 8000 49 and 34, 1100 x 300 31 and 25; 16000 x 30 trees of 2220 23
-// and 27, 8000 x 60 28 and 27, 1100 x 300 54 and 27; 4000 x 64 trees of 8000 22 and 24,
-// 8000 43 and 30; 1100 x 64 trees of 30000 22 and 21; 10000 x 16 trees of 200000 16
-// and 24, 16000 x 16 of 100000 31 and 28.
-PredictRoute predict_route(const TreesView& F, int64_t n, int32_t n_trees) {
-  const int64_t pairs = n * n_trees, r = F.train_rows;
-  const bool small = r <= 8192;
-  if (n <= 1024 && n_trees <= (small ? 2 * kRowBlock : kRowBlock)) {
-    if (pairs <= (small ? (int64_t)5 << 16 : (int64_t)1 << 17)) return PredictRoute::kRow;
-  } else if (pairs <= (small ? (int64_t)1 << 18 : (int64_t)1 << 17) && n_trees > kRowBlock) {
-    return PredictRoute::kRowParts;
+// The route by the (row, tree) pairs and the leaves of a tree, from which the reads
+// that share no cache line cost more.  One launch instead of three is worth 8 us, so
+// few pairs take a workgroup per row, which reads another tree with every lane, or
+// lanes of a row; several workgroups per row where it has more trees than one fetches
+// soon.  Then a row per thread, which staging beats from the last limit on.  The
+// limits are those of the fastest route over 13000 predictions (1 to 200000 rows, 1
+// to 2000 trees of 1 to 126000 leaves, 3 to 80 columns).  Limits by the training rows
+// alone, calibrated on deep trees and without the row per thread, had left 1 in 14
+// behind that kernel, by up to 1.7 times.  For instance (us, by route): 300 trees of
+// 75 leaves, 700 rows: a workgroup per row 11, lanes 17, a row per thread 21, staged
+// 22; 3000 rows: 37, 25, 26, 26; 8000 rows: 92, 74, 43, 42; of 5000 leaves, 100 rows:
+// 15, 53, 22, 24; 1500 rows: 65, 66, 38, 31.
+struct RouteLimits {
+  int32_t leaves;     // of trees with fewer leaves than this, in units of 1024 pairs:
+  int32_t row, row2;  // a workgroup per row up to 1024 rows and 512 trees, and 1024
+  int32_t rows;       // the same for up to 4096 rows and 512 trees, counted as 192 at least
+  int32_t parts;      // several workgroups per row, more than 512 trees
+  int32_t lanes[5];   // lanes of a row up to 32, 64, 128, 320 and 512 trees
+  int32_t direct;     // a row per thread
+};
+constexpr RouteLimits kRouteLimits[] = {
+    {1, 512, 512, 1024, 512, {1700, 1700, 1700, 1700, 1700}, INT32_MAX},  // a root alone
+    {4, 512, 512, 1024, 512, {1700, 1700, 1700, 1700, 1700}, 16384},
+    {16, 512, 704, 1024, 512, {2000, 2000, 2000, 1448, 1024}, 4096},
+    {64, 512, 512, 1024, 352, {1200, 1448, 1448, 1024, 512}, 1200},
+    {256, 352, 352, 512, 256, {1200, 860, 704, 704, 0}, 1024},
+    {1024, 352, 256, 352, 256, {704, 512, 512, 224, 0}, 512},
+    {4096, 256, 176, 64, 176, {512, 352, 304, 128, 0}, 256},
+    {16384, 128, 0, 64, 128, {512, 208, 64, 0, 0}, 256},
+    {65536, 128, 0, 64, 128, {256, 176, 0, 0, 0}, 192},
+    {INT32_MAX, 91, 0, 64, 128, {256, 128, 0, 0, 0}, 128}};
+
+PredictRoute predict_route(const TreesView& F, int64_t n, int32_t n_trees, int32_t C) {
+  const RouteLimits* L = kRouteLimits;
+  while (F.leaves >= L->leaves) ++L;
+  const int64_t pairs = (n * n_trees + 1023) / 1024;
+  // trees grown on many rows lie far apart in memory, whatever their leaves (66183
+  // rows, 1946 leaves, 547 rows x 453 trees: a workgroup per row 35 us, staged 27;
+  // 23836 rows, 3575 leaves, 2364 x 92: lanes 28 us, a row per thread 22)
+  const bool far = F.train_rows > 8192;
+  const int group = n_trees <= 32 ? 0 : n_trees <= 64 ? 1 : n_trees <= 128 ? 2 : n_trees <= 320 ? 3 : 4;
+  const bool lanes = n_trees <= 512 && pairs <= L->lanes[group] && !(far && group > 1 && F.leaves >= 1024);
+  if (n <= 1024) {
+    const int32_t row = far ? std::min(L->row, 176) : L->row;
+    if (pairs <= (n_trees <= kRowBlock ? row : n_trees <= 2 * kRowBlock ? L->row2 : 0)) return PredictRoute::kRow;
+  } else if (lanes) {
+    return PredictRoute::kLanes;
+  } else if (n <= 4096 && n_trees <= kRowBlock && n * std::max(n_trees, 192) / 1024 <= L->rows) {
+    return PredictRoute::kRow;
   }
-  const int64_t lanes = r <= 256                                    ? (int64_t)5 << 18
-                        : r <= 512                                  ? (int64_t)5 << 17
-                        : r <= 1024 || (r <= 4096 && n_trees <= 32) ? (int64_t)1 << 19
-                        : r <= 4096                                 ? (int64_t)3 << 17
-                        : r <= 16384                                ? (int64_t)1 << 18
-                                                                    : (int64_t)3 << 16;
-  const int32_t most = r <= 256 ? 512 : r <= 4096 ? 128 : r <= 16384 ? 64 : 16;
-  if (n_trees <= most && pairs <= lanes) return PredictRoute::kLanes;
-  return PredictRoute::kMany;
+  if (n <= 4096 && n_trees > kRowBlock && pairs <= L->parts) return PredictRoute::kRowParts;
+  if (lanes) return PredictRoute::kLanes;
+  // (wide rows of the smallest trees: staging reads them in order)
+  const int wide = F.leaves < 1 || F.leaves >= 16 || C <= 24 ? 0 : C <= 48 ? 1 : 2;
+  return pairs <= L->direct >> wide ? PredictRoute::kDirect : PredictRoute::kMany;
 }
 
 namespace {
@@ -369,7 +439,7 @@ void launch_select_device(const TreesView& F, int32_t tree_begin, int32_t tree_e
                           int64_t m, int32_t C, int32_t n_devices, int32_t num_trees, uint8_t* expanded, int64_t* sum,
                           double* times, int32_t* best, hipStream_t s) {
   const int64_t rows = m * n_devices;
-  if (predict_route(F, rows, tree_end - tree_begin) == PredictRoute::kRow) {
+  if (predict_route(F, rows, tree_end - tree_begin, C) == PredictRoute::kRow) {
     launch_row(F, tree_begin, tree_end, feature_codes, rows, C, n_devices, nullptr, times, num_trees, 1, s);
   } else {
     const int eb = (int)std::max<int64_t>(1, std::min<int64_t>(4096, (rows * C + 255) / 256));
@@ -456,7 +526,7 @@ void traverse_many(const TreesView& F, int32_t tree_begin, int32_t tree_end, con
 void launch_predict(const TreesView& F, int32_t tree_begin, int32_t tree_end, const uint8_t* codes, int64_t n,
                     int32_t C, int64_t* sum, double* y, int32_t num_trees, hipStream_t s) {
   if (n <= 0) return;
-  const PredictRoute route = predict_route(F, n, tree_end - tree_begin);
+  const PredictRoute route = predict_route(F, n, tree_end - tree_begin, C);
   if (route == PredictRoute::kRow) {
     launch_row(F, tree_begin, tree_end, codes, n, C, 0, sum, y, num_trees, 1, s);
     return;
@@ -474,6 +544,22 @@ void launch_predict(const TreesView& F, int32_t tree_begin, int32_t tree_end, co
     k_traverse_lanes<<<(unsigned)(((n << lg) + kPredBlock - 1) / kPredBlock), kPredBlock, 0, s>>>(
         F, tree_begin, tree_end, lg, codes, n, C, reinterpret_cast<unsigned long long*>(sum), y, (double)num_trees);
     AIWC_HIP(hipGetLastError());
+    return;
+  }
+  if (route == PredictRoute::kDirect) {
+    // about four workgroups per CU, the chunks of an XCD's workgroups the same
+    const int32_t T = tree_end - tree_begin;
+    const int64_t n_rb = (n + kPredBlock - 1) / kPredBlock, target = 4LL * device_info().cus;
+    int64_t n_chunks = std::max<int64_t>(1, std::min<int64_t>(T, (target + n_rb - 1) / n_rb));
+    if (n_chunks > 1) n_chunks = std::min<int64_t>(T, (n_chunks + 7) / 8 * 8);
+    const int32_t chunk = (int32_t)((T + n_chunks - 1) / n_chunks);
+    n_chunks = (T + chunk - 1) / chunk;
+    if (n_chunks > 1) zero_sums(sum, n, s);
+    k_traverse_direct<<<(unsigned)(n_rb * n_chunks), kPredBlock, 0, s>>>(
+        F, tree_begin, tree_end, chunk, (int32_t)n_chunks, codes, n, C, reinterpret_cast<unsigned long long*>(sum), y,
+        (double)num_trees);
+    AIWC_HIP(hipGetLastError());
+    if (n_chunks > 1 && y) finalize_sums(sum, n, num_trees, y, s);
     return;
   }
   // 256 or 512 of a tree's nodes in the LDS: the fewer, the more workgroups fit

@@ -63,6 +63,39 @@ def test_predict_paths(rf, oracle, C, trees, rows):
         assert np.array_equal(rf.aiwc_rf_predict(forest, off).cpu().numpy(), yhat[:n]), n
 
 
+# trees of few and of many leaves (by min.node.size), rows on both sides of the limits
+# of each route: a workgroup per row (below and above 1024 rows), several, lanes, a row
+# per thread (chunks of the trees, and one chunk for a root alone), staged
+ROUTES = [
+    (6, 60, 100, 40, (1, 1100, 300000)), (30, 400, 30, 1100, (1, 327, 328, 700, 1117, 1118)),
+    (5, 400, 30, 400, (1310, 1311, 2621, 2622, 3072, 3073)), (6, 300, 5, 122, (2950, 5908, 5909, 8594, 8596)),
+    (9, 2220, 1, 505, (519, 520, 700)), (9, 2220, 1, 300, (873, 874, 900, 1024, 1025)),
+    (7, 9000, 1, 60, (1024, 3549, 3550, 4369, 4370)), (50, 40, 9, 700, (700, 1500, 2048, 3000)),
+]
+
+
+@pytest.mark.parametrize("C,n,min_node,trees,rows", ROUTES)
+def test_predict_routes(rf, oracle, C, n, min_node, trees, rows):
+    import torch
+
+    log(f"predict routes C={C} n={n} min_node={min_node} trees={trees}")
+    rng = np.random.default_rng(n + trees)
+    codes = rng.integers(0, 61, (n, C)).astype(np.uint8)
+    y = rng.normal(0.0, 1.0, n)
+    nb = np.full(C, 61, np.int32)
+    forest = rf.aiwc_rf_fit(to_dev(codes), rf.aiwc_rf_binner_from_counts(nb), to_dev(y),
+                            rf.make_params(trees, 3, min_node, True, 6))
+    of = oracle.fit(codes, nb, y, trees, 3, min_node, seed=6)
+    q = rng.integers(0, 256, (max(rows), C)).astype(np.uint8)
+    P, yhat = oracle.predict(of, q)
+    dq = to_dev(q)
+    for k in rows:
+        assert np.array_equal(rf.aiwc_rf_predict(forest, dq[:k]).cpu().numpy(), yhat[:k]), k
+        out = torch.empty(k, dtype=torch.float64, device="cuda")
+        assert np.array_equal(rf.aiwc_rf_predict_noalloc(forest, dq[:k], out).cpu().numpy(), yhat[:k]), k
+        assert np.array_equal(rf.aiwc_rf_predict_sum(forest, dq[:k], 0, trees).cpu().numpy(), P[:k]), k
+
+
 # (kernel, device) rows below and above the per-row kernel's limit
 @pytest.mark.parametrize("D,m,trees", [(1, 5, 30), (15, 4, 30), (15, 68, 30), (15, 69, 30), (32, 100, 30), (15, 4, 1100)])
 def test_select_paths(rf, oracle, D, m, trees):

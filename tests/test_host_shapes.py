@@ -97,3 +97,44 @@ def test_wide_limit_alone_finds_a_shape(tmp_path, monkeypatch, items):
         block, limit = map(int, run_exe(exe, [n, items, 64]).split()[:2])
         assert limit == 1000 and block >= 192
     assert int(run_exe(exe, [1000, 20000, 64]).split()[0]) == 64
+
+
+ROUTES = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "internal.h"
+int main(int argc, char** argv) {
+  for (int i = 1; i + 5 <= argc; i += 5) {
+    aiwc_rf_forest f;
+    f.params.push_back({1, 1, std::atoi(argv[i + 1]), 1, 1});
+    f.n_train.push_back(std::atoi(argv[i]));
+    const aiwc::TreesView t = aiwc::trees_of(&f, 0);
+    std::printf("%d\n", (int)aiwc::predict_route(t, std::atoi(argv[i + 2]), std::atoi(argv[i + 3]), std::atoi(argv[i + 4])));
+  }
+}
+"""
+ROW, LANES, PARTS, DIRECT, STAGED = range(5)
+
+
+def test_prediction_routes(tmp_path):
+    exe = build_host(tmp_path, ROUTES)
+
+    def routes(cases):
+        return [int(v) for v in run_exe(exe, [v for c in cases for v in c]).split()]
+
+    # (training rows, min.node.size, rows, trees, columns): fastest in measurements
+    want = {
+        (2220, 9, 1, 505, 35): ROW, (2220, 9, 60, 505, 35): ROW, (300, 5, 700, 300, 20): ROW,
+        (400, 30, 1500, 400, 35): ROW, (300, 5, 3000, 200, 20): LANES, (300, 5, 8000, 60, 20): LANES,
+        (20000, 5, 3000, 60, 20): LANES, (2220, 5, 20, 2000, 20): PARTS, (2220, 5, 100, 1100, 20): PARTS,
+        (40, 30, 700, 1100, 20): DIRECT, (300, 30, 700, 1100, 20): DIRECT, (300, 5, 8000, 122, 20): DIRECT,
+        (300, 5, 900, 513, 20): DIRECT, (30, 50, 100000, 500, 70): DIRECT, (200000, 5, 4096, 500, 65): STAGED,
+        (200000, 5, 200000, 500, 65): STAGED, (2220, 5, 60000, 500, 35): STAGED, (40, 9, 40000, 500, 75): STAGED,
+    }
+    assert dict(zip(want, routes(list(want)))) == want
+    # each route takes the fewest rows of what it is for, and none comes back
+    for n_train, k, trees, C in itertools.product((30, 300, 2220, 30000, 200000), (1, 9), (1, 40, 500, 600, 1100), (5, 66)):
+        seen = routes([(n_train, k, n, trees, C) for n in (1, 10, 100, 300, 1000, 2000, 4096, 5000, 20000, 100000, 10 ** 6)])
+        assert seen[0] in (ROW, PARTS)
+        firsts = [r for i, r in enumerate(seen) if i == 0 or r != seen[i - 1]]
+        assert STAGED not in firsts[:-1] and (PARTS not in seen or trees > 512) and (LANES not in seen or trees <= 512)
