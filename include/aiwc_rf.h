@@ -390,6 +390,10 @@ int aiwc_rf_rank_accuracy(const double* times, const double* truth, int64_t m, i
  * requests that arrive while no range is large enough wait, in arrival order,
  * until running batches free their slots.  No allocation happens per request.
  *
+ * One dispatcher thread: while batches are out it wakes every 5 microseconds to look
+ * for finished ones (every 20 after half a millisecond without any, or with requests
+ * waiting for a range); without requests it sleeps until one is submitted.
+ *
  * create:  forest/forest_index to serve; memory_budget_bytes (see above);
  *          max_batch_rows caps one batch; n_streams in [1, 8].  EINVAL for bad
  *          arguments or a budget below one row, ESTATE if the fit failed, ENOMEM
