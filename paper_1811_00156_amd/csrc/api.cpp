@@ -118,6 +118,20 @@ GrowConfig aiwc::grow_config(int64_t n_cap, int64_t n_items, const std::vector<i
 
 namespace {
 
+// Node arrays of one tree, unpacked from its node words and weights.
+void unpack_nodes(const uint64_t* words, const uint32_t* N, size_t count, uint8_t* col, uint8_t* bin, int32_t* left,
+                  int64_t* q, int32_t* Nout) {
+  for (size_t i = 0; i < count; ++i) {
+    const uint64_t v = words[i];
+    const bool leaf = node_col(v) == kLeafCol;
+    if (col) col[i] = (uint8_t)node_col(v);
+    if (bin) bin[i] = leaf ? 0 : (uint8_t)node_bin(v);
+    if (left) left[i] = leaf ? -1 : (int32_t)node_left(v);
+    if (q) q[i] = leaf ? node_q(v) : 0;
+    if (Nout) Nout[i] = (int32_t)N[i];
+  }
+}
+
 // Makes a device current for a scope.
 struct OnDevice {
   int prev = 0;
@@ -761,21 +775,16 @@ int aiwc_rf_forest_export_host(const aiwc_rf_forest* f, int32_t forest_index, in
         N.resize(cnt);
         AIWC_HIP(hipMemcpy(words.data(), f->nodes.p + base, sizeof(uint64_t) * cnt, hipMemcpyDeviceToHost));
         AIWC_HIP(hipMemcpy(N.data(), f->node_N.p + base, sizeof(uint32_t) * cnt, hipMemcpyDeviceToHost));
-        for (size_t i = 0; i < cnt; ++i, ++out) {
-          const uint64_t v = words[i];
-          const bool leaf = node_col(v) == kLeafCol;
-          if (col_host) col_host[out] = (uint8_t)node_col(v);
-          if (bin_host) bin_host[out] = leaf ? 0 : (uint8_t)node_bin(v);
-          if (left_host) left_host[out] = leaf ? -1 : (int32_t)node_left(v);
-          if (q_host) q_host[out] = leaf ? node_q(v) : 0;
-          if (N_host) N_host[out] = (int32_t)N[i];
-        }
+        unpack_nodes(words.data(), N.data(), cnt, col_host ? col_host + out : nullptr, bin_host ? bin_host + out : nullptr,
+                     left_host ? left_host + out : nullptr, q_host ? q_host + out : nullptr,
+                     N_host ? N_host + out : nullptr);
+        out += (int64_t)cnt;
       }
     };
-    if (nn.size() == 1 || all <= (nn.size() == 2 ? 49152 : nn.size() <= 4 ? 16384 : 0)) {
+    if (nn.size() == 1 || all <= (nn.size() == 2 ? 131072 : nn.size() <= 4 ? 16384 : 0)) {
       // (one tree 66 us, by the slices below 144, of 27000 nodes 105 and 143; two of
-      // 12000 118 and 141, of 27000 equal; three of 12000 154 and 150, of 2000 nodes
-      // about as long either way)
+      // 12000 118 and 141, of 50000 151 and 156; three of 12000 154 and 150, of 2000
+      // nodes about as long either way)
       take_trees(0, (int32_t)nn.size(), 0);
       return;
     }
