@@ -858,7 +858,7 @@ int aiwc_rf_predict(const aiwc_rf_forest* f, int32_t forest_index, const uint8_t
     const int32_t nt = f->params[forest_index].num_trees;
     const int64_t t0 = f->first_task[forest_index];
     require_fitted(f);
-    DevBuf<int64_t> sum(needs_sums(predict_route(trees_of(f, forest_index), n, nt, f->n_cols)) ? (size_t)n : 0, s);
+    DevBuf<int64_t> sum(needs_sums(predict_route(trees_of(f, forest_index), n, nt, f->n_cols, false)) ? (size_t)n : 0, s);
     launch_predict(trees_of(f, forest_index), (int32_t)t0, (int32_t)(t0 + nt), codes, n, f->n_cols, sum.p,
                    y_log10_out, nt, s);
   });
@@ -1034,7 +1034,7 @@ int aiwc_rf_select_device(const aiwc_rf_forest* f, int32_t forest_index, const u
     const int64_t t0 = f->first_task[forest_index];
     require_fitted(f);
     const int64_t rows = m * D;
-    const PredictRoute route = predict_route(trees_of(f, forest_index), rows, nt, f->n_cols);
+    const PredictRoute route = predict_route(trees_of(f, forest_index), rows, nt, f->n_cols, false);
     DevBuf<uint8_t> expanded(route == PredictRoute::kRow ? 0 : (size_t)(rows * f->n_cols), s);
     DevBuf<int64_t> sum(needs_sums(route) ? (size_t)rows : 0, s);
     DevBuf<double> times_tmp(times_out ? 0 : (size_t)rows, s);

@@ -386,7 +386,7 @@ void launch_predict(const TreesView& F, int32_t tree_begin, int32_t tree_end, co
 // selection whose (kernel, device) rows have a workgroup each needs no expanded codes.
 enum class PredictRoute { kRow, kLanes, kRowParts, kDirect, kMany };
 inline bool needs_sums(PredictRoute r) { return r != PredictRoute::kRow && r != PredictRoute::kLanes; }
-PredictRoute predict_route(const TreesView& F, int64_t n, int32_t n_trees, int32_t C);
+PredictRoute predict_route(const TreesView& F, int64_t n, int32_t n_trees, int32_t C, bool sums);  // (sums: no answers)
 // Lets a kernel take all of the device's LDS as dynamic LDS (set once per device).
 void allow_lds(const void* kernel);
 

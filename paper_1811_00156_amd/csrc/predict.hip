@@ -382,27 +382,31 @@ constexpr RouteLimits kRouteLimits[] = {
     {64, 512, 512, 1024, 352, {1200, 1448, 1448, 1024, 512}, 1200},
     {256, 352, 352, 512, 256, {1200, 860, 704, 704, 0}, 1024},
     {1024, 352, 256, 352, 256, {704, 512, 512, 224, 0}, 512},
-    {4096, 256, 176, 64, 176, {512, 352, 304, 128, 0}, 256},
+    {4096, 256, 224, 64, 208, {512, 352, 304, 128, 0}, 256},
     {16384, 128, 0, 64, 128, {512, 208, 64, 0, 0}, 256},
     {65536, 128, 0, 64, 128, {256, 176, 0, 0, 0}, 192},
     {INT32_MAX, 91, 0, 64, 128, {256, 128, 0, 0, 0}, 128}};
 
-PredictRoute predict_route(const TreesView& F, int64_t n, int32_t n_trees, int32_t C) {
+PredictRoute predict_route(const TreesView& F, int64_t n, int32_t n_trees, int32_t C, bool sums) {
   const RouteLimits* L = kRouteLimits;
   while (F.leaves >= L->leaves) ++L;
   const int64_t pairs = (n * n_trees + 1023) / 1024;
+  // the pairs that one launch of a workgroup per row or lanes is held against: sums
+  // alone take two launches otherwise, not three, so it saves half as much (18858 rows
+  // x 22 trees of 790 leaves: lanes 23 us, a row per thread 19)
+  const int64_t by_row = sums ? 3 * pairs / 2 : pairs, by_lanes = sums ? 2 * pairs : pairs;
   // trees grown on many rows lie far apart in memory, whatever their leaves (66183
   // rows, 1946 leaves, 547 rows x 453 trees: a workgroup per row 35 us, staged 27;
   // 23836 rows, 3575 leaves, 2364 x 92: lanes 28 us, a row per thread 22)
   const bool far = F.train_rows > 8192;
   const int group = n_trees <= 32 ? 0 : n_trees <= 64 ? 1 : n_trees <= 128 ? 2 : n_trees <= 320 ? 3 : 4;
-  const bool lanes = n_trees <= 512 && pairs <= L->lanes[group] && !(far && group > 1 && F.leaves >= 1024);
+  const bool lanes = n_trees <= 512 && by_lanes <= L->lanes[group] && !(far && group > 1 && F.leaves >= 1024);
   if (n <= 1024) {
     const int32_t row = far ? std::min(L->row, 176) : L->row;
-    if (pairs <= (n_trees <= kRowBlock ? row : n_trees <= 2 * kRowBlock ? L->row2 : 0)) return PredictRoute::kRow;
+    if (by_row <= (n_trees <= kRowBlock ? row : n_trees <= 2 * kRowBlock ? L->row2 : 0)) return PredictRoute::kRow;
   } else if (lanes) {
     return PredictRoute::kLanes;
-  } else if (n <= 4096 && n_trees <= kRowBlock && n * std::max(n_trees, 192) / 1024 <= L->rows) {
+  } else if (n <= 4096 && n_trees <= kRowBlock && n * std::max(n_trees, 192) / 1024 <= (sums ? 2 * L->rows / 3 : L->rows)) {
     return PredictRoute::kRow;
   }
   if (n <= 4096 && n_trees > kRowBlock && pairs <= L->parts) return PredictRoute::kRowParts;
@@ -439,7 +443,7 @@ void launch_select_device(const TreesView& F, int32_t tree_begin, int32_t tree_e
                           int64_t m, int32_t C, int32_t n_devices, int32_t num_trees, uint8_t* expanded, int64_t* sum,
                           double* times, int32_t* best, hipStream_t s) {
   const int64_t rows = m * n_devices;
-  if (predict_route(F, rows, tree_end - tree_begin, C) == PredictRoute::kRow) {
+  if (predict_route(F, rows, tree_end - tree_begin, C, false) == PredictRoute::kRow) {
     launch_row(F, tree_begin, tree_end, feature_codes, rows, C, n_devices, nullptr, times, num_trees, 1, s);
   } else {
     const int eb = (int)std::max<int64_t>(1, std::min<int64_t>(4096, (rows * C + 255) / 256));
@@ -526,7 +530,7 @@ void traverse_many(const TreesView& F, int32_t tree_begin, int32_t tree_end, con
 void launch_predict(const TreesView& F, int32_t tree_begin, int32_t tree_end, const uint8_t* codes, int64_t n,
                     int32_t C, int64_t* sum, double* y, int32_t num_trees, hipStream_t s) {
   if (n <= 0) return;
-  const PredictRoute route = predict_route(F, n, tree_end - tree_begin, C);
+  const PredictRoute route = predict_route(F, n, tree_end - tree_begin, C, !y);
   if (route == PredictRoute::kRow) {
     launch_row(F, tree_begin, tree_end, codes, n, C, 0, sum, y, num_trees, 1, s);
     return;

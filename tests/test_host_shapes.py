@@ -104,12 +104,13 @@ ROUTES = r"""
 #include <cstdlib>
 #include "internal.h"
 int main(int argc, char** argv) {
-  for (int i = 1; i + 5 <= argc; i += 5) {
+  for (int i = 2; i + 5 <= argc; i += 5) {
     aiwc_rf_forest f;
     f.params.push_back({1, 1, std::atoi(argv[i + 1]), 1, 1});
     f.n_train.push_back(std::atoi(argv[i]));
     const aiwc::TreesView t = aiwc::trees_of(&f, 0);
-    std::printf("%d\n", (int)aiwc::predict_route(t, std::atoi(argv[i + 2]), std::atoi(argv[i + 3]), std::atoi(argv[i + 4])));
+    std::printf("%d\n", (int)aiwc::predict_route(t, std::atoi(argv[i + 2]), std::atoi(argv[i + 3]), std::atoi(argv[i + 4]),
+                                                       std::atoi(argv[1]) != 0));
   }
 }
 """
@@ -119,8 +120,8 @@ ROW, LANES, PARTS, DIRECT, STAGED = range(5)
 def test_prediction_routes(tmp_path):
     exe = build_host(tmp_path, ROUTES)
 
-    def routes(cases):
-        return [int(v) for v in run_exe(exe, [v for c in cases for v in c]).split()]
+    def routes(cases, sums=0):
+        return [int(v) for v in run_exe(exe, [sums] + [v for c in cases for v in c]).split()]
 
     # (training rows, min.node.size, rows, trees, columns): fastest in measurements
     want = {
@@ -132,6 +133,9 @@ def test_prediction_routes(tmp_path):
         (200000, 5, 200000, 500, 65): STAGED, (2220, 5, 60000, 500, 35): STAGED, (40, 9, 40000, 500, 75): STAGED,
     }
     assert dict(zip(want, routes(list(want)))) == want
+    # sums alone are a launch less by the other routes
+    assert routes([(3158, 5, 18858, 22, 28), (300, 5, 750, 300, 20), (300, 5, 900, 300, 20)]) == [LANES, ROW, ROW]
+    assert routes([(3158, 5, 18858, 22, 28), (300, 5, 750, 300, 20), (300, 5, 900, 300, 20)], 1) == [DIRECT, ROW, LANES]
     # each route takes the fewest rows of what it is for, and none comes back
     for n_train, k, trees, C in itertools.product((30, 300, 2220, 30000, 200000), (1, 9), (1, 40, 500, 600, 1100), (5, 66)):
         seen = routes([(n_train, k, n, trees, C) for n in (1, 10, 100, 300, 1000, 2000, 4096, 5000, 20000, 100000, 10 ** 6)])
