@@ -29,6 +29,10 @@
 //      segments of the other entry buffer (wave-aggregated cursor atomics).
 // All sums are integers and the only floating point is the binary64 score, so
 // the order in which rows are visited never changes a result.
+// "The tuning grid" whose times stand in this file is one launch of 1700 forests x
+// 256 trees (2220 rows x 35 columns of 64 bins, 10 folds x mtry 1 to 34 x five
+// min.node.size); it takes 201 to 217 ms now, by the frame's seed, and the times
+// that are compared with each other are of one frame.
 #include <limits.h>
 
 #include <type_traits>

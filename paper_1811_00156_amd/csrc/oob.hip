@@ -23,11 +23,10 @@ constexpr int kOobBlock = 256;
 // It lists the rows that the tree left out (a bitmap word per 64 rows), so that
 // every lane walks a row of it, K rows per lane at a time, with the tree's first
 // nodes in the wave's part of the LDS.  One thread per row and forest walking
-// every tree in turn, codes and nodes gathered from memory, took 11.7 ms for the
-// paper's frame and 2000 trees (nine workgroups) and 19.5 ms for the tuning
-// grid's 1700 forests; now 0.13 and 5.6 ms, bound by the latency of the walk's
-// dependent reads (128 nodes per tree in the LDS; 256 and 512 cost waves: 6.8
-// and 8.9 ms).
+// every tree in turn, codes and nodes gathered from memory, took 11.7 ms for 2000
+// trees on 2220 rows (nine workgroups) and 19.5 ms for the tuning grid's 1700
+// forests; now 0.06 and 7.2 ms, bound by the latency of the walk's dependent reads
+// (128 nodes per tree in the LDS; 256 and 512 cost waves: 1.2 and 1.6 times as long).
 constexpr int kScoreWaves = 8;
 constexpr uint32_t kScoreTop = 128;
 
@@ -223,7 +222,7 @@ void launch_score(const TreesView& T, const TreeTask* tasks, const uint64_t* inb
 
 // A wave walks its rows 128 at a time (two per lane): a workgroup takes 128 held-out
 // rows, or 512 training rows, of which a tree left a third out (the tuning grid's
-// out-of-bag scores: 5.6 ms with 512 rows, 6.6 with 256, 8.3 with 1024).  Waves
+// out-of-bag scores, the whole call: 6.8 ms with 512 rows, 7.9 with 256, 8.4 with 1024).  Waves
 // that would have no tree of their own share one: eight waves a single tree's rows,
 // four the rows of two.  And while the launch has less than eight waves per CU
 // with a tree to walk, a workgroup takes half the rows.  Always 512 rows and a wave

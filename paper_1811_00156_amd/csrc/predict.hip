@@ -4,7 +4,8 @@
 // right; the leaf values of its trees add up as exact int64.  Many rows: a
 // workgroup per (row block, tree chunk), rows and the trees' upper levels in
 // the LDS; partial sums of different chunks meet in a 64-bit integer atomic
-// add, which is exact in any order.  Few rows: a workgroup per row.
+// add, which is exact in any order.  Fewer: a row per thread with codes and nodes
+// where they are, lanes of a row, or workgroups of a row (predict_route).
 #include <map>
 #include <mutex>
 
@@ -29,7 +30,7 @@ __device__ __align__(256) unsigned long long scratch[kNoAllocPredictRows];
 // turn by all of its workgroups, an XCD's L2 holds the trees in use.  Before,
 // codes and nodes were both gathered from memory (200000 rows x 65 columns, 500
 // trees of 200000 rows: 9.7 ms, the address unit 84 % busy and 5.1e8 cache lines
-// missing the L2); now 1.9 ms, bound by the latency of the dependent reads, so
+// missing the L2); now 1.9 to 2.0 ms, bound by the latency of the dependent reads, so
 // that workgroups are small (256 threads waited less at the barriers than 512 or
 // 1024: 1.9, 2.3 and 2.5 ms) and one row per thread with up to 32 waves per CU
 // beats two or four rows with fewer waves (2.9 and 4.3 ms).
